@@ -1321,10 +1321,10 @@ __global__ __launch_bounds__(kRansacThreads) void k_vpx_ransac(Dev d, const uint
 // M_1 = Sobel-x of M_0 (Alg. "Lane position validation"), and the energy of every candidate
 // along its track (Eq. lane_energy, Eq. lane_visualisation).
 //
-// One workgroup per frame.  First q is computed for every road edge (each wave a group of rows)
-// into a per-edge buffer.  Then the road rows are swept upwards.  At the step of row v every
+// One workgroup of BT threads per frame.  First q is computed for every road edge (each wave a
+// group of rows) into a per-edge buffer.  Then the road rows are swept upwards.  At the step of row v every
 // thread pushes its NC columns (consecutive when NC is odd, a stride coprime with the LDS
-// banks; else t, t + 256, ...) of the dense q row v-4 (scattered into LDS during the previous
+// banks; else t, t + BT, ...) of the dense q row v-4 (scattered into LDS during the previous
 // step) into a 9-row register ring (rows v-4..v+4) and forms V(x, v) = sum_y s_y C(x, v+y),
 // C = vertical 7-row sums, with the zero padding of M_0 outside the image (a uniform branch:
 // rows strictly inside take both neighbours without a select), while the edges of row v-5 are
@@ -1333,7 +1333,7 @@ __global__ __launch_bounds__(kRansacThreads) void k_vpx_ransac(Dev d, const uint
 // few edge lanes only; consecutive columns share their three-column sums) into one of two LDS
 // rows, and every candidate adds M_1 at its track column of row v+1.  The q, V and M_1 rows are
 // double-buffered by row parity, so one barrier per row orders every write before its reads.
-// Rows are padded to the NC * 256 columns the threads own (the columns past W hold zeros), so
+// Rows are padded to the NC * BT columns the threads own (the columns past W hold zeros), so
 // the column loops carry no bounds test.  The row loop is unrolled nine times so that the ring
 // rotates by renaming registers instead of moving them.
 // mode 0 / 1: G_x w_g with the exponent as printed / squared; mode 2: the prior work's vote
@@ -1353,26 +1353,26 @@ __device__ __forceinline__ float edge_q(const ld_edge& ed, int r, double vx, dou
     return (float)ed.gx * w;
 }
 
-template <int NC, int NT>
-__global__ __launch_bounds__(kBlock) void k_energy(Dev d, const uint8_t* cand_mask, float* energy_out) {
-    extern __shared__ float fsm[];
+template <int NC, int NT, int BT, int PD>
+__global__ __launch_bounds__(BT) void k_energy(Dev d, const uint8_t* cand_mask, float* energy_out, int stage_off) {
+    extern __shared__ __attribute__((aligned(16))) float fsm[];
     const int b = blockIdx.x, t = threadIdx.x, lane = lane_id(), wave = t / kWave;
     if (frame_masked(d, b)) return;
     const int W = d.W, H = d.H, W2 = d.W2, v_max = H - 1;
     const FrameInfo fi = d.info[b];
     double* Eout = d.energy + (int64_t)b * W2;
     if (fi.flags & (LD_FLAG_NOROAD | LD_FLAG_NOVP)) {
-        for (int i = t; i < W2; i += kBlock) {
+        for (int i = t; i < W2; i += BT) {
             Eout[i] = 0.0;
             if (energy_out) energy_out[(int64_t)b * W2 + i] = 0.0f;
         }
         return;
     }
-    constexpr int WP = NC * kBlock;  // columns owned by the threads (>= W)
+    constexpr int WP = NC * BT;  // columns owned by the threads (>= W)
     // a thread owns NC consecutive columns when NC is odd (a stride coprime with the LDS banks),
-    // else columns t, t + 256, ...
+    // else columns t, t + BT, ...
     constexpr bool kConsec = NC % 2 == 1;
-    auto col = [&](int k) { return kConsec ? t * NC + k : t + k * kBlock; };
+    auto col = [&](int k) { return kConsec ? t * NC + k : t + k * BT; };
     // by row parity: dense q rows; V rows, column u at u + 2 (two zero columns each side); M_1
     // rows (entries >= W stay 0)
     auto qb = [&](int par) -> float* { return fsm + par * WP; };
@@ -1394,7 +1394,7 @@ __global__ __launch_bounds__(kBlock) void k_energy(Dev d, const uint8_t* cand_ma
     // lane (i = lane, lane + 64) of each, every load of the group issued before any q is
     // formed (clamped to the row's W slots; the counts mask them); longer rows go on in a loop
     constexpr int kQRows = 4;
-    for (int r0 = v_h + wave * kQRows; r0 <= v_max; r0 += (kBlock / kWave) * kQRows) {
+    for (int r0 = v_h + wave * kQRows; r0 <= v_max; r0 += (BT / kWave) * kQRows) {
         int cnt[kQRows];
         double vx[kQRows], vy[kQRows];
         ld_edge e0[kQRows], e1[kQRows];
@@ -1416,7 +1416,17 @@ __global__ __launch_bounds__(kBlock) void k_energy(Dev d, const uint8_t* cand_ma
                 qbuf[(int64_t)r * W + i] = edge_q(edges[(int64_t)r * W + i], r, vx[j], vy[j], inv_sg2, sq);
         }
     }
-    for (int i = t; i < 6 * WP + 10; i += kBlock) fsm[i] = 0.0f;
+    for (int i = t; i < 6 * WP + 10; i += BT) fsm[i] = 0.0f;
+    // the track coefficients and edge counts of the swept rows, in LDS when they fit (stage_off
+    // > 0): a row's scalar loads would otherwise be waited for at its barrier
+    double2* sAB = reinterpret_cast<double2*>(fsm + stage_off);
+    int* scnt = reinterpret_cast<int*>(sAB + H);
+    const bool staged = stage_off > 0;
+    if (staged)
+        for (int r = v_h + t; r <= v_max; r += BT) {
+            sAB[r] = r < v_max ? make_double2(tA[r], tB[r]) : make_double2(0.0, 1.0);
+            scnt[r] = rowcnt[r];
+        }
     float ring[NC][9];
 #pragma unroll
     for (int k = 0; k < NC; ++k)
@@ -1426,28 +1436,34 @@ __global__ __launch_bounds__(kBlock) void k_energy(Dev d, const uint8_t* cand_ma
     bool live[NT];
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
-        const int i = t + k * kBlock;
+        const int i = t + k * BT;
         uu[k] = (double)(i - d.half);
         ee[k] = 0.0;
         live[k] = i < W2 && (cand_mask == nullptr || cand_mask[(int64_t)b * W2 + i] != 0);
     }
     __syncthreads();
 
-    // the next row to scatter: its count and each thread's first edge are loaded a step ahead
-    // (from a clamped, always valid index; the count masks them when they are used)
-    int nx_r = -1, nx_cnt = 0, nx_u = 0;
-    float nx_q = 0.0f;
-    auto prefetch = [&](int r) {
-        const int rr = min(max(r, 0), v_max), i = min(t, W - 1);
-        nx_r = r;
-        nx_cnt = (r >= v_h && r <= v_max) ? rowcnt[rr] : 0;
-        nx_u = edges[(int64_t)rr * W + i].u;
-        nx_q = qbuf[(int64_t)rr * W + i];
+    // the next PD rows to scatter: each thread's first edge of row r waits in slot
+    // (v_max - r) mod PD, loaded PD steps ahead (from a clamped, always valid index; the row's
+    // count masks it when it is used)
+    int nx_u[PD];
+    float nx_q[PD];
+    auto count = [&](int r) -> int {
+        if (r < v_h || r > v_max) return 0;
+        return staged ? scnt[r] : rowcnt[r];
     };
-    auto scatter_next = [&](float* q) {
-        if (t < nx_cnt) q[nx_u] = nx_q;
-        for (int i = t + kBlock; i < nx_cnt; i += kBlock)
-            q[edges[(int64_t)nx_r * W + i].u] = qbuf[(int64_t)nx_r * W + i];
+    auto prefetch = [&](auto slot, int r) {
+        constexpr int K = decltype(slot)::value;
+        const int rr = min(max(r, 0), v_max), i = min(t, W - 1);
+        nx_u[K] = edges[(int64_t)rr * W + i].u;
+        nx_q[K] = qbuf[(int64_t)rr * W + i];
+    };
+    auto scatter = [&](auto slot, int r, float* q) {
+        constexpr int K = decltype(slot)::value;
+        const int n = count(r);
+        if (t < n) q[nx_u[K]] = nx_q[K];
+        for (int i = t + BT; i < n; i += BT)
+            q[edges[(int64_t)r * W + i].u] = qbuf[(int64_t)r * W + i];
     };
     // slot S of the ring takes the newest row; reads and re-zeroes the owned columns of q
     auto push = [&](auto Sc, float* q) {
@@ -1466,9 +1482,15 @@ __global__ __launch_bounds__(kBlock) void k_energy(Dev d, const uint8_t* cand_ma
     // A_w, B_w are loaded one step before their row's turn (fma(1, u, 0) = u for w = v_max).
     double cA = 0.0, cB = 1.0;
     auto coef = [&](int w) {
-        const bool upd = w < v_max;
-        cA = upd ? tA[w] : 0.0;
-        cB = upd ? tB[w] : 1.0;
+        if (staged) {
+            const double2 ab = sAB[w];
+            cA = ab.x;
+            cB = ab.y;
+        } else {
+            const bool upd = w < v_max;
+            cA = upd ? tA[w] : 0.0;
+            cB = upd ? tB[w] : 1.0;
+        }
     };
     auto candidates = [&](const float* m1row) {
         const double A = cA, Bc = cB;
@@ -1482,18 +1504,21 @@ __global__ __launch_bounds__(kBlock) void k_energy(Dev d, const uint8_t* cand_ma
     };
     // rows v_max .. v_max-3 enter slots 0, 8, 7, 6; rows below the image stay zero; row
     // v_max-4 waits in its q row for the first step
-    prefetch(v_max);
-    scatter_next(qb(v_max & 1));               __syncthreads(); push(IntC<0>{}, qb(v_max & 1));
-    prefetch(v_max - 1);
-    scatter_next(qb((v_max - 1) & 1));         __syncthreads(); push(IntC<8>{}, qb((v_max - 1) & 1));
-    prefetch(v_max - 2);
-    scatter_next(qb((v_max - 2) & 1));         __syncthreads(); push(IntC<7>{}, qb((v_max - 2) & 1));
-    prefetch(v_max - 3);
-    scatter_next(qb((v_max - 3) & 1));         __syncthreads(); push(IntC<6>{}, qb((v_max - 3) & 1));
-    prefetch(v_max - 4);
-    scatter_next(qb((v_max - 4) & 1));
-    prefetch(v_max - 5);
-    __syncthreads();
+    auto enter = [&](auto kc, auto Sc) {                  // row v_max - k
+        constexpr int K = decltype(kc)::value;
+        scatter(IntC<K % PD>{}, v_max - K, qb((v_max - K) & 1));
+        prefetch(IntC<K % PD>{}, v_max - K - PD);
+        __syncthreads();
+        if constexpr (K < 4) push(Sc, qb((v_max - K) & 1));
+    };
+    prefetch(IntC<0>{}, v_max);
+    if constexpr (PD > 1) prefetch(IntC<1 % PD>{}, v_max - 1);
+    if constexpr (PD > 2) prefetch(IntC<2 % PD>{}, v_max - 2);
+    enter(IntC<0>{}, IntC<0>{});
+    enter(IntC<1>{}, IntC<8>{});
+    enter(IntC<2>{}, IntC<7>{});
+    enter(IntC<3>{}, IntC<6>{});
+    enter(IntC<4>{}, IntC<5>{});
     int v = v_max;
     // one row: newest ring slot S holds row v-4, slot (S + j) % 9 row v-4+j
     auto step = [&](auto Sc) -> bool {
@@ -1527,8 +1552,9 @@ __global__ __launch_bounds__(kBlock) void k_energy(Dev d, const uint8_t* cand_ma
             }
         };
         if (up && dn) vcol(std::bool_constant<true>{}); else vcol(std::bool_constant<false>{});
-        scatter_next(qb(par ^ 1));       // row v - 5
-        prefetch(v - 6);
+        // row v - 5 (v = v_max - (5 - S) modulo 9, and PD divides 9)
+        scatter(IntC<(10 - S) % PD>{}, v - 5, qb(par ^ 1));
+        prefetch(IntC<(10 - S) % PD>{}, v - 5 - PD);
         __syncthreads();
         float* mrow = mb(par);
         const float* vr = Vp(par);
@@ -1573,11 +1599,216 @@ __global__ __launch_bounds__(kBlock) void k_energy(Dev d, const uint8_t* cand_ma
     }
 #pragma unroll
     for (int k = 0; k < NT; ++k) {
-        const int i = t + k * kBlock;
+        const int i = t + k * BT;
         if (i < W2) {
             Eout[i] = ee[k];
             if (energy_out) energy_out[(int64_t)b * W2 + i] = (float)ee[k];
         }
+    }
+}
+
+// The same energies by two launches, for up to kSplitFrames frames: k_m1 forms M_1 of every
+// track row (in the q buffer, which is a frame's size), k_tracks follows the tracks, a candidate
+// a thread.  Every sum is taken in the order of k_energy, so the energies are the same bits.
+// Neither has a chain over the rows with a barrier a row: 1242 x 375, one frame, 187 us by
+// k_energy, 4 + 15 us by these two.
+//
+// k_m1: a workgroup takes kM1Rows rows of M_1 and kM1Waves x kM1Cols columns.  The edges on
+// those rows and four more either side are listed (a row has few in these columns, so q formed
+// row by row would run mostly empty waves), their q scattered into a dense LDS tile; then each
+// wave takes 64 columns (two of halo either side) down the tile with its rows of q in registers,
+// the neighbours' V by wave shifts, so no V is stored.  A wave without an edge in its columns
+// writes zeros.  Bound by its loads' latency (info, then edges; five workgroups a CU by LDS) and
+// the M_1 write: 256 frames 0.27 GB in 128 us.
+constexpr int kM1Rows = 16, kM1Cols = 60, kM1Waves = 4;
+constexpr int kM1Halo = 4;                                   // rows of q above and below
+constexpr int kM1List = 1024;                                // listed edges of a tile
+constexpr int kM1Span = kM1Waves * kM1Cols + 4;              // columns of the LDS tile
+
+__device__ __forceinline__ float wave_next0(float x) {       // lane l + 1's x, 0 on lane 63
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x130, 0xF, 0xF, true));
+}
+__device__ __forceinline__ float wave_prev0(float x) {       // lane l - 1's x, 0 on lane 0
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0x138, 0xF, 0xF, true));
+}
+
+__global__ __launch_bounds__(kM1Waves * kWave) void k_m1(Dev d) {
+    constexpr int kTileRows = kM1Rows + 2 * kM1Halo, kT = kM1Waves * kWave;
+    __shared__ __attribute__((aligned(16))) float q[kTileRows][kM1Span];
+    __shared__ uint2 list[kM1List];
+    __shared__ double sv[kTileRows][2];
+    __shared__ int act[kM1Waves], s_n;
+    const int b = blockIdx.z, t = threadIdx.x, lane = lane_id(), wave = t / kWave;
+    if (frame_masked(d, b)) return;
+    const FrameInfo fi = d.info[b];
+    if (fi.flags & (LD_FLAG_NOROAD | LD_FLAG_NOVP)) return;
+    const int W = d.W, H = d.H, v_max = H - 1, v_h = fi.v_h;
+    const int v0 = fi.v_end + blockIdx.y * kM1Rows, u0 = blockIdx.x * (kM1Waves * kM1Cols) - 2;
+    if (v0 > v_max) return;
+    // the wave's rows of the tile: the counts and the first 64 edges of each in flight at once
+    constexpr int kPer = (kTileRows + kM1Waves - 1) / kM1Waves;
+    const ld_edge* edges = d.edges + (int64_t)b * H * W;
+    int cnt[kPer];
+    uint2 e0[kPer];
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int r = v0 - kM1Halo + wave + j * kM1Waves, rc = min(max(r, 0), v_max);
+        cnt[j] = d.rowcnt[(int64_t)b * H + rc];
+        e0[j] = reinterpret_cast<const uint2*>(edges + (int64_t)rc * W)[min(lane, W - 1)];
+        if (r != rc || r < v_h || wave + j * kM1Waves >= kTileRows) cnt[j] = 0;
+    }
+    static_assert(kTileRows * kM1Span % 4 == 0, "the tile is cleared by 16-byte stores");
+    for (int i = t; i < kTileRows * kM1Span / 4; i += kT) reinterpret_cast<float4*>(&q[0][0])[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if (t < kM1Waves) act[t] = 0;
+    if (t == 0) s_n = 0;
+    if (t < kTileRows) {
+        const double* tv = d.tab + (int64_t)b * 6 * H + 2 * H + min(max(v0 - kM1Halo + t, 0), v_max);
+        sv[t][0] = tv[H];      // V_px
+        sv[t][1] = tv[0];      // V_py
+    }
+    __syncthreads();
+    const float inv_sg2 = (float)(1.0 / (d.P.sigma_g * d.P.sigma_g));
+    const int sq = d.P.vote ? 2 : d.P.weight_squared;
+    auto place = [&](uint2 w, int row) {
+        ld_edge e;
+        e.u = (int16_t)(w.x & 0xFFFFu);
+        e.gx = (int16_t)(w.x >> 16);
+        e.gy = (int16_t)(w.y & 0xFFFFu);
+        e.bin = 0;
+        const int x = e.u - u0;
+        q[row][x] = edge_q(e, v0 - kM1Halo + row, sv[row][0], sv[row][1], inv_sg2, sq);
+        const int k = x / kM1Cols;                            // columns 60 k .. 60 k + 63 belong to wave k
+        if (k < kM1Waves) act[k] = 1;
+        if (x % kM1Cols < 4 && k > 0) act[k - 1] = 1;
+    };
+    // the tile's edges are listed first, so that q is formed by full waves (a row holds few of
+    // this tile's columns); the edges past the list's end are placed at once
+#pragma unroll
+    for (int j = 0; j < kPer; ++j) {
+        const int row = wave + j * kM1Waves;
+        for (int i0 = 0; i0 < cnt[j]; i0 += kWave) {
+            uint2 e = e0[j];
+            if (i0 > 0) e = reinterpret_cast<const uint2*>(edges + (int64_t)(v0 - kM1Halo + row) * W)[min(i0 + lane, W - 1)];
+            const int x = (int)(int16_t)(e.x & 0xFFFFu) - u0;
+            const bool on = i0 + lane < cnt[j] && (unsigned)x < (unsigned)kM1Span;
+            const uint64_t m = __ballot(on);
+            if (m != 0) {
+                int base = 0;
+                if (lane == 0) base = atomicAdd(&s_n, __popcll(m));
+                const int slot = __builtin_amdgcn_readfirstlane(base) + __popcll(m & lanes_below());
+                e.y = (e.y & 0xFFFFu) | ((uint32_t)row << 16);
+                if (on && slot < kM1List) list[slot] = e;
+                else if (on) place(e, row);
+            }
+        }
+    }
+    __syncthreads();
+    const int n = min(s_n, kM1List);
+    for (int i = t; i < n; i += kT) {
+        const uint2 e = list[i];
+        place(e, (int)(e.y >> 16));
+    }
+    __syncthreads();
+    const int u = u0 + wave * kM1Cols + lane;                 // lanes 2 .. 61 write their column
+    const bool mine = lane >= 2 && lane < 2 + kM1Cols && u < W;
+    float* out = d.qbuf + (int64_t)b * H * W + u;
+    const int rows = min(kM1Rows, v_max - v0 + 1);
+    if (!act[wave]) {
+        if (mine)
+            for (int i = 0; i < rows; ++i) out[(int64_t)(v0 + i) * W] = 0.0f;
+        return;
+    }
+    float r[kTileRows];
+#pragma unroll
+    for (int j = 0; j < kTileRows; ++j) r[j] = q[j][wave * kM1Cols + lane];
+#pragma unroll
+    for (int i = 0; i < kM1Rows; ++i) {
+        const int v = v0 + i;
+        if (v > v_max) break;
+        const float s5 = (((r[i + 2] + r[i + 3]) + r[i + 4]) + r[i + 5]) + r[i + 6];
+        const float cm1 = (r[i] + r[i + 1]) + s5;
+        const float c0 = (r[i + 1] + s5) + r[i + 7];
+        const float cp1 = (s5 + r[i + 7]) + r[i + 8];
+        float V = 2.0f * c0;
+        V += v >= 1 ? cm1 : 0.0f;
+        V += v + 1 <= v_max ? cp1 : 0.0f;
+        const float n1 = wave_next0(V), g1 = (V + n1) + wave_next0(n1);   // V(u) + V(u+1) + V(u+2)
+        const float g2 = wave_prev0(wave_prev0(g1));                       // V(u-2) + V(u-1) + V(u)
+        float m1 = g1 - g2;
+        if (u < 1 || u >= W - 1) m1 = (u + 1 <= W - 1 ? g1 : 0.0f) - (u >= 1 ? g2 : 0.0f);
+        if (mine) out[(int64_t)v * W] = m1;
+    }
+}
+
+// k_tracks: one candidate a thread, one wave a workgroup (a frame spreads over 2W / 64 of them).
+// The columns of kTrackRows rows are found first, then their M_1 loads are issued together and
+// added in row order, the next rows' columns and loads going on meanwhile.  A row is read through
+// a buffer resource that ends with it, so a column outside the image reads 0.  Issue bound with
+// many frames (1024: 245 us, about ten operations a row and candidate), with few by the chain of
+// 13 groups of loads (one frame 15 us).
+constexpr int kTrackRows = 16;
+
+__global__ __launch_bounds__(kWave) void k_tracks(Dev d, const uint8_t* cand_mask, float* energy_out) {
+    const int b = blockIdx.y, i = blockIdx.x * kWave + threadIdx.x;
+    if (frame_masked(d, b)) return;
+    const int W = d.W, H = d.H, W2 = d.W2, v_max = H - 1;
+    const FrameInfo fi = d.info[b];
+    const bool in = i < W2;
+    const bool live = in && (cand_mask == nullptr || cand_mask[(int64_t)b * W2 + i] != 0);
+    double ee = 0.0;
+    if (!(fi.flags & (LD_FLAG_NOROAD | LD_FLAG_NOVP)) && __any(live)) {
+        const int v_end = __builtin_amdgcn_readfirstlane(fi.v_end);
+        const double* __restrict__ tA = d.tab + (int64_t)b * 6 * H + 4 * H;
+        const double* __restrict__ tB = tA + H;
+        float* base = d.qbuf + (int64_t)b * H * W;
+        double uu = (double)(i - d.half);
+        // rows top .. top - kTrackRows + 1; with tail set some of them lie below v_end or all do:
+        // nothing is read there and 0 is added
+        auto fetch = [&](auto tail, int top, float (&m)[kTrackRows]) {
+            constexpr bool kTail = decltype(tail)::value;
+            double A[kTrackRows], B[kTrackRows];
+#pragma unroll
+            for (int j = 0; j < kTrackRows; ++j) {
+                const int v = kTail ? max(top - j, 0) : top - j;
+                A[j] = tA[v];
+                B[j] = tB[v];
+            }
+#pragma unroll
+            for (int j = 0; j < kTrackRows; ++j) {
+                const int v = top - j, row = (kTail ? max(v, v_end) : v) * W;
+                uu = fma(B[j], uu, A[j]);
+                const unsigned c = min((unsigned)(int)floor(uu + 0.5), (unsigned)W);
+                const __amdgpu_buffer_rsrc_t rs =
+                    __builtin_amdgcn_make_buffer_rsrc(base, 0, !kTail || v >= v_end ? (row + W) * 4 : 0, 0x00020000);
+                m[j] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (int)(c * 4u), row * 4, 0));
+            }
+        };
+        auto fetch_at = [&](int top, float (&m)[kTrackRows]) {
+            if (top - kTrackRows + 1 >= v_end) fetch(std::false_type{}, top, m);
+            else fetch(std::true_type{}, top, m);
+        };
+        auto add = [&](const float (&m)[kTrackRows]) {
+#pragma unroll
+            for (int j = 0; j < kTrackRows; ++j) ee += (double)m[j];
+        };
+        // row v_max: the start column itself
+        {
+            const int c = i - d.half;
+            ee = (unsigned)c < (unsigned)W ? (double)base[v_max * W + c] : 0.0;
+        }
+        float ma[kTrackRows], mb[kTrackRows];
+        fetch_at(v_max - 1, ma);
+        for (int v = v_max - 1; v >= v_end; v -= 2 * kTrackRows) {
+            fetch_at(v - kTrackRows, mb);
+            add(ma);
+            fetch_at(v - 2 * kTrackRows, ma);
+            add(mb);
+        }
+    }
+    if (in) {
+        if (!live) ee = 0.0;
+        d.energy[(int64_t)b * W2 + i] = ee;
+        if (energy_out) energy_out[(int64_t)b * W2 + i] = (float)ee;
     }
 }
 
@@ -2328,7 +2559,7 @@ size_t edges_lds(int nwaves) {
     return (sizeof(double) + 3 * sizeof(uint32_t)) * kEdgeStrip + sizeof(uint2) * kEdgeQueue * (size_t)nwaves;
 }
 
-size_t energy_lds(int nc) { return sizeof(float) * (6 * (size_t)nc * kBlock + 10); }
+size_t energy_lds(int columns) { return sizeof(float) * (6 * (size_t)columns + 10); }
 
 // Raise a kernel's dynamic LDS limit once per size (later launches, including those recorded
 // into a captured graph, issue nothing but the launch).
@@ -2540,26 +2771,59 @@ ld_status run_vp(ld_frame f, const uint8_t* grey, int64_t gp, const void* disp, 
     return s;
 }
 
-template <int NC, int NT>
+template <int NC, int NT, int BT, int PD>
 void launch_energy(ld_frame f, const Dev& d, const uint8_t* mask, float* eout, hipStream_t st) {
-    const size_t l = energy_lds(NC);
-    allow_lds(k_energy<NC, NT>, l);
-    hipLaunchKernelGGL((k_energy<NC, NT>), dim3(f->active), dim3(kBlock), l, st, d, mask, eout);
+    static_assert(9 % PD == 0, "the unrolled sweep rotates the prefetch slots by renaming");
+    const size_t base = (energy_lds(NC * BT) + 15) / 16 * 16, rows = (size_t)d.H * (sizeof(double) * 2 + sizeof(int));
+    const bool staged = base + rows <= (size_t)kMaxLds;
+    const size_t l = staged ? base + rows : base;
+    allow_lds(k_energy<NC, NT, BT, PD>, l);
+    hipLaunchKernelGGL((k_energy<NC, NT, BT, PD>), dim3(f->active), dim3(BT), l, st, d, mask, eout,
+                       staged ? (int)(base / sizeof(float)) : 0);
 }
+
+// Which form of the energies a launch takes (us of the step; 1242 x 375 and, after the slash,
+// 1920 x 1080 frames with u16 disparity):
+//   frames          1     61    128     192     256     384    512    1024
+//   two launches  24/51   59   109/412 163/591 206/785  322   426     806
+//   k_energy 512    -      -   189/602 194/614 198/617  257   262/914  515
+//   k_energy 256  187/740 201  218/828 223/836 225/837  257   260/1047 388
+// A frame's sweep is one workgroup with a barrier a row, so below about a workgroup per CU its
+// time is its latency; the two launches use the whole chip for any number of frames but move
+// M_1 through memory (R W floats a frame, written and read).  Past kSplitFrames that costs more
+// than the sweep.  With one or two frames per CU the sweep is shortest with 512 threads (two
+// waves a SIMD, edges loaded three rows ahead); with four, 256 threads issue less for the same
+// columns.  Above 1536 columns 256 threads would own 8 and more columns each (192 VGPRs, two
+// workgroups a CU): 512 threads there for every number of frames.
+constexpr int kSplitFrames = 192, kWideFrames = 384, kWideColumns = 1536;
 
 ld_status run_energy(ld_frame f, const uint8_t* mask, float* eout, hipStream_t st, const Dev* dsel = nullptr) {
     ProfScope ps(f, 4, st);
     const Dev& d = dsel ? *dsel : f->d;
+    if (f->active <= kSplitFrames) {
+        const int cols = kM1Waves * kM1Cols;
+        const dim3 g1((d.W + cols - 1) / cols, (d.H + kM1Rows - 1) / kM1Rows, f->active);
+        hipLaunchKernelGGL(k_m1, g1, dim3(kM1Waves * kWave), 0, st, d);
+        hipLaunchKernelGGL(k_tracks, dim3((d.W2 + kWave - 1) / kWave, f->active), dim3(kWave), 0, st, d, mask, eout);
+        return launch_ok();
+    }
+    if (f->active <= kWideFrames || d.W > kWideColumns) {
+        const int nc = (d.W + 511) / 512;
+        if (nc <= 1) launch_energy<1, 2, 512, 3>(f, d, mask, eout, st);
+        else if (nc <= 2) launch_energy<2, 4, 512, 3>(f, d, mask, eout, st);
+        else if (nc <= 3) launch_energy<3, 6, 512, 3>(f, d, mask, eout, st);
+        else if (nc <= 4) launch_energy<4, 8, 512, 3>(f, d, mask, eout, st);
+        else if (nc <= 6) launch_energy<6, 12, 512, 3>(f, d, mask, eout, st);
+        else launch_energy<8, 16, 512, 3>(f, d, mask, eout, st);
+        return launch_ok();
+    }
     const int nc = (d.W + kBlock - 1) / kBlock;
-    if (nc <= 1) launch_energy<1, 2>(f, d, mask, eout, st);
-    else if (nc <= 2) launch_energy<2, 4>(f, d, mask, eout, st);
-    else if (nc <= 3) launch_energy<3, 6>(f, d, mask, eout, st);
-    else if (nc <= 4) launch_energy<4, 8>(f, d, mask, eout, st);
-    else if (nc <= 5) launch_energy<5, 10>(f, d, mask, eout, st);
-    else if (nc <= 6) launch_energy<6, 12>(f, d, mask, eout, st);
-    else if (nc <= 8) launch_energy<8, 16>(f, d, mask, eout, st);
-    else if (nc <= 12) launch_energy<12, 24>(f, d, mask, eout, st);
-    else launch_energy<16, 32>(f, d, mask, eout, st);
+    if (nc <= 1) launch_energy<1, 2, kBlock, 1>(f, d, mask, eout, st);
+    else if (nc <= 2) launch_energy<2, 4, kBlock, 1>(f, d, mask, eout, st);
+    else if (nc <= 3) launch_energy<3, 6, kBlock, 1>(f, d, mask, eout, st);
+    else if (nc <= 4) launch_energy<4, 8, kBlock, 1>(f, d, mask, eout, st);
+    else if (nc <= 5) launch_energy<5, 10, kBlock, 1>(f, d, mask, eout, st);
+    else launch_energy<6, 12, kBlock, 1>(f, d, mask, eout, st);
     return launch_ok();
 }
 
