@@ -43,6 +43,7 @@ struct FrameInfo {
 
 constexpr int kMaxRounds = 64;
 constexpr int kBig = 0x3FFFFFFF;
+constexpr int kCUs = 256;              // compute units of one GPU
 constexpr int kMaxLds = 160 * 1024;   // LDS bytes a workgroup may hold on gfx950
 
 // Device view of a frame object: sizes, parameters and the scratch carried between steps.
@@ -954,8 +955,7 @@ __global__ __launch_bounds__(1024) void k_edges(Dev d, const uint8_t* grey, int6
 // S6 + S7 + S8: band accumulator m_x (Alg. "Dense V_px accumulation", a band of 2 chi + 1 rows
 // clipped to the road), DP path over the 2W vote columns (Eq. dense_vpx_estimation), RANSAC
 // quartic gamma (Alg. "gamma estimation"), V_px table (Eq. vpx_estimation) and the
-// coefficients of the lane track of Eq. lane_visualisation.  One workgroup per frame, one
-// thread per run of kDpRun consecutive columns.
+// coefficients of the lane track of Eq. lane_visualisation.  One workgroup per frame.
 //
 // DP step.  The value E + lambda|tau| and the tie rank of tau in the scan order
 // 0, -1, +1, -2, +2, ... (0..10) are packed into one key (value << 4 | rank): the minimum key
@@ -964,35 +964,11 @@ __global__ __launch_bounds__(1024) void k_edges(Dev d, const uint8_t* grey, int6
 // Sh(c') - (16 lambda + 2) c' + ((16 lambda + 2) c - 1) and of tau = +a is
 // Sh(c') + (16 lambda + 2) c' - (16 lambda + 2) c (c' = c + tau), so each side is a plain
 // minimum of a per-column term over a window, plus a per-c constant.  The rank (4 bits) is
-// the backtrace, eight columns per 32-bit word.
-constexpr int kDpRun = 8;
-constexpr int kFitWalk = 16;         // rows of the backtrace per register chunk of the walk
+// the backtrace.
+constexpr int kDpRun = 8;            // columns of a backtrace word of the windowed search
+constexpr int kFitWalk = 8;          // rows of the backtrace per register chunk of the walk
 
-// The band edges of one row, up to kBandPer per thread (a row holds at most W edges and the
-// workgroup has at least W/4 threads).
-constexpr int kBandPer = 4;
-
-__device__ __forceinline__ void band_load(const ld_edge* row_edges, int cnt, int* bins) {
-#pragma unroll
-    for (int k = 0; k < kBandPer; ++k) {
-        const int i = threadIdx.x + k * blockDim.x;
-        bins[k] = i < cnt ? row_edges[i].bin : -1;
-    }
-}
-
-__device__ __forceinline__ int* smem_i(unsigned char* p) { return reinterpret_cast<int*>(p); }
-
-// position of column c (c >= -8) in a run-interleaved row with NR runs
-__device__ __forceinline__ int ipos(int c, int NR) { return (c & (kDpRun - 1)) * NR + (c >> 3) + 1; }
-
-__device__ __forceinline__ void band_apply(const int* bins, int sign, int* hist, int NR) {
-#pragma unroll
-    for (int k = 0; k < kBandPer; ++k)
-        if (bins[k] >= 0) atomicAdd(&hist[ipos(bins[k], NR)], sign);
-}
-
-__device__ __forceinline__ int rank_to_tau(int r) { return r == 0 ? 0 : ((r & 1) ? -((r + 1) >> 1) : (r >> 1)); }
-// rank_to_tau(r) + 8 in bits 4r .. 4r+3 for r = 0 .. 10
+// tau of rank r, plus 8, in bits 4r .. 4r+3 for r = 0 .. 10
 constexpr uint64_t kRankTau = [] {
     uint64_t x = 0;
     for (int r = 0; r <= 10; ++r) x |= (uint64_t)((r == 0 ? 0 : ((r & 1) ? -((r + 1) >> 1) : (r >> 1))) + 8) << (4 * r);
@@ -1053,212 +1029,372 @@ __device__ void vpx_fit_tail(Dev& d, int b, FrameInfo fi, int* PX, int* PY, int*
     }
 }
 
-// NRC: the run count NR of the interleaved rows as a compile-time constant (>= nwords + 2,
-// so the LDS offsets of the window below become immediates), or 0 for nwords + 2 at run time.
-// Seven waves per SIMD (72 VGPRs, a few bytes spilled outside the row loop) leave room for
-// four 320-thread frames on every CU however their waves fall on its SIMDs, so a 1024-frame
-// batch runs in one round; at six waves per SIMD some CUs held only three of them.
-template <int MAXT, int NRC>
-__global__ __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(7))) void k_vpx_fit(Dev d) {
-    extern __shared__ unsigned char smem[];
-    __shared__ int64_t rv[kMaxWaves];
-    __shared__ int ri[kMaxWaves];
-    __shared__ int red[kMaxWaves];
-    const int b = blockIdx.x, t = threadIdx.x, nt = blockDim.x;
+// The workgroup's first vpx_fit_waves(2W) waves own kFitCols consecutive columns a thread and keep
+// their DP row (E << 4) in registers; the five columns either side come from the neighbouring
+// lanes by wave shifts, and at a wave's ends from the neighbouring wave through LDS.  The vote
+// columns of the road rows are staged in LDS first (rows past stage_cap read their edges from
+// memory).  One more wave keeps the band's counts, one LDS row of them for the rows of each
+// parity: while a row is worked on from its parity's counts, the other parity's move on by the
+// two rows that enter and the two that leave.  So a row has one barrier, its window and minima
+// touch no LDS, and nothing in it waits for memory (with the votes read from memory a row ahead,
+// a row took 1.1 us for any number of columns and waves).
+//
+// What bounds it: one frame alone, a row's chain of barrier, seam and count reads (about 300
+// cycles) and its 200 operations; many frames, the operations issued, about 13 a column.  Ten
+// columns a thread make four waves of 1242 wide frames, one a SIMD; 4, 6, 8, 12 and 16 were
+// slower alone and with 1024 frames.  1242 x 375, one frame 218 -> 133 us, 1024 frames 418 -> 340
+// us; 1920 x 1080, one frame 660 -> 480 us, 256 frames 705 -> 518 us.
+constexpr int kFitCols = 10;         // columns a thread
+constexpr int kSeam = 8;             // LDS words of one end of a wave's row (five used)
+constexpr int kNoVote = 0xFFFF;      // a staged edge without a vote column
+
+__host__ __device__ constexpr int vpx_fit_waves(int W2) { return (W2 + kFitCols * kWave - 1) / (kFitCols * kWave); }
+
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) void k_vpx_fit(Dev d, int stage_cap) {
+    constexpr int K = kFitCols;
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    __shared__ int64_t rv[kMaxWaves + 1];
+    __shared__ int ri[kMaxWaves + 1];
+    __shared__ int red[kMaxWaves + 1];
+    const int b = blockIdx.x, t = threadIdx.x, nt = blockDim.x, lane = lane_id();
+    const int wave = __builtin_amdgcn_readfirstlane(t / kWave), nw = nwaves() - 1;   // nw: the waves that own columns
     if (frame_masked(d, b)) return;
-    const int H = d.H, W2 = d.W2, v_max = H - 1;
-    const int nwords = (W2 + kDpRun - 1) / kDpRun;
+    const int H = d.H, W = d.W, W2 = d.W2, v_max = H - 1;
     FrameInfo fi = d.info[b];
     for (int v = t; v < H; v += nt) d.mxpath[(int64_t)b * H + v] = -1;
     if (fi.flags & LD_FLAG_NOROAD) return;
-    const int v_h = fi.v_h, R = v_max - v_h + 1, chi = d.P.chi;
-    // DP rows and the band histogram are stored run-interleaved, column c at
-    // (c mod 8) * NR + c / 8 + 1, so that the lanes of a wave (one run of 8 columns each)
-    // touch consecutive words; runs -1 and nruns are padding (kBig).
-    const int NR = NRC > 0 ? NRC : nwords + 2;
-    const int WP = kDpRun * NR;
-    int* hist = reinterpret_cast<int*>(smem);   // WP, interleaved, 16 x the band's votes
-    int* Sa = hist + WP;                 // E << 4
-    int* Sb = Sa + WP;
-    int* cntL = Sb + WP;                 // per-row edge counts
-    const ld_edge* fedges = d.edges + (int64_t)b * H * d.W;
-    for (int v = t; v < H; v += nt) cntL[v] = d.rowcnt[(int64_t)b * H + v];
-    for (int i = t; i < WP; i += nt) { hist[i] = 0; Sa[i] = kBig; Sb[i] = kBig; }
+    const int v_h = __builtin_amdgcn_readfirstlane(fi.v_h), R = v_max - v_h + 1, chi = d.P.chi;
+    const int WP = nw * kWave * K;                             // columns of one row of counts
+    int* hist = reinterpret_cast<int*>(smem);                  // 2 x WP, by row parity: 16 x the band's votes
+    int* seam = reinterpret_cast<int*>(hist + 2 * WP);         // 2 x (nw + 2) x 2 x kSeam: the columns either side of a wave
+    int* roff = seam + 2 * (nw + 2) * 2 * kSeam;               // R + 1: edges on the road rows above
+    uint16_t* wb = reinterpret_cast<uint16_t*>(roff + H + 1);  // stage_cap vote columns
+    const ld_edge* fedges = d.edges + (int64_t)b * H * W;
+    for (int r = t; r < R; r += nt) roff[r + 1] = d.rowcnt[(int64_t)b * H + v_h + r];
+    for (int i = t; i < 2 * WP; i += nt) hist[i] = 0;
+    for (int i = t; i < 2 * (nw + 2) * 2 * kSeam; i += nt) seam[i] = kBig;
+    // staging: a wave takes kStageRows rows at a time, their first 64 edges in flight at once
+    constexpr int kStageRows = 16;
+    int c[kStageRows];
+    auto load_rows = [&](int r0) {
+#pragma unroll
+        for (int j = 0; j < kStageRows; ++j)
+            c[j] = fedges[(int64_t)(v_h + min(r0 + j, R - 1)) * W + min(lane, W - 1)].bin;
+    };
+    load_rows(wave * kStageRows);
     __syncthreads();
-    int ne = 0;
-    for (int v = v_h + t; v <= v_max; v += nt) ne += cntL[v];
-    ne = block_sum_i32(ne, red);
-    int nv = 0;   // votes that landed in a column (counted as each row enters the band)
-    // initial band rows max(v_max - chi, v_h) .. v_max, four rows of loads in flight at a time
-    for (int v = max(v_max - chi, v_h); v <= v_max; v += 4) {
-        int bins[4][kBandPer];
+    if (wave == 0) {                                           // inclusive prefix, 64 rows a scan
+        int carry = 0;
+        for (int base = 0; base < R; base += kWave) {
+            int x = base + lane < R ? roff[base + lane + 1] : 0;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = v + j;
-            band_load(fedges + (int64_t)r * d.W, r <= v_max ? cntL[r] : 0, bins[j]);
+            for (int o = 1; o < kWave; o <<= 1) {
+                const int y = __shfl_up(x, o, kWave);
+                if (lane >= o) x += y;
+            }
+            if (base + lane < R) roff[base + lane + 1] = carry + x;
+            carry += __shfl(x, kWave - 1, kWave);
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-#pragma unroll
-            for (int k = 0; k < kBandPer; ++k) nv += bins[j][k] >= 0 ? 1 : 0;
-            band_apply(bins[j], 16, hist, NR);
-        }
+        if (lane == 0) roff[0] = 0;
     }
     __syncthreads();
-    for (int c = t; c < W2; c += nt) Sa[ipos(c, NR)] = -hist[ipos(c, NR)];
-    __syncthreads();
-    const int tau_max = d.P.tau_x_max;
-    const int slope = 16 * d.P.lambda_x + 2;
-    uint32_t* back = reinterpret_cast<uint32_t*>(d.back_x) + (int64_t)b * H * nwords;
-    const int c0 = t * kDpRun;
-    // each thread's window Sh(c0-5 .. c0+12) of a DP row: window column c0 - 5 + j sits at int
-    // index t + K[j] (K uniform over the workgroup: K[j] = ((3 + j) mod 8) NR + (3 + j) div 8)
-    constexpr int kWin = kDpRun + 10;
-    int K[kWin];
+    int nv = 0;   // votes that landed in a column
+    for (int r0 = wave * kStageRows; r0 < R; r0 += (nw + 1) * kStageRows) {
+        const int mine = roff[min(r0 + lane, R)];              // lane l: the offset of row r0 + l
 #pragma unroll
-    for (int j = 0; j < kWin; ++j) K[j] = ((3 + j) & (kDpRun - 1)) * NR + ((3 + j) >> 3);
-    const bool full5 = tau_max == 5;
-    // band rows entering / leaving at the next DP row: each thread's first edge of both rows is
-    // prefetched one row ahead (one register each keeps the kernel at 80 VGPRs); the edges past
-    // the first blockDim.x of a row (rare) are read when the row is applied
-    auto first_bin = [&](int r, bool in) -> int {
-        const int n = in ? cntL[r] : 0;
-        return t < n ? fedges[(int64_t)r * d.W + t].bin : -1;
-    };
-    auto rest_apply = [&](int r, bool in, int sign) {
-        const int n = in ? cntL[r] : 0;
-        for (int i = t + nt; i < n; i += nt) {
-            const int c = fedges[(int64_t)r * d.W + i].bin;
-            if (c >= 0) {
-                atomicAdd(&hist[ipos(c, NR)], 16 * sign);
-                nv += sign > 0 ? 1 : 0;
+        for (int j = 0; j < kStageRows; ++j) {
+            const int r = r0 + j, o = __builtin_amdgcn_readlane(mine, j), n = __builtin_amdgcn_readlane(mine, j + 1) - o;
+            const bool fits = o + n <= stage_cap;              // (rows past the last have n = 0)
+            if (lane < n) {
+                nv += c[j] >= 0 ? 1 : 0;
+                if (fits) wb[o + lane] = (uint16_t)c[j];       // -1 is kNoVote
             }
-        }
-    };
-    int nadd, nrem;
-    {
-        const int v = v_max - 1;
-        const int ra = v - chi, rr = v + chi + 1;
-        nadd = first_bin(max(ra, 0), ra >= v_h);
-        nrem = first_bin(min(rr, v_max), rr <= v_max);
-    }
-    // bits of the backtrace word that belong to columns below W2
-    const uint32_t wmask = c0 + kDpRun <= W2 ? 0xFFFFFFFFu : (1u << (4 * max(W2 - c0, 0))) - 1u;
-    int parity = 0;   // 0: read Sa, write Sb
-    // The row recursion, instantiated once for the full window (tau_max = 5) and once for a
-    // narrower one, so the per-column minima carry no run-time test.  The per-c constant of
-    // the window minima cancels between the shifted terms and the result, so only the
-    // uniform offsets slope * (j - 5) and slope * k enter.
-    auto dp_rows = [&](auto full) {
-        constexpr bool kFull = decltype(full)::value;
-        for (int v = v_max - 1; v >= v_h; --v) {
-            const int cadd = nadd, crem = nrem;
-            if (v - 1 >= v_h) {
-                const int ra = v - 1 - chi, rr = v + chi;
-                nadd = first_bin(max(ra, 0), ra >= v_h);
-                nrem = first_bin(min(rr, v_max), rr <= v_max);
-            }
-            nv += cadd >= 0 ? 1 : 0;
-            if (cadd >= 0) atomicAdd(&hist[ipos(cadd, NR)], 16);
-            if (crem >= 0) atomicAdd(&hist[ipos(crem, NR)], -16);
-            {
-                const int ra = v - chi, rr = v + chi + 1;
-                rest_apply(max(ra, 0), ra >= v_h, 1);
-                rest_apply(min(rr, v_max), rr <= v_max, -1);
-            }
-            __syncthreads();
-            if (c0 < W2) {
-                const int* src = (parity ? Sb : Sa) + t;
-                int* dst = (parity ? Sa : Sb) + t;
-                const int* hs = hist + t;
-                int w[kWin], h[kDpRun], TL[kWin], TR[kWin];
-#pragma unroll
-                for (int j = 0; j < kWin; ++j) w[j] = src[K[j]];
-#pragma unroll
-                for (int k = 0; k < kDpRun; ++k) h[k] = hs[K[k + 5]];
-#pragma unroll
-                for (int j = 0; j < kWin; ++j) {
-                    TL[j] = w[j] - slope * (j - 5);     // tau < 0 terms, less slope * c
-                    TR[j] = w[j] + slope * (j - 5);     // tau > 0 terms, plus slope * c
+            if (n > kWave)
+                for (int i = lane + kWave; i < n; i += kWave) {
+                    const int bin = fedges[(int64_t)(v_h + r) * W + i].bin;
+                    nv += bin >= 0 ? 1 : 0;
+                    if (fits) wb[o + i] = (uint16_t)bin;
                 }
-                uint32_t word = 0;
-#pragma unroll
-                for (int k = 0; k < kDpRun; ++k) {
-                    int lm, rm;
-                    if constexpr (kFull) {
-                        lm = min(min(min(TL[k], TL[k + 1]), min(TL[k + 2], TL[k + 3])), TL[k + 4]);
-                        rm = min(min(min(TR[k + 6], TR[k + 7]), min(TR[k + 8], TR[k + 9])), TR[k + 10]);
-                    } else {
-                        lm = kBig; rm = kBig;
-#pragma unroll
-                        for (int a = 1; a <= 5; ++a)
-                            if (a <= tau_max) { lm = min(lm, TL[k + 5 - a]); rm = min(rm, TR[k + 5 + a]); }
-                    }
-                    const int key = min(w[k + 5], min(lm + (slope * k - 1), rm - slope * k));
-                    // (E_min - votes) << 4; columns past W2 keep the padding value
-                    dst[K[k + 5]] = c0 + k < W2 ? (key & -16) - h[k] : kBig;
-                    word |= (uint32_t)(key & 15) << (4 * k);
+        }
+        load_rows(r0 + (nw + 1) * kStageRows);
+    }
+    __syncthreads();
+    // one vote enters (x = 1) or leaves (-1) the counts
+    auto vote = [&](int* to, int bin, int x) {
+        if (bin != kNoVote) atomicAdd(&to[bin], 16 * x);
+    };
+    // the votes of road rows r0 .. r1, from the lane's i-th edge of each row on
+    auto vote_rows = [&](int* to, int r0, int r1, int x) {
+        for (int r = r0; r <= r1; ++r) {
+            const int o = roff[r], n = roff[r + 1] - o;
+            const bool fits = o + n <= stage_cap;
+            for (int i = lane; i < n; i += kWave) {
+                int bin = fits ? wb[o + i] : kNoVote;
+                if (!fits) {
+                    const int e = fedges[(int64_t)(v_h + r) * W + i].bin;
+                    bin = e >= 0 ? e : kNoVote;
                 }
-                back[(int64_t)v * nwords + t] = word & wmask;
+                vote(to, bin, x);
             }
-            __syncthreads();
-            parity ^= 1;
         }
     };
-    if (full5) dp_rows(std::true_type{});
-    else dp_rows(std::false_type{});
-    int* Sc = parity ? Sb : Sa;
-    int64_t bvv = INT64_MAX;
-    int bi = 0x7fffffff;
-    for (int c = t; c < W2; c += nt) {
-        const int64_t e = Sc[ipos(c, NR)] >> 4;
-        if (e < bvv) { bvv = e; bi = c; }
-    }
-    block_argmin_i64(bvv, bi, rv, ri);
-    // backtrace, by wave 0: lane l holds word w0 + l of each of kFitWalk rows (64 words = 512
-    // columns), with the next chunk in flight; the column is wave-uniform, so a step is a
-    // readlane and a few scalar operations.  The path moves at most 5 columns a row, so from
-    // the start column c of a chunk it stays within c +- 5 kFitWalk over this chunk and within
-    // c +- 10 kFitWalk over the next, which the next chunk's words (centred on c) cover.
-    if (t < kWave) {
-        const int l = t;
-        int c = bi;
-        auto wbase = [&](int col) { return max(0, min((col >> 3) - 31, nwords - kWave)); };
-        uint32_t bk[kFitWalk], bn[kFitWalk];
-        auto load_chunk = [&](int v0, int w0, uint32_t (&dst)[kFitWalk]) {
-            const int wi = min(w0 + l, nwords - 1);
-#pragma unroll
-            for (int r = 0; r < kFitWalk; ++r) {
-                const int v = min(v0 + r, v_max - 1);          // rows v < v_max hold an entry
-                dst[r] = back[(int64_t)v * nwords + wi];
+    // the bands of the two lowest rows (road rows R - 1 and R - 2)
+    for (int r = max(R - 1 - chi, 0) + wave; r < R; r += nw + 1) vote_rows(hist + (v_max & 1) * WP, r, r, 1);
+    for (int r = max(R - 2 - chi, 0) + wave; r <= min(R - 2 + chi, R - 1); r += nw + 1)
+        vote_rows(hist + ((v_max & 1) ^ 1) * WP, r, r, 1);
+    // backtrace: the ranks of a thread's columns in two words, at the start of the q buffer's row
+    // of W words (k_energy and k_m1 write that buffer later)
+    const int L = (W2 + K - 1) / K;                            // threads with a column
+    uint2* back = reinterpret_cast<uint2*>(d.qbuf + ((int64_t)b * H * W & ~(int64_t)1));
+    const int64_t pitch = W / 2;
+    const int c0 = t * K;
+    int S[K];
+    if (wave == nw) {
+        // While row v is worked on from the counts of its parity, those of the other parity go
+        // from the band of row v + 1 to that of v - 1: rows v - 1 - chi and v - chi enter, v + chi and
+        // v + 1 + chi leave (with chi = 0 one each), two runs of staged edges.  Lane l holds
+        // both runs (offset, count; -1 when not all staged) of iteration 64 m + l; their first
+        // 128 entries are read a row ahead.
+        int oA = 0, nA = 0, oR = 0, nR = 0;
+        const int two = chi > 0 ? 1 : 0;
+        auto heads = [&](int it0) {
+            const int r = R - 1 - it0 - lane;                  // road row of iteration it0 + lane
+            const int a0 = max(r - 1 - chi, 0), a1 = r - 1 - chi + two, l0 = r + 1 + chi - two, l1 = min(r + 1 + chi, R - 1);
+            nA = nR = 0;
+            if (r >= 1 && a1 >= 0) {
+                oA = roff[a0];
+                nA = roff[a1 + 1] - oA;
+                if (oA + nA > stage_cap) nA = -1;
+            }
+            if (r >= 1 && l0 <= l1) {
+                oR = roff[l0];
+                nR = roff[l1 + 1] - oR;
+                if (oR + nR > stage_cap) nR = -1;
             }
         };
-        int wcur = wbase(c);
-        load_chunk(v_h, wcur, bk);
-        for (int v0 = v_h; v0 <= v_max; v0 += kFitWalk) {
-            const int wnext = wbase(c);
-            load_chunk(v0 + kFitWalk, wnext, bn);          // clamped rows: always a full chunk
-            int pv = 0;
+        auto own = [&](int o, int n, int i) -> int { return i < n ? wb[o + i] : kNoVote; };
+        int cA, cR, bA[2], bR[2];
+        auto next = [&](int it) {
+            const int l = it & (kWave - 1);
+            const int fA = __builtin_amdgcn_readlane(oA, l), fR = __builtin_amdgcn_readlane(oR, l);
+            cA = __builtin_amdgcn_readlane(nA, l);
+            cR = __builtin_amdgcn_readlane(nR, l);
 #pragma unroll
-            for (int r = 0; r < kFitWalk; ++r) {
-                const int v = v0 + r;
-                if (v <= v_max) {
-                    if (l == r) pv = c;
-                    if (v < v_max) {
-                        const uint32_t word = __builtin_amdgcn_readlane(bk[r], (c >> 3) - wcur);
-                        c += rank_to_tau((int)((word >> (4 * (c & 7))) & 15u));
+            for (int j = 0; j < 2; ++j) {
+                bA[j] = own(fA, cA, lane + j * kWave);
+                bR[j] = own(fR, cR, lane + j * kWave);
+            }
+        };
+        heads(0);
+        next(1);
+        __builtin_amdgcn_s_setprio(3);                         // the others wait for this wave at each row
+        __syncthreads();                                       // row v_max
+        for (int it = 1; it < R; ++it) {
+            const int r = R - 1 - it;
+            __syncthreads();
+            int* to = hist + ((v_max - it - 1) & 1) * WP;
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                vote(to, bA[j], 1);
+                vote(to, bR[j], -1);
+            }
+            if (r >= 1) {
+                // runs past 128 edges or not staged (rare)
+                const int fA = __builtin_amdgcn_readlane(oA, it & (kWave - 1)), fR = __builtin_amdgcn_readlane(oR, it & (kWave - 1));
+                for (int i = lane + 2 * kWave; i < cA; i += kWave) vote(to, wb[fA + i], 1);
+                for (int i = lane + 2 * kWave; i < cR; i += kWave) vote(to, wb[fR + i], -1);
+                if (cA < 0) vote_rows(to, max(r - 1 - chi, 0), r - 1 - chi + two, 1);
+                if (cR < 0) vote_rows(to, r + 1 + chi - two, min(r + 1 + chi, R - 1), -1);
+            }
+            if (((it + 1) & (kWave - 1)) == 0) heads(it + 1);
+            next(it + 1);
+        }
+    } else {
+        const int tau_max = d.P.tau_x_max;
+        const int slope = 16 * d.P.lambda_x + 2;
+        const int* own0 = hist + t * K;
+        const int seam_par = (nw + 2) * 2 * kSeam;
+        // the first lane reads the columns before the wave, the last lane those after it
+        const int* get0 = seam + (wave + 1) * 2 * kSeam + (lane == kWave - 1 ? kSeam : 0);
+        int* put0 = seam + (lane == 0 ? wave * 2 * kSeam + kSeam : (wave + 2) * 2 * kSeam);
+        auto counts = [&](int par, int (&h)[K]) {
+            static_assert(K % 2 == 0, "counts are read by twos");
+            const int2* p = reinterpret_cast<const int2*>(own0 + par * WP);
+#pragma unroll
+            for (int q = 0; q < K / 2; ++q) {
+                const int2 x = p[q];
+                h[2 * q] = x.x; h[2 * q + 1] = x.y;
+            }
+        };
+        // the wave's first and last five columns, for the row that parity `par` reads
+        auto put_seams = [&](int par) {
+            if (lane == 0 || lane == kWave - 1) {
+                int x[5];
+#pragma unroll
+                for (int j = 0; j < 5; ++j) x[j] = lane == 0 ? S[j] : S[K - 5 + j];
+                int* s = put0 + par * seam_par;
+                *reinterpret_cast<int4*>(s) = make_int4(x[0], x[1], x[2], x[3]);
+                s[4] = x[4];
+            }
+        };
+        // One row: TL[j] = S(c0 - 5 + j) - slope (j - 5) for tau < 0, TR for tau > 0, the offset of
+        // a term from its column taken against the thread's first column; the minima over five
+        // consecutive entries share their middle three.  Instantiated for the full window
+        // (tau_max = 5) and for a narrower one, and for the wave that holds the last column, whose
+        // columns past it keep the padding value.
+        auto row = [&](auto full, auto last, int par, int v) __attribute__((always_inline)) {
+            constexpr bool kFull = decltype(full)::value, kLast = decltype(last)::value;
+            int w[K + 10];
+            int h[K];
+            {
+                const int* sg = get0 + par * seam_par;
+                const int4 g4 = *reinterpret_cast<const int4*>(sg);
+                const int g[5] = {g4.x, g4.y, g4.z, g4.w, sg[4]};
+                counts(par, h);
+#pragma unroll
+                for (int j = 0; j < 5; ++j) {
+                    w[j] = __builtin_amdgcn_update_dpp(g[j], S[K - 5 + j], 0x138, 0xF, 0xF, false);      // lane - 1
+                    w[K + 5 + j] = __builtin_amdgcn_update_dpp(g[j], S[j], 0x130, 0xF, 0xF, false);      // lane + 1
+                }
+            }
+#pragma unroll
+            for (int k = 0; k < K; ++k) w[k + 5] = S[k];
+            int lm[K], rm[K];
+            if constexpr (kFull) {
+                int TL[K + 4], TR[K + 4];
+#pragma unroll
+                for (int j = 0; j < K + 4; ++j) {
+                    TL[j] = w[j] - slope * (j - 5);
+                    TR[j] = w[j + 6] + slope * (j + 1);
+                }
+                auto min5 = [](auto n, const int* T, int* m) { // m[k] = min T[k .. k + 4], k = 0 .. n - 1
+                    const int x = min(min(T[2], T[3]), T[4]);
+                    m[0] = min(min(T[0], T[1]), x);
+                    m[1] = min(min(T[1], x), T[5]);
+                    if constexpr (decltype(n)::value == 4) {
+                        m[2] = min(min(x, T[5]), T[6]);
+                        m[3] = min(min(T[3], T[4]), min(min(T[5], T[6]), T[7]));
                     }
+                };
+                static_assert(K == 10, "the minima of ten columns");
+                min5(IntC<4>{}, TL, lm); min5(IntC<4>{}, TL + 4, lm + 4); min5(IntC<2>{}, TL + 8, lm + 8);
+                min5(IntC<4>{}, TR, rm); min5(IntC<4>{}, TR + 4, rm + 4); min5(IntC<2>{}, TR + 8, rm + 8);
+            } else {
+#pragma unroll
+                for (int k = 0; k < K; ++k) {
+                    lm[k] = kBig; rm[k] = kBig;
+#pragma unroll
+                    for (int a = 1; a <= 5; ++a)
+                        if (a <= tau_max) {
+                            lm[k] = min(lm[k], w[k + 5 - a] - slope * (k - a));
+                            rm[k] = min(rm[k], w[k + 5 + a] + slope * (k + a));
+                        }
+                }
+            }
+            uint32_t word[2] = {0, 0};
+#pragma unroll
+            for (int k = 0; k < K; ++k) {
+                const int key = min(min(w[k + 5], lm[k] + (slope * k - 1)), rm[k] - slope * k);
+                const int e = (key & -16) - h[k];              // (E_min - votes) << 4
+                S[k] = !kLast || c0 + k < W2 ? e : kBig;
+                word[k / 8] = __builtin_amdgcn_alignbit((uint32_t)key, word[k / 8], 4);   // enters from the top
+            }
+            if (!kLast || c0 < W2) (back + v * pitch)[t] = make_uint2(word[0], word[1]);
+            put_seams(par ^ 1);
+        };
+        auto rows = [&](auto full, auto last) __attribute__((always_inline)) {
+            __syncthreads();                                   // row v_max: its counts alone
+            int h[K];
+            counts(v_max & 1, h);
+#pragma unroll
+            for (int k = 0; k < K; ++k) S[k] = c0 + k < W2 ? -h[k] : kBig;
+            put_seams((v_max & 1) ^ 1);
+            int v = v_max - 1;
+            if (v >= v_h && (v & 1) == 0) {
+                __syncthreads();
+                row(full, last, 0, v);
+                --v;
+            }
+            for (; v >= v_h; v -= 2) {                         // v is odd here
+                __syncthreads();
+                row(full, last, 1, v);
+                if (v - 1 < v_h) break;
+                __syncthreads();
+                row(full, last, 0, v - 1);
+            }
+        };
+        if (tau_max != 5) rows(std::false_type{}, std::true_type{});
+        else if ((wave + 1) * K * kWave > W2) rows(std::true_type{}, std::true_type{});
+        else rows(std::true_type{}, std::false_type{});
+    }
+    int64_t bvv = INT64_MAX;
+    int bi = 0x7fffffff;
+    if (wave < nw) {
+#pragma unroll
+        for (int k = 0; k < K; ++k)
+            if (c0 + k < W2 && (int64_t)(S[k] >> 4) < bvv) { bvv = S[k] >> 4; bi = c0 + k; }
+    }
+    block_argmin_i64(bvv, bi, rv, ri);
+    // backtrace, by wave 0: lane l holds the ranks of thread w0 + l of each of kFitWalk rows (64
+    // threads, 64 K columns); the column is wave-uniform, so a step is a readlane and a few scalar
+    // operations.  kAhead chunks of rows are in flight beside the one that is walked: the path
+    // moves at most 5 columns a row, so the words centred on a chunk's start column, 32 K to
+    // either side, cover it up to the end of the last of them.
+    if (t < kWave) {
+        constexpr int kAhead = 3;
+        static_assert(5 * (kAhead + 1) * kFitWalk + K <= 32 * K, "a chunk's words cover the path");
+        const int l = t;
+        int c = __builtin_amdgcn_readfirstlane(bi);
+        struct Chunk { uint2 w[kFitWalk]; int w0; };
+        auto load_chunk = [&](int v0, Chunk& q) {
+            q.w0 = max(0, min(c / K - 32, L - kWave));
+            const int wi = min(q.w0 + l, L - 1);
+#pragma unroll
+            for (int r = 0; r < kFitWalk; ++r)                 // rows v < v_max hold an entry
+                q.w[r] = back[max(min(v0 + r, v_max - 1), 0) * pitch + wi];
+        };
+        // the rank of a thread's column k: eight in the first word, the rest at the second's top
+        auto rank_of = [](const uint2& w, int lane_of, int k) -> int {
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)w.x, lane_of);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)w.y, lane_of);
+            return (int)((k < 8 ? lo >> (4 * k) : hi >> (4 * (k + 8 - K))) & 15u);
+        };
+        auto walk = [&](int v0, const Chunk& q) {
+            int pv = 0;
+            auto step = [&](int r) {
+                const int g = c / K;
+                c += (int)((kRankTau >> (4 * rank_of(q.w[r], g - q.w0, c - g * K))) & 15u) - 8;
+            };
+            if (v0 + kFitWalk <= v_max) {                      // every row of the chunk has an entry
+#pragma unroll
+                for (int r = 0; r < kFitWalk; ++r) {
+                    pv = l == r ? c : pv;
+                    step(r);
+                }
+            } else {
+#pragma unroll
+                for (int r = 0; r < kFitWalk; ++r) {
+                    if (v0 + r > v_max) break;
+                    pv = l == r ? c : pv;
+                    if (v0 + r < v_max) step(r);
                 }
             }
             if (l < kFitWalk && v0 + l <= v_max) d.mxpath[(int64_t)b * H + v0 + l] = pv;
+        };
+        Chunk q[kAhead + 1];
 #pragma unroll
-            for (int r = 0; r < kFitWalk; ++r) bk[r] = bn[r];
-            wcur = wnext;
+        for (int i = 0; i < kAhead; ++i) load_chunk(v_h + i * kFitWalk, q[i]);
+        for (int v0 = v_h; v0 <= v_max; v0 += (kAhead + 1) * kFitWalk) {
+#pragma unroll
+            for (int i = 0; i <= kAhead; ++i) {
+                load_chunk(v0 + (i + kAhead) * kFitWalk, q[(i + kAhead) % (kAhead + 1)]);
+                walk(v0 + i * kFitWalk, q[i]);
+            }
         }
     }
     nv = block_sum_i32(nv, red);
     if (t == 0) {
-        fi.n_edges = ne;
+        fi.n_edges = roff[R];
         fi.n_votes = nv;
         d.info[b] = fi;
     }
@@ -2536,23 +2672,10 @@ size_t vdisp_fit_lds(const Dev& d) {
            (size_t)kVdWalk * kVdWalkCols;
 }
 
-int vpx_fit_threads(const Dev& d) {
-    const int runs = (d.W2 + kDpRun - 1) / kDpRun;
-    return std::min(1024, std::max(64, (runs + 63) / 64 * 64));
-}
-
-// the compile-time run count k_vpx_fit<512, NRC> uses for this width (0: none fits)
-int vpx_fit_nrc(const Dev& d) {
-    const int nr = (d.W2 + kDpRun - 1) / kDpRun + 2;
-    for (int c : {64, 128, 256, 320, 512})
-        if (nr <= c) return c;
-    return 0;
-}
-
+// LDS of k_vpx_fit without the staged vote columns
 size_t vpx_fit_lds(const Dev& d) {
-    const int nrc = vpx_fit_nrc(d);
-    const size_t WP = (size_t)kDpRun * (nrc > 0 ? nrc : (d.W2 + kDpRun - 1) / kDpRun + 2);
-    return sizeof(int) * (3 * WP + (size_t)d.H);
+    const int nw = vpx_fit_waves(d.W2);
+    return sizeof(int) * ((size_t)nw * kWave * kFitCols * 2 + 2 * (size_t)(nw + 2) * 2 * kSeam + (size_t)d.H + 1);
 }
 
 size_t edges_lds(int nwaves) {
@@ -2729,26 +2852,23 @@ ld_status run_edges(ld_frame f, const uint8_t* grey, int64_t gp, const void* dis
 
 // the full band accumulator and row DP of S6-S7 for the frames that `d` selects
 ld_status run_vpx_dp(ld_frame f, const Dev& d, hipStream_t st) {
-    const size_t l4 = vpx_fit_lds(d);
-    const int nt4 = vpx_fit_threads(d);
-    ProfScope ps(f, 3, st);
-    const int nrc = vpx_fit_nrc(d);
-    auto launch = [&](auto kernel) {
-        allow_lds(kernel, l4);
-        hipLaunchKernelGGL(kernel, dim3(f->active), dim3(nt4), l4, st, d);
+    const size_t fixed = vpx_fit_lds(d);
+    const int nt = kWave * (vpx_fit_waves(d.W2) + 1);
+    // Vote columns staged: what LDS leaves when a CU holds the frames that it is given, fewer where
+    // that would not stage an edge on every 96 pixels (road scenes hold one on 55 to 170): a
+    // row that is not staged costs a load's latency, about two staged rows.
+    auto room = [&](int per_cu) -> size_t {
+        const size_t share = (size_t)kMaxLds / per_cu - 1024;      // 1 KiB: the static arrays
+        return share > fixed ? (share - fixed) / sizeof(uint16_t) / 8 * 8 : 0;
     };
-    if (nt4 <= 512) {
-        switch (nrc) {
-            case 64: launch(k_vpx_fit<512, 64>); break;
-            case 128: launch(k_vpx_fit<512, 128>); break;
-            case 256: launch(k_vpx_fit<512, 256>); break;
-            case 320: launch(k_vpx_fit<512, 320>); break;
-            case 512: launch(k_vpx_fit<512, 512>); break;
-            default: launch(k_vpx_fit<512, 0>); break;
-        }
-    } else {
-        launch(k_vpx_fit<1024, 0>);
-    }
+    const size_t px = (size_t)d.W * d.H;
+    int per_cu = std::max(1, std::min(4, (f->active + kCUs - 1) / kCUs));
+    while (per_cu > 1 && room(per_cu) < px / 96) --per_cu;
+    const int cap = (int)std::min((px + 7) / 8 * 8, room(per_cu));
+    const size_t l4 = fixed + sizeof(uint16_t) * (size_t)cap;
+    ProfScope ps(f, 3, st);
+    allow_lds(k_vpx_fit, l4);
+    hipLaunchKernelGGL(k_vpx_fit, dim3(f->active), dim3(nt), l4, st, d, cap);
     return launch_ok();
 }
 

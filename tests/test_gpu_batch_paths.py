@@ -34,3 +34,24 @@ def test_energies_by_frame_count(kind, w, h, n):
     out = run_gpu(g, d, dm)
     for b in sorted({0, n // 2, n - 1}):
         compare_frame(out, b, g[b], d[b], dm)
+
+
+@pytest.mark.parametrize("kind,w,h,kw", [
+    # one wave of columns to its last, one and two more columns; several waves
+    ("road", 319, 96, {}), ("road", 320, 96, {}), ("road", 321, 97, {}), ("road", 640, 80, {}), ("road", 643, 66, {}),
+    # bands of one row, of three, and past the road
+    ("road", 321, 96, {"chi": 0}), ("road", 257, 96, {"chi": 1}), ("road", 257, 96, {"chi": 400}),
+    # narrower windows, and rows far longer than a wave
+    ("road", 321, 64, {"tau_x_max": 0}), ("road", 321, 64, {"tau_x_max": 4, "lambda_x": 7}),
+    ("random", 333, 61, {}), ("random", 300, 90, {"chi": 0}),
+    # more edges than LDS stages: the rows past it read theirs from memory
+    ("random", 1000, 400, {}),
+])
+def test_vpx_path_by_width_and_band(kind, w, h, kw):
+    import oracle
+    from paper_1807_02752_amd import ld
+    g, d = _frames(kind, w, h, 2)
+    dm = 32 if kind == "random" else 48
+    out = run_gpu(g, d, dm, params=ld.params_default(**kw))
+    for b in range(2):
+        compare_frame(out, b, g[b], d[b], dm, params=oracle.default_params(**kw))
