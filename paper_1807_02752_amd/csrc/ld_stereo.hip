@@ -22,9 +22,13 @@
 // of all slots together) so that a block's words are constant offsets from one address; the
 // sum of products takes the rows in slot order for both blocks, which leaves it unchanged.  The
 // column sums over the ring follow each new row incrementally, the block sums of a row come
-// from the column sums four columns a thread, and the square roots of the block variances are
-// kept per column (FP64), so a candidate costs its 2 rho + 1 rows of byte dot products, a
-// subtraction, a multiplication and a division.  A pixel with a matched neighbour below scores
+// from the column sums four columns a thread, and the block variances are kept per column as
+// integers with their FP32 reciprocal roots.  A candidate costs its 2 rho + 1 rows of byte dot
+// products and one FP32 multiplication (the own block's root is the same for all of a pixel's
+// candidates); the quotient in FP64 is formed only for two candidates whose FP32 values are
+// within 2e-6 of each other, some ten times the rounding of those (1 ulp of the root, half of the
+// conversion and of the product), so the choice is the FP64 one.  The FP64 division and roots of
+// every candidate were a tenth of the sweep (512 pairs of 1242 x 375: 11.0 -> 9.9 ms).  A pixel with a matched neighbour below scores
 // its few propagated candidates (up to three runs) in one loop of its own lane; a pixel without
 // one (every pixel of the first row) searches all of 1..d_max, which would hold up the 63 other
 // lanes of its wave, so such pixels are queued: many (the first row) are taken one a lane, few
@@ -57,9 +61,49 @@ size_t stereo_lds(int W, int rho) {
     return round16(2 * rows * Wp)                      // image rings (u8)
            + 4 * sizeof(int32_t) * (Wp + 2 * kPad)     // column sums S, Q of both images
            + 2 * sizeof(int32_t) * Wp                  // block sums S of both images
-           + 2 * sizeof(double) * Wp                   // sqrt of the block variances of both images
+           + 4 * sizeof(int32_t) * Wp                  // block variances and their reciprocal roots, both images
            + 4 * Wp                                    // disparities of the previous and the current row, both maps
            + 2 * sizeof(uint16_t) * Wp + 16;           // queues of full-range pixels and their lengths, both maps
+}
+
+// The best candidate so far: its FP32 cost without the own block's factor, its exact numerator and
+// its disparity (0: none).
+struct Best {
+    float f = -3.0e38f;
+    int num = 0, d = 0;
+};
+
+// The union of [l - tau, l + tau] over the matched neighbours (l > 0) within 1 .. d_max, as up to
+// three disjoint runs in increasing order (an empty one has b < a).
+struct Runs { int a0, b0, a1, b1, a2, b2; };
+__device__ __forceinline__ Runs runs_of(int l0, int l1, int l2, int tau, int d_max) {
+    int s0 = l0 ? l0 : kNone, s1 = l1 ? l1 : kNone, s2 = l2 ? l2 : kNone;
+    {   // s0 <= s1 <= s2
+        const int a = min(s0, s1), c = max(s0, s1);
+        const int hi3 = max(c, s2), mid = min(c, s2);
+        s0 = min(a, mid); s1 = max(a, mid); s2 = hi3;
+    }
+    // (written as selects: a wave's lanes take every path)
+    Runs r{max(s0 - tau, 1), min(s0 + tau, d_max), 1, 0, 1, 0};
+    {
+        const int lo = s1 - tau, hi = min(s1 + tau, d_max);
+        const bool in = s1 < kNone, join = lo <= r.b0 + 1, own = in && !join;
+        r.b0 = in && join ? max(r.b0, hi) : r.b0;
+        r.a1 = own ? lo : 1;
+        r.b1 = own ? hi : 0;
+    }
+    {
+        const int lo = s2 - tau, hi = min(s2 + tau, d_max);
+        const bool in = s2 < kNone, two = r.b1 >= r.a1, join = lo <= (two ? r.b1 : r.b0) + 1;
+        const bool own = in && !join;
+        r.b0 = in && join && !two ? max(r.b0, hi) : r.b0;
+        r.b1 = in && join && two ? max(r.b1, hi) : r.b1;
+        r.a2 = own && two ? lo : 1;
+        r.b2 = own && two ? hi : 0;
+        r.a1 = own && !two ? lo : r.a1;
+        r.b1 = own && !two ? hi : r.b1;
+    }
+    return r;
 }
 
 template <int RHO>
@@ -94,7 +138,7 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
     const uint8_t* ga = (m == 0 ? left + (int64_t)b * H * lp : right + (int64_t)b * H * rp);
     const int64_t pa = m == 0 ? lp : rp;
     uint8_t* out = (m == 0 ? lf : rt) + (int64_t)b * H * W;
-    const int sgn = m == 0 ? -1 : 1;
+    const int sgn = m == 0 ? -1 : 0;                              // x = u + (d ^ sgn) - sgn
     const int Wp = (W + 3) / 4 * 4, Wq = Wp / 4;
     uint32_t* ring0 = reinterpret_cast<uint32_t*>(smem);
     uint32_t* ring1 = ring0 + K * Wq;
@@ -104,9 +148,11 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
     int32_t* colQ1 = colS1 + Wp + 2 * kPad;
     int32_t* S0 = colQ1 + Wp + kPad;
     int32_t* S1 = S0 + Wp;
-    double* sq0 = reinterpret_cast<double*>(S1 + Wp);
-    double* sq1 = sq0 + Wp;
-    uint8_t* pc = reinterpret_cast<uint8_t*>(sq1 + Wp);
+    float* rq0 = reinterpret_cast<float*>(S1 + Wp);    // 1 / sqrt(n Q - S^2); 0 where no block fits or it is flat
+    float* rq1 = rq0 + Wp;
+    int32_t* var0 = reinterpret_cast<int32_t*>(rq1 + Wp);   // n Q - S^2
+    int32_t* var1 = var0 + Wp;
+    uint8_t* pc = reinterpret_cast<uint8_t*>(var1 + Wp);
     uint16_t* queues = reinterpret_cast<uint16_t*>(pc + 4 * Wp);
     int* qns = reinterpret_cast<int*>(queues + 2 * Wp);
     uint32_t* ringA = m == 0 ? ring0 : ring1;
@@ -116,8 +162,10 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
     int32_t* colQ_a = m == 0 ? colQ0 : colQ1;
     int32_t* S_a = m == 0 ? S0 : S1;
     const int32_t* S_b = m == 0 ? S1 : S0;
-    double* sq_a = m == 0 ? sq0 : sq1;
-    const double* sq_b = m == 0 ? sq1 : sq0;
+    float* rq_a = m == 0 ? rq0 : rq1;
+    const float* rq_b = m == 0 ? rq1 : rq0;
+    int32_t* var_a = m == 0 ? var0 : var1;
+    const int32_t* var_b = m == 0 ? var1 : var0;
     uint8_t* prev = pc + (2 * m) * Wp;
     uint8_t* cur = pc + (2 * m + 1) * Wp;
     uint16_t* queue = queues + m * Wp;
@@ -151,16 +199,23 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
         }
         colS_a[u] = sa; colQ_a[u] = qa;
     }
-    // the candidate of disparity d for the pixel at u: its cost against the best so far (bc
-    // starts at -inf), the first strictly larger one kept (with d increasing that leaves ties to
-    // the smaller d).  The numerator n P - S_a S_b is exact in 32 bits (each product below 2^30
-    // for rho <= 5); a candidate whose block leaves the image or is flat is scored at a stand-in
-    // position and not taken
-    auto score = [&](const uint32_t (&A)[K][NW], int u, int Sa, double da, int d, int& best, double& bc) {
-        const int x = u + sgn * d;
+    // the FP64 cost of a candidate (num its numerator, xc its column)
+    auto cost = [&](int num, int va, int xc) -> double {
+        return (double)num / (sqrt((double)va) * sqrt((double)var_b[xc]));
+    };
+    // the candidate of disparity d for the pixel at u against the best so far (b.d = 0: none); ties
+    // go to the smaller d.  The numerator n P - S_a S_b is exact in 32 bits (each product below
+    // 2^30 for rho <= 5); a candidate whose block leaves the image or is flat is scored at a
+    // stand-in position and not taken.  The cost decides by its FP64 value, but is compared by
+    // an FP32 one first, num rounded times the reciprocal root of the variance (v_rsq_f32,
+    // within an ulp): that is within 4e-7 of the true ratio (the own block's factor left out), so
+    // two candidates further apart than 2e-6 of the larger are in the order of their FP64
+    // costs, and only the others take the two square roots and the division.
+    auto score = [&](const uint32_t (&A)[K][NW], int u, int Sa, int d, Best& b) {
+        const int x = u + (d ^ sgn) - sgn;
         const bool inr = (unsigned)(x - RHO) <= (unsigned)(W - 1 - 2 * RHO);
         const int xc = inr ? x : RHO;
-        const double db = sq_b[xc];
+        const float rb = rq_b[xc];
         uint32_t P = 0;
 #pragma unroll
         for (int j = 0; j < K; ++j) {
@@ -169,11 +224,19 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
 #pragma unroll
             for (int k = 0; k < NW; ++k) P = __builtin_amdgcn_udot4(A[j][k], Bw[k], P, false);
         }
-        const int num = N * (int)P - Sa * S_b[xc];
-        const double c = (double)num / (da * db);
-        const bool take = inr & (db > 0.0) & (c > bc);
-        best = take ? d : best;
-        bc = take ? c : bc;
+        const int num = __mul24(N, (int)P) - __mul24(Sa, S_b[xc]);
+        const float f = (float)num * rb;
+        const float g = f - b.f, tol = fmaxf(fabsf(f), fabsf(b.f)) * 2.0e-6f;
+        const bool on = inr & (rb > 0.0f);
+        bool take = on & (g > tol);
+        if (on & (fabsf(g) <= tol)) {
+            const int va = var_a[u];
+            const double c = cost(num, va, xc), bc = cost(b.num, va, u + (b.d ^ sgn) - sgn);
+            take = c > bc || (c == bc && d < b.d);
+        }
+        b.f = take ? f : b.f;
+        b.num = take ? num : b.num;
+        b.d = take ? d : b.d;
     };
     auto own_block = [&](int u, uint32_t (&A)[K][NW]) {
 #pragma unroll
@@ -186,8 +249,8 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
         const bool more = v > RHO;             // a row v - rho - 1 follows
         const int vlo = v - RHO;
         __syncthreads();
-        // block sums and sqrt(n Q - S^2) of the own image, four columns a thread (0 where no
-        // block fits)
+        // block sums, variances n Q - S^2 and their reciprocal roots of the own image, four
+        // columns a thread (root 0 where no block fits)
         for (int g = tm; g < Wq; g += kT) {
             int cs[2][4 * (2 * kC + 1)];
             const int32_t* arr[2] = {colS_a, colQ_a};
@@ -213,20 +276,20 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
                     bs[a][i] = s_;
                 }
             }
-            int4 oa;
-            double qa4[4];
+            int4 oa, ov;
+            float4 orq;
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int u = 4 * g + i;
                 const bool fits = u >= RHO && u <= W - 1 - RHO;
                 const int va = N * bs[1][i] - bs[0][i] * bs[0][i];
-                qa4[i] = fits && va > 0 ? sqrt((double)va) : 0.0;
                 (&oa.x)[i] = fits ? bs[0][i] : 0;
+                (&ov.x)[i] = va;
+                (&orq.x)[i] = fits && va > 0 ? __builtin_amdgcn_rsqf((float)va) : 0.0f;
             }
             *reinterpret_cast<int4*>(S_a + 4 * g) = oa;
-#pragma unroll
-            for (int i = 0; i < 4; i += 2)
-                *reinterpret_cast<double2*>(sq_a + 4 * g + i) = make_double2(qa4[i], qa4[i + 1]);
+            *reinterpret_cast<int4*>(var_a + 4 * g) = ov;
+            *reinterpret_cast<float4*>(rq_a + 4 * g) = orq;
         }
         __syncthreads();
         // the own image's next row from HBM while this one is matched: four bytes a word for
@@ -244,8 +307,8 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
         // neighbours, in increasing d, in the pixel's own lane; the others are queued
         const bool first = v == vb;
         for (int u = tm; u < W; u += kT) {
-            int best = 0;
-            if (u >= RHO && u <= W - 1 - RHO && sq_a[u] > 0.0) {
+            Best best;
+            if (u >= RHO && u <= W - 1 - RHO && rq_a[u] > 0.0f) {
                 int l0 = 0, l1 = 0, l2 = 0;
                 if (!first) {
                     l0 = u - 1 >= RHO ? prev[u - 1] : 0;
@@ -255,46 +318,25 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
                 if ((l0 | l1 | l2) == 0) {
                     queue[atomicAdd(qn, 1)] = (uint16_t)u;
                 } else {
-                    int s0 = l0 ? l0 : kNone, s1 = l1 ? l1 : kNone, s2 = l2 ? l2 : kNone;
-                    {   // s0 <= s1 <= s2
-                        const int a = min(s0, s1), c = max(s0, s1);
-                        const int hi3 = max(c, s2), mid = min(c, s2);
-                        s0 = min(a, mid); s1 = max(a, mid); s2 = hi3;
-                    }
-                    // the union as up to three disjoint runs in increasing order
-                    int a0 = max(s0 - tau, 1), b0 = min(s0 + tau, d_max), a1 = 1, b1 = 0, a2 = 1, b2 = 0;
-                    if (s1 < kNone) {
-                        const int lo = s1 - tau, hi = min(s1 + tau, d_max);
-                        if (lo <= b0 + 1) b0 = max(b0, hi); else { a1 = lo; b1 = hi; }
-                    }
-                    if (s2 < kNone) {
-                        const int lo = s2 - tau, hi = min(s2 + tau, d_max);
-                        if (b1 >= a1) {
-                            if (lo <= b1 + 1) b1 = max(b1, hi); else { a2 = lo; b2 = hi; }
-                        } else {
-                            if (lo <= b0 + 1) b0 = max(b0, hi); else { a1 = lo; b1 = hi; }
-                        }
-                    }
+                    Runs r = runs_of(l0, l1, l2, tau, d_max);
                     uint32_t A[K][NW];
                     own_block(u, A);
                     const int Sa = S_a[u];
-                    const double da = sq_a[u];
-                    double bc = -__builtin_inf();
                     // one loop over all the candidates (a lane's runs follow each other
                     // without waiting for the other lanes' runs to end)
-                    const int n = (b0 - a0 + 1) + max(b1 - a1 + 1, 0) + max(b2 - a2 + 1, 0);
-                    int d = a0, e = b0;
+                    const int n = (r.b0 - r.a0 + 1) + max(r.b1 - r.a1 + 1, 0) + max(r.b2 - r.a2 + 1, 0);
+                    int d = r.a0, e = r.b0;
                     for (int k = 0; k < n; ++k) {
-                        score(A, u, Sa, da, d, best, bc);
+                        score(A, u, Sa, d, best);
                         const bool nx = d == e;
-                        d = nx ? a1 : d + 1;
-                        e = nx ? b1 : e;
-                        a1 = nx ? a2 : a1;
-                        b1 = nx ? b2 : b1;
+                        d = nx ? r.a1 : d + 1;
+                        e = nx ? r.b1 : e;
+                        r.a1 = nx ? r.a2 : r.a1;
+                        r.b1 = nx ? r.b2 : r.b1;
                     }
                 }
             }
-            cur[u] = (uint8_t)best;
+            cur[u] = (uint8_t)best.d;
         }
         __syncthreads();
         // queued pixels: many (the first row) one a lane over all of 1..d_max; few one a wave,
@@ -308,11 +350,9 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
                     uint32_t A[K][NW];
                     own_block(u, A);
                     const int Sa = S_a[u];
-                    const double da = sq_a[u];
-                    int best = 0;
-                    double bc = -__builtin_inf();
-                    for (int d = 1; d <= d_max; ++d) score(A, u, Sa, da, d, best, bc);
-                    cur[u] = (uint8_t)best;
+                    Best best;
+                    for (int d = 1; d <= d_max; ++d) score(A, u, Sa, d, best);
+                    cur[u] = (uint8_t)best.d;
                 }
             } else if (nq > 0) {
                 const int wv = tm >> 6, lane = tm & 63;
@@ -321,10 +361,10 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
                     uint32_t A[K][NW];
                     own_block(u, A);
                     const int Sa = S_a[u];
-                    const double da = sq_a[u];
-                    int best = 0;
-                    double bc = -__builtin_inf();
-                    for (int d = 1 + lane; d <= d_max; d += 64) score(A, u, Sa, da, d, best, bc);
+                    Best b;
+                    for (int d = 1 + lane; d <= d_max; d += 64) score(A, u, Sa, d, b);
+                    int best = b.d;
+                    double bc = best != 0 ? cost(b.num, var_a[u], u + (best ^ sgn) - sgn) : -__builtin_inf();
 #pragma unroll
                     for (int off = 32; off >= 1; off >>= 1) {
                         const double oc = __shfl_xor(bc, off);

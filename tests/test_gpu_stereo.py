@@ -139,3 +139,31 @@ def test_lanes_from_estimated_disparity():
         assert np.array_equal(out[b], want)
         r = par.compare_frame(res, b, L[b], want, 128)
         assert r.n_lanes >= 2
+
+
+@pytest.mark.parametrize("rho,w,h,n,d_max,tau", [
+    # every form of the sweep (eight, four and two lanes a pixel in strips; a frame a workgroup),
+    # at every block size, with row blocks of one row, of all their rows and one more, and widths
+    # at the strips' ends
+    (3, 34, 22, 1, 20, 1), (3, 35, 23, 1, 20, 1), (1, 70, 19, 2, 40, 0), (2, 101, 37, 1, 64, 2), (4, 130, 43, 1, 90, 1),
+    (5, 103, 44, 2, 255, 1), (3, 98, 38, 40, 48, 1), (5, 197, 27, 45, 255, 2), (1, 99, 34, 50, 30, 1),
+    (3, 226, 23, 129, 60, 1), (2, 227, 20, 130, 33, 0), (4, 226, 25, 129, 140, 1), (5, 120, 26, 200, 255, 1),
+    (3, 64, 22, 600, 30, 1), (4, 64, 24, 600, 30, 1), (5, 90, 24, 600, 60, 1),
+])
+def test_sweep_forms(rho, w, h, n, d_max, tau):
+    rng = np.random.default_rng(1000 * rho + w)
+    views = []
+    for k in range(2):
+        wide = rng.integers(0, 256, size=(h, w + 24)).astype(np.uint8)
+        shift = np.minimum(2 + np.arange(h) // 4 + 3 * k, 20)
+        left = np.ascontiguousarray(wide[:, :w])
+        right = np.stack([wide[v, shift[v]:shift[v] + w] for v in range(h)])
+        left[: h // 3, w // 2:] = 77                          # flat blocks, and pixels above a flat band
+        right[: h // 3, w // 2:] = 77
+        left[2 * h // 3, :] = 50                              # an equal row: equal costs side by side
+        right[2 * h // 3, :] = 50
+        views.append((left, np.ascontiguousarray(right)))
+    got = _stereo_gpu(np.stack([views[i % 2][0] for i in range(n)]), np.stack([views[i % 2][1] for i in range(n)]),
+                      d_max, rho=rho, tau=tau)
+    for i in sorted({0, 1, n - 2, n - 1} & set(range(n))):
+        _check(views[i % 2][0][None], views[i % 2][1][None], d_max, [g[i:i + 1] for g in got], rho=rho, tau=tau)
