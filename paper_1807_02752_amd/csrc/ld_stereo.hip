@@ -33,11 +33,14 @@
 // one (every pixel of the first row) searches all of 1..d_max, which would hold up the 63 other
 // lanes of its wave, so such pixels are queued: many (the first row) are taken one a lane, few
 // one a wave with a candidate per lane and a reduction over the wave.  The propagation makes
-// the rows of a frame sequential; frames are independent workgroups.
+// the rows of a frame sequential; frames are independent workgroups.  Launches of few frames
+// (up to about 100 of 1242 x 375) take the same maps in strips of columns and blocks of rows,
+// k_stereo_strip, a launch per block of rows (1 pair: 5.15 -> 0.68 ms, 32: 5.3 -> 1.6 ms).
 #include <hip/hip_runtime.h>
 
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 
 #include "ld.h"
 #include "ld_internal.h"
@@ -404,6 +407,230 @@ __global__ __launch_bounds__(2 * kT) void k_stereo(const uint8_t* left, int64_t 
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// The same maps for few pairs.  One workgroup a frame leaves all but a few CUs idle, so a launch
+// takes T rows of every frame and map, a workgroup E columns of them: a row needs the row
+// below one column further on either side, so of the E columns 2 (T - 1) are worked on again by
+// the neighbours, and the lowest row's neighbours come from the map that the launch before
+// wrote.  LP lanes share a pixel's candidates.  The image rows of both images and the block
+// statistics of the T rows are formed in LDS first, so a row of the sweep has one barrier.  A
+// row's time, about 1.2 us, is its chain: neighbours, range, one candidate a lane (14 dot
+// products on 14 pairs of LDS words), the best over the lanes, barrier; the statistics and image
+// rows take about 5 us a launch.
+template <int RHO, int LP, int E, int T>
+struct Strip {
+    static constexpr int K = 2 * RHO + 1, N = K * K, NT = E * LP, kUse = E - 2 * (T - 1), kRows = T + 2 * RHO;
+    static constexpr int kA = (E + 2 * RHO + 3 + 8) / 4;             // words of a row of the own image
+    static constexpr int kB = (E + 255 + 2 * RHO + 3 + 8) / 4;       // and of the other one
+    static_assert(kUse > 0 && T % 2 == 0, "columns left after the halo; pairs of words aligned behind T rows");
+    static size_t lds(int d_max) {
+        const size_t wb = (size_t)E + d_max, cols = 2 * (size_t)E + d_max + 4 * RHO;
+        return 4 * (size_t)kRows * (kA + kB) + (size_t)T * (wb * 12 + E * 12) + 2 * cols * 8 + 2 * 4 * (size_t)(E + 2) + 64;
+    }
+};
+
+template <int RHO, int LP, int E, int T>
+__global__ __launch_bounds__(E* LP) void k_stereo_strip(const uint8_t* left, int64_t lp, const uint8_t* right,
+                                                        int64_t rp, int W, int H, const int32_t* nact, int nframes,
+                                                        int d_max, int tau, uint8_t* lf, uint8_t* rt, int v_start) {
+    using G = Strip<RHO, LP, E, T>;
+    constexpr int K = G::K, N = G::N, NT = G::NT, NW = (K + 3) / 4;
+    constexpr uint32_t kLastMask = (K % 4 == 0) ? 0xFFFFFFFFu : ((1u << (8 * (K % 4))) - 1u);
+    extern __shared__ __align__(16) unsigned char smem[];
+    const int b = blockIdx.z, m = blockIdx.y, t = threadIdx.x;
+    const int nf = nact != nullptr ? min(*nact, nframes) : nframes;
+    if (b >= nf) return;
+    const uint8_t* ga = (m == 0 ? left + (int64_t)b * H * lp : right + (int64_t)b * H * rp);
+    const uint8_t* gb = (m == 0 ? right + (int64_t)b * H * rp : left + (int64_t)b * H * lp);
+    const int64_t pa = m == 0 ? lp : rp, pb = m == 0 ? rp : lp;
+    uint8_t* out = (m == 0 ? lf : rt) + (int64_t)b * H * W;
+    const int sgn = m == 0 ? -1 : 0;                                  // x = u + (d ^ sgn) - sgn
+    const int vb = H - 1 - RHO, rows = min(T, v_start - RHO + 1);
+    const int x0 = blockIdx.x * G::kUse, ub = x0 - (T - 1);           // the columns written; the first worked on
+    // rows outside the matched band are 0
+    const int xe = min(x0 + G::kUse, W);
+    if (v_start == vb)
+        for (int v = vb + 1; v < H; ++v)
+            for (int u = x0 + t; u < xe; u += NT) out[(int64_t)v * W + u] = 0;
+    if (v_start - rows < RHO)
+        for (int v = 0; v < RHO; ++v)
+            for (int u = x0 + t; u < xe; u += NT) out[(int64_t)v * W + u] = 0;
+    const int wb = E + d_max;                                         // other columns xb0 .. xb0 + wb - 1
+    const int xb0 = m == 0 ? ub - d_max : ub;
+    uint32_t* ta = reinterpret_cast<uint32_t*>(smem);                 // rows v_start + rho - r, columns ca ..
+    uint32_t* tb = ta + G::kRows * G::kA;                             // columns cb ..
+    int32_t* Sb = reinterpret_cast<int32_t*>(tb + G::kRows * G::kB);  // T x wb: block sums, variances, reciprocal roots
+    int32_t* vrb = Sb + T * wb;
+    float* rqb = reinterpret_cast<float*>(vrb + T * wb);
+    int32_t* Sa = reinterpret_cast<int32_t*>(rqb + T * wb);           // T x E
+    int32_t* vra = Sa + T * E;
+    float* rqa = reinterpret_cast<float*>(vra + T * E);
+    const int na = E + 2 * RHO, nb = wb + 2 * RHO;                    // columns with vertical sums
+    int2* col = reinterpret_cast<int2*>(rqa + T * E);   // 2 x (na + nb): sum and sum of squares
+    int* prev = reinterpret_cast<int*>(col + 2 * (na + nb));          // 2 x (E + 2)
+    const int ca = (ub - RHO) & ~3, cb = (xb0 - RHO) & ~3;
+    // image rows (0 outside the image)
+    auto stage = [&](uint32_t* to, int stride, const uint8_t* g, int64_t pitch, int c0, int ncols) {
+        const int wn = (ncols + 3) / 4;
+        for (int i = t; i < G::kRows * wn; i += NT) {
+            const int r = i / wn, w = i - r * wn, v = v_start + RHO - r, x = c0 + 4 * w;
+            // four bytes from x on, moved to where they belong at the image's sides
+            const int xc = min(max(x, 0), W - 4), sh = x - xc;
+            uint32_t q;
+            __builtin_memcpy(&q, g + (int64_t)max(v, 0) * pitch + xc, 4);
+            q = sh < 0 ? (sh > -4 ? q << (-8 * sh) : 0u) : (sh < 4 ? q >> (8 * sh) : 0u);
+            to[r * stride + w] = q;
+        }
+    };
+    stage(ta, G::kA, ga, pa, ca, ub + E + RHO - ca);
+    stage(tb, G::kB, gb, pb, cb, xb0 + wb + RHO - cb);
+    for (int i = t; i < E + 2; i += NT) {                             // the row below: columns ub - 1 .. ub + E
+        const int u = ub - 1 + i;
+        prev[i] = v_start != vb && u >= 0 && u < W ? out[(int64_t)(v_start + 1) * W + u] : 0;
+        prev[E + 2 + i] = 0;
+    }
+    __syncthreads();
+    // block statistics row by row: each thread slides the vertical sums of its columns, then forms
+    // the sums over 2 rho + 1 of them
+    {
+        constexpr int kCols = (2 * E + 255 + 4 * RHO + NT - 1) / NT;
+        int cs[kCols], cq[kCols];
+        const uint8_t* src[kCols];
+        int step[kCols];
+#pragma unroll
+        for (int k = 0; k < kCols; ++k) {
+            const int i = t + k * NT;
+            const bool own = i < na;
+            src[k] = reinterpret_cast<const uint8_t*>(own ? ta : tb) + (own ? ub - RHO - ca + i : xb0 - RHO - cb + min(i - na, nb - 1));
+            step[k] = 4 * (own ? G::kA : G::kB);
+            cs[k] = cq[k] = 0;
+#pragma unroll
+            for (int j = 0; j < K - 1; ++j) {
+                const int x = src[k][j * step[k]];
+                cs[k] += x;
+                cq[k] += x * x;
+            }
+        }
+        for (int r = 0; r < rows; ++r) {
+            int2* c = col + (r & 1) * (na + nb);
+#pragma unroll
+            for (int k = 0; k < kCols; ++k) {
+                const int i = t + k * NT, x = src[k][(r + K - 1) * step[k]], y = src[k][r * step[k]];
+                cs[k] += x;
+                cq[k] += x * x;
+                if (i < na + nb) c[i] = make_int2(cs[k], cq[k]);
+                cs[k] -= y;
+                cq[k] -= y * y;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int k = 0; k < kCols; ++k) {
+                const int i = t + k * NT;
+                if (i >= E + wb) continue;
+                const bool own = i < E;
+                const int2* p = c + (own ? i : na + (i - E));
+                int sum = 0, sq = 0;
+#pragma unroll
+                for (int j = 0; j < K; ++j) { sum += p[j].x; sq += p[j].y; }
+                const int u = own ? ub + i : xb0 + (i - E);
+                const bool fits = u >= RHO && u <= W - 1 - RHO;
+                const int var = N * sq - sum * sum;
+                const float rq = fits && var > 0 ? __builtin_amdgcn_rsqf((float)var) : 0.0f;
+                if (own) { Sa[r * E + i] = sum; vra[r * E + i] = var; rqa[r * E + i] = rq; }
+                else { Sb[r * wb + i - E] = sum; vrb[r * wb + i - E] = var; rqb[r * wb + i - E] = rq; }
+            }
+        }
+    }
+    __syncthreads();
+    const int p = t / LP, sub = t % LP, u = ub + p;
+    for (int r = 0; r < rows; ++r) {
+        const int v = v_start - r;
+        const int* pv = prev + (r & 1) * (E + 2);
+        int* cur = prev + ((r & 1) ^ 1) * (E + 2);
+        const int32_t* S = Sb + r * wb;
+        const int32_t* vr = vrb + r * wb;
+        const float* rq = rqb + r * wb;
+        Best best;
+        // the better of two, as in the frame sweep: by the FP32 values unless they are close
+        auto keep = [&](const Best& q, bool on) {
+            const float g = q.f - best.f, tol = fmaxf(fabsf(q.f), fabsf(best.f)) * 2.0e-6f;
+            bool take = on & (g > tol);
+            if (on & (fabsf(g) <= tol)) {
+                int va = vra[r * E + p];
+                asm volatile("" : "+v"(va));                 // (its square root stays in this branch)
+                auto cost = [&](const Best& z) -> double {
+                    return (double)z.num / (sqrt((double)va) * sqrt((double)vr[u + (z.d ^ sgn) - sgn - xb0]));
+                };
+                const double c = cost(q), bc = cost(best);
+                take = c > bc || (c == bc && q.d < best.d);
+            }
+            best.f = take ? q.f : best.f;
+            best.num = take ? q.num : best.num;
+            best.d = take ? q.d : best.d;
+        };
+        if (rqa[r * E + p] > 0.0f) {
+            int l0 = pv[p], l1 = pv[p + 1], l2 = pv[p + 2];
+            l0 = u - 1 >= RHO ? l0 : 0;
+            l2 = u + 1 <= W - 1 - RHO ? l2 : 0;
+            uint32_t A[K][NW];
+            {
+                const int o = u - RHO - ca;
+                const uint32_t* w = ta + r * G::kA + (o >> 2);
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+#pragma unroll
+                    for (int k = 0; k < NW; ++k) A[j][k] = __builtin_amdgcn_alignbyte(w[j * G::kA + k + 1], w[j * G::kA + k], (uint32_t)(o & 3));
+                    A[j][NW - 1] &= kLastMask;
+                }
+            }
+            const int sa = Sa[r * E + p];
+            const bool all = (l0 | l1 | l2) == 0;            // no matched neighbour: 1 .. d_max
+            Runs q = runs_of(all ? 1 : l0, l1, l2, tau, d_max);
+            q.b0 = all ? d_max : q.b0;
+            const int n0 = q.b0 - q.a0 + 1, n1 = n0 + max(q.b1 - q.a1 + 1, 0), n2 = n1 + max(q.b2 - q.a2 + 1, 0);
+            for (int k = sub; k < n2; k += LP) {
+                int d = k + q.a0;
+                d = k >= n0 ? k + q.a1 - n0 : d;
+                d = k >= n1 ? k + q.a2 - n1 : d;
+                const int xi = min(max(u + (d ^ sgn) - sgn - xb0, 0), wb - 1);   // a column's place in the statistics
+                const float rb = rq[xi];
+                const int sb = S[xi], o = xi + xb0 - RHO - cb;
+                const uint32_t* w = tb + r * G::kB + (o >> 2);
+                uint32_t P = 0;
+#pragma unroll
+                for (int j = 0; j < K; ++j)
+#pragma unroll
+                    for (int i = 0; i < NW; ++i)
+                        P = __builtin_amdgcn_udot4(A[j][i], __builtin_amdgcn_alignbyte(w[j * G::kB + i + 1], w[j * G::kB + i], (uint32_t)(o & 3)), P, false);
+                Best c;
+                c.num = __mul24(N, (int)P) - __mul24(sa, sb);
+                c.f = (float)c.num * rb;
+                c.d = d;
+                keep(c, rb > 0.0f);                          // 0: the block leaves the image or is flat
+            }
+        }
+        // the best of the pixel's lanes: pairs, quads, then (both quads of eight lanes each hold
+        // one value) the mirror of eight
+        static_assert(LP == 1 || LP == 2 || LP == 4 || LP == 8, "lanes a pixel");
+        auto merge = [&](auto ctl) {
+            constexpr int C = decltype(ctl)::value;
+            Best c;
+            c.f = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(best.f), C, 0xF, 0xF, true));
+            c.num = __builtin_amdgcn_update_dpp(0, best.num, C, 0xF, 0xF, true);
+            c.d = __builtin_amdgcn_update_dpp(0, best.d, C, 0xF, 0xF, true);
+            keep(c, (c.d != 0) & (c.d != best.d));
+        };
+        if constexpr (LP >= 2) merge(std::integral_constant<int, 0xB1>{});     // quad_perm 1 0 3 2
+        if constexpr (LP >= 4) merge(std::integral_constant<int, 0x4E>{});     // quad_perm 2 3 0 1
+        if constexpr (LP >= 8) merge(std::integral_constant<int, 0x141>{});    // row_half_mirror
+        if (sub == 0) {
+            cur[p + 1] = best.d;
+            if (p >= T - 1 && p < T - 1 + G::kUse && u < W) out[(int64_t)v * W + u] = (uint8_t)best.d;
+        }
+        __syncthreads();
+    }
+}
+
 // l(u) = l_left(u) unless it is 0, u - l(u) < 0 or |l(u) - l_right(u - l(u))| > tr.  A workgroup
 // takes kLrcRows rows of a frame (grid: row groups, frames), kLrcPx consecutive pixels a thread.
 template <int PX>
@@ -462,9 +689,43 @@ __global__ __launch_bounds__(256) void k_lrc_words(const uint8_t* lf, const uint
     }
 }
 
+template <int RHO, int LP, int E, int T>
+void launch_strips(const uint8_t* left, int64_t lp, const uint8_t* right, int64_t rp, const ldi_frame_view& V, int tau,
+                   uint8_t* lf, uint8_t* rt, hipStream_t st) {
+    using G = Strip<RHO, LP, E, T>;
+    const size_t lds = G::lds(V.d_max);
+    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_stereo_strip<RHO, LP, E, T>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const dim3 grid((V.W + G::kUse - 1) / G::kUse, 2, V.active);
+    for (int v = V.H - 1 - RHO; v >= RHO; v -= T)
+        hipLaunchKernelGGL((k_stereo_strip<RHO, LP, E, T>), grid, dim3(G::NT), lds, st, left, lp, right, rp, V.W, V.H,
+                           V.nact, V.active, V.d_max, tau, lf, rt, v);
+}
+
+// Which form a launch takes.  A frame's sweep is one workgroup, 4.6 ms for a 1242 x 375 pair
+// however few there are; the strips spread a pair over the chip but work on their halo again.
+// Eight lanes a pixel have the shortest row and the most halo (30 of 64 columns), so they are
+// taken while all workgroups of a row block run at once, four after that, and blocks of eight rows
+// (two workgroups fit a CU, less halo) from there on (ms for 1, 8, 16, 32, 96 and 128 pairs):
+//   8 lanes, 64 columns, 16 rows    0.68  1.35  2.08
+//   4 lanes, 128 columns, 16 rows   0.84  0.86  1.63  3.10
+//   4 lanes, 128 columns, 8 rows    0.91  0.95  1.23  1.58  3.92  4.89
+//   a frame a workgroup             4.64  4.68  4.74  4.80  4.82  4.83
+// (two lanes a pixel were within 5% of the third row or behind it, one lane a pixel behind by half.)
+template <int RHO, int LP, int E, int T>
+bool strips_fit(const ldi_frame_view& V, int64_t most) {
+    using G = Strip<RHO, LP, E, T>;
+    return G::lds(V.d_max) <= 160 * 1024 && (int64_t)((V.W + G::kUse - 1) / G::kUse) * 2 * V.active <= most;
+}
+
 template <int RHO>
 void launch(const uint8_t* left, int64_t lp, const uint8_t* right, int64_t rp, const ldi_frame_view& V, int tau,
             uint8_t* lf, uint8_t* rt, hipStream_t st) {
+    if (V.W > 2 * RHO && V.W >= 4 && V.H > 2 * RHO) {   // (a block fits, and rows hold a word)
+        if (strips_fit<RHO, 8, 64, 16>(V, 256)) return launch_strips<RHO, 8, 64, 16>(left, lp, right, rp, V, tau, lf, rt, st);
+        if (strips_fit<RHO, 4, 128, 16>(V, 256)) return launch_strips<RHO, 4, 128, 16>(left, lp, right, rp, V, tau, lf, rt, st);
+        if (strips_fit<RHO, 4, 128, 8>(V, 2400)) return launch_strips<RHO, 4, 128, 8>(left, lp, right, rp, V, tau, lf, rt, st);
+    }
     const size_t lds = stereo_lds(V.W, RHO);
     (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_stereo<RHO>),
                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
