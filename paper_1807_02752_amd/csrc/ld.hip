@@ -140,32 +140,56 @@ __device__ __forceinline__ void block_argmin_i64(int64_t& v, int& i, int64_t* rv
 // ------------------------------------------------------------------------------------------
 // RANSAC (Alg. "beta/gamma estimation with the assist of RANSAC").  Each round scores up to
 // 64 random samples of DEG+1 points, one per lane of wave 0, and the points are split over
-// the waves of the workgroup for the inlier count; the best sample's outliers are removed by a stable
-// ballot compaction; the loop ends when the inliers reach eps of the round's points.  The
-// final model is refitted on the survivors from exact 128-bit moments.
+// the waves of the workgroup for the inlier count; the best sample's outliers are removed by a
+// stable ballot compaction; the loop ends when the inliers reach eps of the round's points.
+// The final model is refitted on the survivors from exact 128-bit moments.
+//
+// A round is a chain of one wave's latency (samples and fits) and of FP64 issue (the counts:
+// 64 samples x the points x 16 operations).  So the random words of the next round, which depend
+// on no result, are formed by other waves beside this round's fits; the points move with the
+// compaction, so a count reads them four at a time with no index between; the best sample is
+// found by every wave for itself; and a fit sums in int64 whatever fits there.  A round of a
+// 1242 x 375 frame's V_px took 13.5 us (words 2.4, fit 2.5, counts 7.5 over three waves) and takes
+// 6.2 (words and draw 0.9, fit 1.8, counts 2.0 over eight); k_vpx_ransac 87 -> 44 us.
 struct RansacShared {
     double models[kMaxHyp][5];
     int mvalid[kMaxHyp];            // 0 invalid, 1 fitted (s basis), 2 caller seed (raw basis)
     int counts[kMaxWaves][kMaxHyp];
-    int wsum[kMaxWaves];
+    uint64_t words[2][8][kMaxHyp];  // random words of this round and the next
+    int wsum[2][kMaxWaves];
     int red[kMaxWaves];
-    int best_h, best_n;
     i128 mred[kMaxWaves][14];
+    double mom[14];
 };
 
+// Model values are Horner sums in (x - off) * scale: the s basis, or x itself for a caller seed.
 template <int DEG>
-__device__ __forceinline__ bool is_inlier(const double* m, int kind, int center, int kshift, int x, int y,
-                                          double tr) {
-    double fv = (kind == 2) ? eval_raw<DEG>(m, x) : eval_s<DEG>(m, center, kshift, x);
-    double res = (double)y - fv;
+__device__ __forceinline__ bool is_inlier(const double* m, int off, double scale, int x, int y, double tr) {
+    const double a = (double)(x - off) * scale;
+    double f = m[DEG];
+#pragma unroll
+    for (int p = DEG - 1; p >= 0; --p) f = f * a + m[p];
+    const double res = (double)y - f;
     return res * res < tr;
 }
 
+// maximum over the wave, in every lane
+__device__ __forceinline__ int wave_max_dpp(int x) {
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false));     // quad_perm 1 0 3 2
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false));     // quad_perm 2 3 0 1
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x141, 0xF, 0xF, false));    // row_half_mirror
+    x = max(x, __builtin_amdgcn_update_dpp(x, x, 0x140, 0xF, 0xF, false));    // row_mirror: rows of 16 done
+    return max(max(__builtin_amdgcn_readlane(x, 0), __builtin_amdgcn_readlane(x, 16)),
+               max(__builtin_amdgcn_readlane(x, 32), __builtin_amdgcn_readlane(x, 48)));
+}
+
+// X, Y: the points (16-byte aligned, lengths rounded up to 4, as X2 and Y2, which take the
+// survivors in turn); both pairs are overwritten.
 template <int DEG>
-__device__ void ransac_block(const int* X, const int* Y, int n0, int* cur, int* cur2, uint32_t* bitmap,
-                             int bitmap_words, RansacShared& S, double tr, const ld_params& P, uint64_t key1,
-                             uint64_t ctr0, int stage, const double* seed_raw, FitRes* out, int* trace) {
-    constexpr int s = DEG + 1;
+__device__ void ransac_block(int* X, int* Y, int n0, int* X2, int* Y2, uint32_t* bitmap, int bitmap_words,
+                             RansacShared& S, double tr, const ld_params& P, uint64_t key1, uint64_t ctr0, int stage,
+                             const double* seed_raw, FitRes* out, int* trace) {
+    constexpr int s = DEG + 1, kBlocks = (s + 3) / 4, NM = Moments<DEG>::kCount;
     const int t = threadIdx.x, lane = lane_id(), wave = t / kWave, nw = nwaves(), nt = blockDim.x;
     FitRes res;
     res.ok = 0; res.flags = 0; res.center = 0; res.kshift = 0; res.rounds = 0; res.n_surv = 0;
@@ -175,6 +199,21 @@ __device__ void ransac_block(const int* X, const int* Y, int n0, int* cur, int* 
         __syncthreads();
         return;
     }
+    const int n_hyp = min(P.n_hyp, kMaxHyp);
+    auto philox = [&](int r, int blk) {
+        return philox4x64_10(ctr0, ((uint64_t)stage << 32) | (uint64_t)(uint32_t)r, (uint64_t)lane, (uint64_t)blk, P.seed,
+                             key1);
+    };
+    // the first random words of round r, a block of four a wave
+    auto draw = [&](int r) {
+        for (int blk = 0; blk < kBlocks; ++blk)
+            if (wave == (1 + blk) % nw) {
+                const U64x4 w = philox(r, blk);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) S.words[r & 1][4 * blk + q][lane] = w.w[q];
+            }
+    };
+    draw(0);
     int xmn = 0x7fffffff, xmx = -0x7fffffff;
     for (int j = t; j < n0; j += nt) { xmn = min(xmn, X[j]); xmx = max(xmx, X[j]); }
     xmn = block_min_i32(xmn, S.red);
@@ -185,13 +224,11 @@ __device__ void ransac_block(const int* X, const int* Y, int n0, int* cur, int* 
     while ((1 << k) < wmax) ++k;
     res.center = center;
     res.kshift = k;
-    for (int j = t; j < n0; j += nt) cur[j] = j;
+    const double scale = ldexp(1.0, -k);
     const int need = max(s, (n0 + 9) / 10);
-    const int n_hyp = min(P.n_hyp, kMaxHyp);
     int n_cur = n0;
     bool converged = false;
     int r = 0;
-    __syncthreads();
     for (; r < P.max_rounds; ++r) {
         // ---- phase A: one sample + fit per hypothesis (wave 0)
         if (t < n_hyp) {
@@ -207,116 +244,118 @@ __device__ void ransac_block(const int* X, const int* Y, int n0, int* cur, int* 
 #pragma unroll
                 for (int e = 0; e < s; ++e) pick[e] = -1;
                 int got = 0;
-                for (int blk = 0; blk < 16 && got < s; ++blk) {
-                    U64x4 w = philox4x64_10(ctr0, ((uint64_t)stage << 32) | (uint64_t)(uint32_t)r, (uint64_t)t,
-                                            (uint64_t)blk, P.seed, key1);
+                auto next = [&](uint64_t w) {
+                    const int ix = (int)__umul64hi(w, (uint64_t)n_cur);
+                    bool dup = false;
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const int ix = (int)__umul64hi(w.w[q], (uint64_t)n_cur);
-                        bool dup = false;
+                    for (int e = 0; e < s; ++e) dup = dup || (e < got && pick[e] == ix);
+                    const bool take = got < s && !dup;
 #pragma unroll
-                        for (int e = 0; e < s; ++e) dup = dup || (e < got && pick[e] == ix);
-                        const bool take = got < s && !dup;
+                    for (int e = 0; e < s; ++e) pick[e] = (take && e == got) ? ix : pick[e];
+                    got += take ? 1 : 0;
+                };
 #pragma unroll
-                        for (int e = 0; e < s; ++e) pick[e] = (take && e == got) ? ix : pick[e];
-                        got += take ? 1 : 0;
+                for (int q = 0; q < s; ++q) next(S.words[r & 1][q][lane]);
+                if (got < s) {
+                    for (int q = s; q < 4 * kBlocks; ++q) next(S.words[r & 1][q][lane]);
+                    for (int blk = kBlocks; blk < 16 && got < s; ++blk) {
+                        const U64x4 w = philox(r, blk);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) next(w.w[q]);
                     }
                 }
                 if (got == s) {
                     int px[s], py[s];
 #pragma unroll
-                    for (int e = 0; e < s; ++e) { px[e] = X[cur[pick[e]]]; py[e] = Y[cur[pick[e]]]; }
+                    for (int e = 0; e < s; ++e) { px[e] = X[pick[e]]; py[e] = Y[pick[e]]; }
                     bool distinct = true;
 #pragma unroll
                     for (int e = 1; e < s; ++e)
 #pragma unroll
                         for (int f = 0; f < e; ++f) distinct = distinct && (px[f] != px[e]);
                     if (distinct) {
-                        Moments M;
-                        moments_zero(M);
+                        Moments<DEG> M;
+                        moments_zero<DEG>(M);
 #pragma unroll
                         for (int e = 0; e < s; ++e) moments_add<DEG>(M, px[e], py[e], center);
-                        kind = solve_moments<DEG>(M, k, model) ? 1 : 0;
+                        double mom[NM];
+#pragma unroll
+                        for (int i = 0; i < NM; ++i) mom[i] = moment_f64<DEG>(M, i);
+                        kind = solve_moments<DEG>(mom, k, model) ? 1 : 0;
                     }
                 }
             }
             for (int p = 0; p < 5; ++p) S.models[t][p] = model[p];
             S.mvalid[t] = kind;
         }
+        if (r + 1 < P.max_rounds) draw(r + 1);
         __syncthreads();
-        // ---- phase B: inlier counts, hypothesis = lane, points split over the waves
+        // ---- phase B: inlier counts, hypothesis = lane, points split over the waves by fours
         {
-            const int h = lane;
             int cnt = -1;
-            if (h < n_hyp && S.mvalid[h] != 0) {
-                double m[5];
+            if (lane < n_hyp && S.mvalid[lane] != 0) {
+                double m[DEG + 1];
 #pragma unroll
-                for (int p = 0; p < 5; ++p) m[p] = S.models[h][p];
-                const int kind = S.mvalid[h];
-                int c4[4] = {0, 0, 0, 0};
-                int jj = wave;
-                for (; jj + 3 * nw < n_cur; jj += 4 * nw) {   // four independent evaluations
-#pragma unroll
-                    for (int u = 0; u < 4; ++u) {
-                        const int j = cur[jj + u * nw];
-                        c4[u] += is_inlier<DEG>(m, kind, center, k, X[j], Y[j], tr) ? 1 : 0;
-                    }
+                for (int p = 0; p <= DEG; ++p) m[p] = S.models[lane][p];
+                const bool raw = S.mvalid[lane] == 2;
+                const int off = raw ? 0 : center;
+                const double sc = raw ? 1.0 : scale;
+                cnt = 0;
+#pragma unroll 2
+                for (int j = 4 * wave; j < n_cur; j += 4 * nw) {
+                    const int4 x = *reinterpret_cast<const int4*>(X + j), y = *reinterpret_cast<const int4*>(Y + j);
+                    const bool i0 = is_inlier<DEG>(m, off, sc, x.x, y.x, tr), i1 = is_inlier<DEG>(m, off, sc, x.y, y.y, tr);
+                    const bool i2 = is_inlier<DEG>(m, off, sc, x.z, y.z, tr), i3 = is_inlier<DEG>(m, off, sc, x.w, y.w, tr);
+                    cnt += (i0 ? 1 : 0) + ((i1 & (j + 1 < n_cur)) ? 1 : 0) + ((i2 & (j + 2 < n_cur)) ? 1 : 0) +
+                           ((i3 & (j + 3 < n_cur)) ? 1 : 0);
                 }
-                for (; jj < n_cur; jj += nw) {
-                    const int j = cur[jj];
-                    c4[0] += is_inlier<DEG>(m, kind, center, k, X[j], Y[j], tr) ? 1 : 0;
-                }
-                cnt = (c4[0] + c4[1]) + (c4[2] + c4[3]);
             }
-            S.counts[wave][h] = cnt;
+            S.counts[wave][lane] = cnt;
         }
         __syncthreads();
-        // ---- phase C: best hypothesis (most inliers, lowest index)
-        if (wave == 0) {
-            int tot = -1;
-            if (lane < n_hyp && S.counts[0][lane] >= 0) {
-                tot = 0;
-                for (int w = 0; w < nw; ++w) tot += S.counts[w][lane];
-            }
-            int bn = tot, bh = lane;
-            for (int o = 32; o > 0; o >>= 1) {
-                int on = __shfl_xor(bn, o, kWave), oh = __shfl_xor(bh, o, kWave);
-                if (on > bn || (on == bn && oh < bh)) { bn = on; bh = oh; }
-            }
-            if (lane == 0) { S.best_h = bn >= 0 ? bh : -1; S.best_n = bn; }
+        // ---- phase C: best hypothesis (most inliers, lowest index), each wave for itself
+        int tot = -1;
+        if (S.counts[0][lane] >= 0) {
+            tot = 0;
+            for (int w = 0; w < nw; ++w) tot += S.counts[w][lane];
         }
-        __syncthreads();
-        const int best_h = S.best_h, best_n = S.best_n;
+        const int key = wave_max_dpp(tot < 0 ? -1 : tot * kMaxHyp + (kMaxHyp - 1 - lane));
+        const int best_h = key < 0 ? -1 : kMaxHyp - 1 - key % kMaxHyp, best_n = key < 0 ? -1 : key / kMaxHyp;
         if (trace && t == 0) { trace[3 * r] = best_h; trace[3 * r + 1] = best_n; trace[3 * r + 2] = n_cur; }
         if (best_h < 0 || best_n < need) { ++r; break; }
         // ---- phase D: keep the inliers of the best sample, in order
         {
-            const double* m = S.models[best_h];
-            const int kind = S.mvalid[best_h];
+            double m[DEG + 1];
+#pragma unroll
+            for (int p = 0; p <= DEG; ++p) m[p] = S.models[best_h][p];
+            const bool raw = S.mvalid[best_h] == 2;
+            const int off = raw ? 0 : center;
+            const double sc = raw ? 1.0 : scale;
             int base = 0;
-            for (int c0 = 0; c0 < n_cur; c0 += nt) {
-                int jj = c0 + t, j = 0;
+            for (int c0 = 0, par = 0; c0 < n_cur; c0 += nt, par ^= 1) {
+                const int j = c0 + t;
+                int x = 0, y = 0;
                 bool pred = false;
-                if (jj < n_cur) {
-                    j = cur[jj];
-                    pred = is_inlier<DEG>(m, kind, center, k, X[j], Y[j], tr);
+                if (j < n_cur) {
+                    x = X[j];
+                    y = Y[j];
+                    pred = is_inlier<DEG>(m, off, sc, x, y, tr);
                 }
-                uint64_t bal = __ballot(pred);
-                int wpre = __popcll(bal & lanes_below());
-                if (lane == 0) S.wsum[wave] = __popcll(bal);
+                const uint64_t bal = __ballot(pred);
+                if (lane == 0) S.wsum[par][wave] = __popcll(bal);
                 __syncthreads();
-                int off = base, tot = 0;
+                int o = base + __popcll(bal & lanes_below());
                 for (int w = 0; w < nw; ++w) {
-                    if (w < wave) off += S.wsum[w];
-                    tot += S.wsum[w];
+                    const int c = S.wsum[par][w];
+                    o += w < wave ? c : 0;
+                    base += c;
                 }
-                if (pred) cur2[off + wpre] = j;
-                base += tot;
-                __syncthreads();
+                if (pred) { X2[o] = x; Y2[o] = y; }
             }
         }
         const bool done = (int64_t)P.eps_den * best_n >= (int64_t)P.eps_num * n_cur;
-        int* tmp = cur; cur = cur2; cur2 = tmp;
+        int* tmp = X; X = X2; X2 = tmp;
+        tmp = Y; Y = Y2; Y2 = tmp;
         n_cur = best_n;
         __syncthreads();
         if (done) { converged = true; ++r; break; }
@@ -327,33 +366,35 @@ __device__ void ransac_block(const int* X, const int* Y, int n0, int* cur, int* 
     // ---- final fit on the survivors: distinct abscissae, exact moments, solve
     for (int i = t; i < bitmap_words; i += nt) bitmap[i] = 0u;
     __syncthreads();
-    for (int jj = t; jj < n_cur; jj += nt) {
-        int x = X[cur[jj]];
+    Moments<DEG> M;
+    moments_zero<DEG>(M);
+    for (int j = t; j < n_cur; j += nt) {                   // (at most 4096 points over 192 threads)
+        const int x = X[j];
         atomicOr(&bitmap[x >> 5], 1u << (x & 31));
+        moments_add<DEG>(M, x, Y[j], center);
     }
+    i128 v[DEG == 2 ? 8 : 16];
+    static_assert(NM == 8 || NM == 14, "moments");
+#pragma unroll
+    for (int i = 0; i < NM; ++i) v[i] = moment_i128<DEG>(M, i);
+    if constexpr (NM == 14) v[14] = v[15] = 0;
+    const i128 mine = wave_sums_i128(v);
+    if (lane < NM) S.mred[wave][lane] = mine;
     __syncthreads();
     int pc = 0;
     for (int i = t; i < bitmap_words; i += nt) pc += __popc(bitmap[i]);
-    const int distinct = block_sum_i32(pc, S.red);
-    Moments M;
-    moments_zero(M);
-    for (int jj = t; jj < n_cur; jj += nt) moments_add<DEG>(M, X[cur[jj]], Y[cur[jj]], center);
-    for (int p = 0; p <= 2 * DEG; ++p) M.sw[p] = wave_sum_i128(M.sw[p]);
-    for (int p = 0; p <= DEG; ++p) M.syw[p] = wave_sum_i128(M.syw[p]);
-    if (lane == 0) {
-        for (int p = 0; p <= 2 * DEG; ++p) S.mred[wave][p] = M.sw[p];
-        for (int p = 0; p <= DEG; ++p) S.mred[wave][9 + p] = M.syw[p];
+    if (t < NM) {
+        i128 sum = S.mred[0][t];
+        for (int w = 1; w < nw; ++w) sum += S.mred[w][t];
+        S.mom[t] = i128_to_f64(sum);
     }
-    __syncthreads();
+    const int distinct = block_sum_i32(pc, S.red);          // (its barriers order S.mom too)
     if (t == 0) {
         if (distinct >= s) {
-            Moments T;
-            moments_zero(T);
-            for (int w = 0; w < nw; ++w) {
-                for (int p = 0; p <= 2 * DEG; ++p) T.sw[p] += S.mred[w][p];
-                for (int p = 0; p <= DEG; ++p) T.syw[p] += S.mred[w][9 + p];
-            }
-            if (solve_moments<DEG>(T, k, res.coef)) {
+            double mom[NM];
+#pragma unroll
+            for (int i = 0; i < NM; ++i) mom[i] = S.mom[i];
+            if (solve_moments<DEG>(mom, k, res.coef)) {
                 res.ok = 1;
                 to_raw<DEG>(res.coef, center, k, res.raw);
             }
@@ -538,13 +579,14 @@ __global__ __launch_bounds__(1024) void k_vdisp_fit(Dev d, const uint64_t* strea
     const int H = d.H, D1 = d.D1, d_max = d.d_max;
     // DP rows hold E << 4 (E <= 0, low 4 bits zero); the kVdPad entries past row H - 1 hold a
     // key that loses to every real one
-    int* E0 = reinterpret_cast<int*>(smem);
+    const int D4 = (D1 + 3) / 4 * 4;
+    int* PX = reinterpret_cast<int*>(smem);
+    int* PY = PX + D4;
+    int* cur = PY + D4;
+    int* cur2 = cur + D4;
+    int* E0 = cur2 + D4;
     int* E1 = E0 + H + kVdPad;
-    int* PX = E1 + H + kVdPad;
-    int* PY = PX + D1;
-    int* cur = PY + D1;
-    int* cur2 = cur + D1;
-    uint32_t* bitmap = reinterpret_cast<uint32_t*>(cur2 + D1);
+    uint32_t* bitmap = reinterpret_cast<uint32_t*>(E1 + H + kVdPad);
     const int bm_words = (H + 31) / 32;
     uint8_t* win = reinterpret_cast<uint8_t*>(bitmap + bm_words);   // kVdWalk x kVdWalkCols
     uint8_t* back = d.back_y + (int64_t)b * D1 * H;
@@ -651,12 +693,12 @@ __global__ __launch_bounds__(1024) void k_vdisp_fit(Dev d, const uint64_t* strea
             const int dd = c0 + t;
             const bool pred = dd <= d_max && myT[(int64_t)dd * Hm + cur[dd]] > 0;
             const uint64_t bal = __ballot(pred);
-            if (lane == 0) S.wsum[wave] = __popcll(bal);
+            if (lane == 0) S.wsum[0][wave] = __popcll(bal);
             __syncthreads();
             int off = base, tot = 0;
             for (int w = 0; w < nw; ++w) {
-                if (w < wave) off += S.wsum[w];
-                tot += S.wsum[w];
+                if (w < wave) off += S.wsum[0][w];
+                tot += S.wsum[0][w];
             }
             if (pred) {
                 const int o = off + __popcll(bal & lanes_below());
@@ -1401,16 +1443,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) void 
 }
 
 // S8 for every frame: RANSAC of the quartic through the row-DP path (read back from the path
-// columns), V_px and the track tables.  One 128-thread workgroup per frame (the RANSAC's
-// registers allow many per CU).  Hypothesis 0: the seed of the narrowed search for the frames
-// that kept one (pruned = 1), otherwise the caller's seed rows.
-// Three waves per frame: the inlier counts of a round split the points over the waves, and
-// three 192-thread workgroups per CU still hold every frame of a 1024 batch at once.
-#ifndef LD_RANSAC_THREADS
-#define LD_RANSAC_THREADS 192
-#endif
-constexpr int kRansacThreads = LD_RANSAC_THREADS;
-__global__ __launch_bounds__(kRansacThreads) void k_vpx_ransac(Dev d, const uint64_t* stream_ids, const int64_t* frame_idx,
+// columns), V_px and the track tables.  One workgroup per frame: three waves, so that a 1024
+// batch's frames are all on the chip at once, eight where the chip holds those.  Hypothesis 0:
+// the seed of the narrowed search for the frames that kept one (pruned = 1), otherwise the
+// caller's seed rows.
+constexpr int kRansacThreads = 192, kRansacThreadsFew = 512;
+__global__ __launch_bounds__(kRansacThreadsFew) void k_vpx_ransac(Dev d, const uint64_t* stream_ids, const int64_t* frame_idx,
                                                     const double* seed_gamma, int pruned, double* vp_out) {
     extern __shared__ unsigned char smem[];
     __shared__ RansacShared S;
@@ -1433,11 +1471,12 @@ __global__ __launch_bounds__(kRansacThreads) void k_vpx_ransac(Dev d, const uint
         return;
     }
     const int v_h = fi.v_h;
+    const int H4 = (H + 3) / 4 * 4;
     int* PX = reinterpret_cast<int*>(smem);
-    int* PY = PX + H;
-    int* cur = PY + H;
-    int* cur2 = cur + H;
-    uint32_t* bitmap = reinterpret_cast<uint32_t*>(cur2 + H);
+    int* PY = PX + H4;
+    int* cur = PY + H4;
+    int* cur2 = cur + H4;
+    uint32_t* bitmap = reinterpret_cast<uint32_t*>(cur2 + H4);
     const int bm_words = (H + 31) / 32;
     for (int v = v_h + t; v <= v_max; v += nt) {
         PX[v - v_h] = v;
@@ -2668,7 +2707,7 @@ int vdisp_fit_threads(const Dev& d) {
 }
 
 size_t vdisp_fit_lds(const Dev& d) {
-    return sizeof(int) * (2 * ((size_t)d.H + kVdPad) + 4 * (size_t)d.D1) + sizeof(uint32_t) * ((d.H + 31) / 32) +
+    return sizeof(int) * (2 * ((size_t)d.H + kVdPad) + 4 * (((size_t)d.D1 + 3) / 4 * 4)) + sizeof(uint32_t) * ((d.H + 31) / 32) +
            (size_t)kVdWalk * kVdWalkCols;
 }
 
@@ -2876,10 +2915,12 @@ ld_status run_vpx_dp(ld_frame f, const Dev& d, hipStream_t st) {
 ld_status run_vpx_ransac(ld_frame f, const uint64_t* sid, const int64_t* fidx, const double* seed_gamma, int pruned,
                          double* vp_out, hipStream_t st) {
     const Dev& d = f->d;
-    const size_t l = sizeof(int) * 4 * (size_t)d.H + sizeof(uint32_t) * ((d.H + 31) / 32);
+    const size_t l = sizeof(int) * 4 * (((size_t)d.H + 3) / 4 * 4) + sizeof(uint32_t) * ((d.H + 31) / 32);
     allow_lds(k_vpx_ransac, l);
     ProfScope ps(f, 10, st);
-    hipLaunchKernelGGL(k_vpx_ransac, dim3(f->active), dim3(kRansacThreads), l, st, d, sid, fidx, seed_gamma, pruned, vp_out);
+    // (44 against 47 us for one 1242 x 375 frame, 80 against 99 for 256 of 1920 x 1080)
+    const int nt = f->active <= 2 * kCUs ? kRansacThreadsFew : kRansacThreads;
+    hipLaunchKernelGGL(k_vpx_ransac, dim3(f->active), dim3(nt), l, st, d, sid, fidx, seed_gamma, pruned, vp_out);
     return launch_ok();
 }
 

@@ -52,15 +52,27 @@ __device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t x, int o) {
     return ((uint64_t)hi << 32) | lo;
 }
 
-// exact 128-bit sum across the wave (integer addition is associative: any order is exact)
-__device__ __forceinline__ i128 wave_sum_i128(i128 x) {
+// Exact 128-bit sums across the wave of NV values a lane (NV a power of two): lanes exchange
+// halves of their values, so a lane ends with the sum of value lane % NV (NV - 1 exchanges and
+// log2(64 / NV) more, where a butterfly a value takes 6 NV).
+template <int NV>
+__device__ __forceinline__ i128 wave_sums_i128(i128 (&v)[NV]) {
+    auto other = [](i128 x, int o) {
+        return (i128)(((u128)shfl_xor_u64((uint64_t)((u128)x >> 64), o) << 64) | (u128)shfl_xor_u64((uint64_t)(u128)x, o));
+    };
+    const int l = lane_id();
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        uint64_t lo = shfl_xor_u64((uint64_t)(u128)x, o);
-        uint64_t hi = shfl_xor_u64((uint64_t)((u128)x >> 64), o);
-        x += (i128)(((u128)hi << 64) | (u128)lo);
+    for (int h = NV / 2; h > 0; h >>= 1) {
+        const bool up = (l & h) != 0;
+#pragma unroll
+        for (int i = 0; i < h; ++i) {
+            const i128 lo = v[i], hi = v[i + h], m = up ? ~(i128)0 : (i128)0, x = (lo ^ hi) & m;
+            v[i] = (lo ^ x) + other(hi ^ x, h);
+        }
     }
-    return x;
+#pragma unroll
+    for (int o = NV; o < kWave; o <<= 1) v[0] += other(v[0], o);
+    return v[0];
 }
 
 // (value, index) minimum across the wave; ties go to the smaller index
@@ -107,22 +119,30 @@ __device__ __forceinline__ double i128_to_f64(i128 v) {
     return neg ? -d : d;
 }
 
+// The moments sum w^p (p = 0 .. 2 DEG) and sum y w^p (p = 0 .. DEG) of a few points.  |w| <= 2^11
+// and |y| < 2^14 (frames of at most 4096 rows and columns, w from the middle of the range): up
+// to w^5 and y w^4, sums of up to 32 points fit in int64; the higher powers are exact 64 x 64 ->
+// 128-bit products in 128-bit sums.
+template <int DEG>
 struct Moments {
-    i128 sw[9];    // sum w^p, p = 0..2m
-    i128 syw[5];   // sum y w^p, p = 0..m
+    static constexpr int kLow = 2 * DEG < 5 ? 2 * DEG : 5;
+    static constexpr int kCount = 3 * DEG + 2;
+    int64_t sw[kLow + 1], syw[DEG + 1];
+    i128 hi[2 * DEG > 5 ? 2 * DEG - 5 : 1];
 };
 
-__device__ __forceinline__ void moments_zero(Moments& M) {
+template <int DEG>
+__device__ __forceinline__ void moments_zero(Moments<DEG>& M) {
 #pragma unroll
-    for (int p = 0; p < 9; ++p) M.sw[p] = 0;
+    for (auto& x : M.sw) x = 0;
 #pragma unroll
-    for (int p = 0; p < 5; ++p) M.syw[p] = 0;
+    for (auto& x : M.syw) x = 0;
+#pragma unroll
+    for (auto& x : M.hi) x = 0;
 }
 
-// |w| < 2^12 and |y| < 2^14 (frames of at most 4096 rows and columns): w^p fits in int64 up
-// to p = 5 and y w^p up to p = 4; the higher powers are exact 64 x 64 -> 128-bit products.
 template <int DEG>
-__device__ __forceinline__ void moments_add(Moments& M, int x, int y, int center) {
+__device__ __forceinline__ void moments_add(Moments<DEG>& M, int x, int y, int center) {
     const int64_t w = x - center;
     int64_t pw[6];
     pw[0] = 1;
@@ -130,25 +150,42 @@ __device__ __forceinline__ void moments_add(Moments& M, int x, int y, int center
     for (int p = 1; p <= 5; ++p) pw[p] = pw[p - 1] * w;
 #pragma unroll
     for (int p = 0; p <= 2 * DEG; ++p) {
-        if (p <= 5) M.sw[p] += (i128)pw[p];
-        else M.sw[p] += (i128)pw[4] * (i128)pw[p - 4];
-        if (p <= DEG) M.syw[p] += (i128)(pw[p] * (int64_t)y);
+        if (p <= 5) M.sw[p] += pw[p];
+        else M.hi[p - 6] += (i128)pw[4] * (i128)pw[p - 4];
+        if (p <= DEG) M.syw[p] += pw[p] * (int64_t)y;
     }
 }
 
-// returns true on success (every pivot positive, finite coefficients)
+// moment i of the order sum w^0 .. sum w^(2 DEG), sum y w^0 .. sum y w^DEG
 template <int DEG>
-__device__ bool solve_moments(const Moments& M, int kshift, double* coef) {
+__device__ __forceinline__ i128 moment_i128(const Moments<DEG>& M, int i) {
+    if (i > 2 * DEG) return (i128)M.syw[i - 2 * DEG - 1];
+    return i <= 5 ? (i128)M.sw[i < Moments<DEG>::kLow ? i : Moments<DEG>::kLow] : M.hi[i - 6];
+}
+
+// its double (an integer of up to 64 bits has the same double by either conversion)
+template <int DEG>
+__device__ __forceinline__ double moment_f64(const Moments<DEG>& M, int i) {
+    if (i > 2 * DEG) return (double)M.syw[i - 2 * DEG - 1];
+    return i <= 5 ? (double)M.sw[i < Moments<DEG>::kLow ? i : Moments<DEG>::kLow] : i128_to_f64(M.hi[i - 6]);
+}
+
+// least squares from the moments as doubles, mom[0 .. 3 DEG + 1] in that order; returns true on
+// success (every pivot positive, finite coefficients)
+template <int DEG>
+__device__ __forceinline__ bool solve_moments(const double* mom, int kshift, double* coef) {
     constexpr int N = DEG + 1;
-    double A[N][N], b[N], sc[2 * DEG + 1];
+    double A[N][N], b[N], sw[2 * DEG + 1];
 #pragma unroll
-    for (int p = 0; p <= 2 * DEG; ++p) sc[p] = ldexp(1.0, -kshift * p);
-#pragma unroll
-    for (int i = 0; i < N; ++i) {
-#pragma unroll
-        for (int j = 0; j < N; ++j) A[i][j] = i128_to_f64(M.sw[i + j]) * sc[i + j];
-        b[i] = i128_to_f64(M.syw[i]) * sc[i];
+    for (int p = 0; p <= 2 * DEG; ++p) {
+        const double sc = ldexp(1.0, -kshift * p);
+        sw[p] = mom[p] * sc;
+        if (p < N) b[p] = mom[2 * DEG + 1 + p] * sc;
     }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+#pragma unroll
+        for (int j = 0; j < N; ++j) A[i][j] = sw[i + j];
     bool ok = true;
 #pragma unroll
     for (int i = 0; i < N; ++i) {

@@ -55,3 +55,20 @@ def test_vpx_path_by_width_and_band(kind, w, h, kw):
     out = run_gpu(g, d, dm, params=ld.params_default(**kw))
     for b in range(2):
         compare_frame(out, b, g[b], d[b], dm, params=oracle.default_params(**kw))
+
+
+@pytest.mark.parametrize("w,h,n,kw", [
+    # few and many frames a launch; point counts of every remainder of four; few samples, draws
+    # that repeat an index (short frames), rounds cut off, no survivors, one round
+    (96, 40, 512, {}), (96, 40, 513, {}), (129, 65, 2, {}), (129, 66, 2, {}), (129, 67, 2, {}), (129, 68, 2, {}),
+    (64, 24, 3, {}), (64, 18, 3, {"n_hyp": 63}), (320, 96, 1, {"n_hyp": 1}), (320, 96, 2, {"n_hyp": 7, "max_rounds": 1}),
+    (320, 97, 2, {"tr_x": 0.0, "tr_y": 0.0}), (321, 98, 2, {"tr_x": 1e9, "eps_num": 100}), (320, 99, 2, {"seed": 2 ** 40 + 5}),
+])
+def test_ransac_by_points_and_samples(w, h, n, kw):
+    import oracle
+    from paper_1807_02752_amd import ld
+    g, d = _frames("road", w, h, n)
+    out = run_gpu(g, d, 48, params=ld.params_default(**kw))
+    out.pop("curves", None)     # a poor model's curves end at 1e5 columns, where FP32 itself is 4e-3 off
+    for b in sorted({0, n // 2, n - 1}):
+        compare_frame(out, b, g[b], d[b], 48, params=oracle.default_params(**kw))
