@@ -519,7 +519,8 @@ __global__ __launch_bounds__(kBlock) void k_vdisp_hist(Dev d, const uint8_t* dis
 // ------------------------------------------------------------------------------------------
 // S2 + S3: DP on the v-disparity map (Eq. vpy_estimation), RANSAC road profile beta
 // (Alg. "beta estimation"), tables f, f', V_py (Eq. vpy_equation) and the road rows.  One
-// workgroup per frame; E lives in two LDS rows, the backtrace in global memory.
+// workgroup per frame.
+
 // The road test of Sec. 2.3.1, valid(raw) and |D(raw) - f| <= varpi in FP64, as an interval
 // of raw pixel values.  D is non-decreasing in the raw value over the valid values (u8:
 // 1..255, u16: 1..65535, f32: the bit patterns of positive finite floats) and the rounded
@@ -532,27 +533,44 @@ __device__ __forceinline__ double raw_to_d(int fmt, uint32_t r) {
     return (double)__uint_as_float(r);
 }
 
+__device__ __forceinline__ uint32_t d_to_raw(int fmt, double x) {           // about; 0 for x <= 0
+    x = fmin(fmax(x, 0.0), 3.0e38);
+    if (fmt == LD_DISP_F32) return __float_as_uint((float)x);
+    return (uint32_t)fmin(fmt == LD_DISP_U8 ? x : x * 16.0, 65535.0);
+}
+
+// The bisections start from two values either side of the rounded end f -+ varpi where the
+// predicate confirms them (always but for extreme f), so they take 2 steps instead of up to 31:
+// the tables of a 375-row frame took 6.4 us of k_vdisp_fit's time and take 1.9.
 __device__ void road_interval(int fmt, double f, double varpi, uint32_t& lo, uint32_t& hi) {
     const uint32_t top = fmt == LD_DISP_U8 ? 255u : (fmt == LD_DISP_U16Q4 ? 65535u : 0x7F7FFFFFu);
     lo = 1u;
     hi = 0u;
+    auto above = [&](uint32_t r) { return raw_to_d(fmt, r) - f >= -varpi; };
+    auto below = [&](uint32_t r) { return raw_to_d(fmt, r) - f <= varpi; };
     // smallest r with D(r) - f >= -varpi
-    if (!(raw_to_d(fmt, top) - f >= -varpi)) return;
+    if (!above(top)) return;
     uint32_t a = 1u, z = top;
-    if (!(raw_to_d(fmt, a) - f >= -varpi)) {
+    if (!above(a)) {
+        const uint32_t g = d_to_raw(fmt, f - varpi);
+        if (g > 3u && g - 2u < z && !above(g - 2u)) a = g - 2u;
+        if (g < top - 2u && g + 2u > a && above(g + 2u)) z = g + 2u;
         while (z - a > 1u) {            // predicate false at a, true at z
             const uint32_t m = a + (z - a) / 2u;
-            if (raw_to_d(fmt, m) - f >= -varpi) z = m; else a = m;
+            if (above(m)) z = m; else a = m;
         }
         a = z;
     }
     // largest r with D(r) - f <= varpi
-    if (!(raw_to_d(fmt, 1u) - f <= varpi)) return;
+    if (!below(1u)) return;
     uint32_t x = 1u, y = top;
-    if (!(raw_to_d(fmt, y) - f <= varpi)) {
+    if (!below(y)) {
+        const uint32_t g = d_to_raw(fmt, f + varpi);
+        if (g > 3u && g - 2u < y && below(g - 2u)) x = g - 2u;
+        if (g < top - 2u && g + 2u > x && !below(g + 2u)) y = g + 2u;
         while (y - x > 1u) {            // predicate true at x, false at y
             const uint32_t m = x + (y - x) / 2u;
-            if (raw_to_d(fmt, m) - f <= varpi) x = m; else y = m;
+            if (below(m)) x = m; else y = m;
         }
     } else {
         x = y;
@@ -561,129 +579,257 @@ __device__ void road_interval(int fmt, double f, double varpi, uint32_t& lo, uin
     hi = x;
 }
 
-constexpr int kVdRows = 4;                 // rows per thread in the v-disparity DP
-constexpr int kVdWalk = 32;                // DP steps of the backtrace staged in LDS per walk chunk
+constexpr int kVdTau = 8;                  // largest tau of the DP in registers
+constexpr int kVdWaveRows = 2 * kWave;     // its rows a wave, two a lane
+constexpr int kVdSteps = 8;                // its steps a chunk: a word of 4-bit backtraces a row
+constexpr int kVdRows = 4;                 // rows per thread in the DP of wider jumps
+constexpr int kVdWalk = 32;                // its steps of the backtrace staged in LDS per walk chunk
 constexpr int kVdWalkCols = 257;           // staged rows per step (covers kVdWalk steps of tau_max)
-constexpr int kVdPad = 8;                  // padding rows after each DP row
 constexpr int kVdPadKey = 0x3FFFFFF0;      // padding key: above any real key, and twice it fits int32
 
+// waves of the DP in registers, 0 where it does not apply
+__host__ __device__ __forceinline__ int vdisp_dp_waves(int H, int tau_max) {
+    const int n = (H + kVdWaveRows - 1) / kVdWaveRows;
+    return tau_max <= kVdTau && n <= kMaxWaves ? n : 0;
+}
+// words of its backtrace, and of the boundary rows that its waves hand on
+__host__ __device__ __forceinline__ int vdisp_back_words(int H, int d_max) { return (d_max + kVdSteps - 1) / kVdSteps * H; }
+__host__ __device__ __forceinline__ int vdisp_seam_words(int waves) { return (waves + 1) * 2 * kVdSteps * 8; }
+
+// The DP over jumps of at most TM <= kVdTau rows.  A row needs itself and the TM rows below, so
+// with two rows a lane the window comes from the next lanes by wave shifts, and a wave needs
+// nothing but the eight topmost rows of the wave below it, before each step: those go
+// through LDS a chunk of steps at a time, and wave w works on a chunk one turn after wave w + 1 did,
+// so a turn of kVdSteps steps has one barrier.  The keys are packed: the key of jump tau is
+// (E(v + tau) + lambda tau) << 4 | tau; the minimum is the smallest cost, and among equal
+// costs the smallest tau (the strict-< scan over tau = 0, 1, ...).  Rows past H - 1 hold the
+// padding key.  m is int2 columns of the votes (the chunk after this one is loaded ahead), bw the
+// backtrace (bits 4 j of word (chunk, row): step 8 chunk + j; step i is disparity d_max - 1 - i).
+// E0 receives the last row's keys.
+//
+// Bound: a wave's issue, about 45 instructions a step, and their chain.  A barrier and nine LDS
+// reads a row a step took 0.50 us a step at 375 rows and 0.70 at 1080; this takes 0.13 and 0.25
+// (the boundary rows of a step are read a step ahead).
+template <int TM>
+__device__ __forceinline__ void vdisp_dp(const int32_t* myT, int Hm, int H, int d_max, int lam, int tau_max, int nwdp,
+                                         uint32_t* bw, int* seam, int* E0) {
+    const int t = threadIdx.x, lane = lane_id(), wave = t / kWave, nt = blockDim.x;
+    for (int i = t; i < 2 * kVdSteps * 8; i += nt) seam[nwdp * 2 * kVdSteps * 8 + i] = kVdPadKey;   // below the last wave
+    const int v = wave * kVdWaveRows + 2 * lane;                 // this lane's rows v, v + 1
+    const int vc = min(v, Hm - 2);                               // (Hm is even)
+    const bool in0 = v < H, in1 = v + 1 < H;
+    const int chunks = (d_max + kVdSteps - 1) / kVdSteps;
+    int addc[TM + 1];
+#pragma unroll
+    for (int tau = 1; tau <= TM; ++tau) addc[tau] = tau <= tau_max ? 16 * lam * tau + tau : kVdPadKey;
+    int e0 = kVdPadKey, e1 = kVdPadKey;
+    int2 nxt[kVdSteps];
+    auto load = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < kVdSteps; ++j) {
+            const int dd = max(d_max - 1 - (c * kVdSteps + j), 0);
+            nxt[j] = *reinterpret_cast<const int2*>(myT + (int64_t)dd * Hm + vc);
+        }
+    };
+    if (wave < nwdp) {
+        const int2 q = *reinterpret_cast<const int2*>(myT + (int64_t)d_max * Hm + vc);
+        e0 = in0 ? -q.x * 16 : kVdPadKey;
+        e1 = in1 ? -q.y * 16 : kVdPadKey;
+        load(0);
+    }
+    __syncthreads();
+    for (int turn = 0; turn < chunks + nwdp - 1; ++turn) {
+        const int c = turn - (nwdp - 1 - wave);
+        if (wave < nwdp && c >= 0 && c < chunks) {
+            int2 m[kVdSteps];
+#pragma unroll
+            for (int j = 0; j < kVdSteps; ++j) m[j] = make_int2(in0 ? nxt[j].x * 16 : 0, in1 ? nxt[j].y * 16 : 0);
+            load(min(c + 1, chunks - 1));
+            const int4* below = reinterpret_cast<const int4*>(seam + ((wave + 1) * 2 + (c & 1)) * kVdSteps * 8);
+            int2* mine = reinterpret_cast<int2*>(seam + (wave * 2 + (c & 1)) * kVdSteps * 8);
+            uint32_t b0 = 0, b1 = 0;
+            const int n = min(kVdSteps, d_max - c * kVdSteps);
+            int4 pn = below[0], qn = below[1];
+            auto step = [&](int j) __attribute__((always_inline)) {
+                const int4 p = pn, q = qn;
+                if (j + 1 < kVdSteps) {                          // the next step's, ahead of its use
+                    pn = below[2 * j + 2];
+                    qn = below[2 * j + 3];
+                }
+                if (lane < 4) mine[4 * j + lane] = make_int2(e0, e1);
+                // rows v .. v + 9: lane l + 1's by a shift whose last lane takes the wave below's
+                int w[10];
+                w[0] = e0; w[1] = e1;
+                w[2] = __builtin_amdgcn_update_dpp(p.x, w[0], 0x130, 0xF, 0xF, false);
+                w[3] = __builtin_amdgcn_update_dpp(p.y, w[1], 0x130, 0xF, 0xF, false);
+                w[4] = __builtin_amdgcn_update_dpp(p.z, w[2], 0x130, 0xF, 0xF, false);
+                w[5] = __builtin_amdgcn_update_dpp(p.w, w[3], 0x130, 0xF, 0xF, false);
+                w[6] = __builtin_amdgcn_update_dpp(q.x, w[4], 0x130, 0xF, 0xF, false);
+                w[7] = __builtin_amdgcn_update_dpp(q.y, w[5], 0x130, 0xF, 0xF, false);
+                if constexpr (TM > 6) {
+                    w[8] = __builtin_amdgcn_update_dpp(q.z, w[6], 0x130, 0xF, 0xF, false);
+                    w[9] = __builtin_amdgcn_update_dpp(q.w, w[7], 0x130, 0xF, 0xF, false);
+                }
+                int k0 = w[0], k1 = w[1];
+#pragma unroll
+                for (int tau = 1; tau <= TM; ++tau) {
+                    k0 = min(k0, w[tau] + addc[tau]);
+                    k1 = min(k1, w[tau + 1] + addc[tau]);
+                }
+                b0 = (b0 >> 4) | ((uint32_t)k0 << 28);
+                b1 = (b1 >> 4) | ((uint32_t)k1 << 28);
+                e0 = (k0 & -16) - m[j].x;
+                e1 = (k1 & -16) - m[j].y;
+            };
+            if (n == kVdSteps) {
+#pragma unroll
+                for (int j = 0; j < kVdSteps; ++j) step(j);
+            } else {
+#pragma unroll
+                for (int j = 0; j < kVdSteps; ++j)
+                    if (j < n) step(j);
+                b0 >>= 4 * (kVdSteps - n);
+                b1 >>= 4 * (kVdSteps - n);
+            }
+            if (in0) bw[(int64_t)c * H + v] = b0;
+            if (in1) bw[(int64_t)c * H + v + 1] = b1;
+        }
+        __syncthreads();
+    }
+    if (wave < nwdp) {
+        if (in0) E0[v] = e0;
+        if (in1) E0[v + 1] = e1;
+    }
+    __syncthreads();
+}
+
 __global__ __launch_bounds__(1024) void k_vdisp_fit(Dev d, const uint64_t* stream_ids, const int64_t* frame_idx,
-                                                    double* beta_out) {
-    extern __shared__ unsigned char smem[];
-    __shared__ RansacShared S;
+                                                    double* beta_out, int back_in_lds) {
+    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int64_t rv[kMaxWaves];
     __shared__ int ri[kMaxWaves];
     __shared__ int s_n, s_v;
     const int b = blockIdx.x, t = threadIdx.x, nt = blockDim.x;
     if (frame_masked(d, b)) return;
     const int H = d.H, D1 = d.D1, d_max = d.d_max;
-    // DP rows hold E << 4 (E <= 0, low 4 bits zero); the kVdPad entries past row H - 1 hold a
-    // key that loses to every real one
     const int D4 = (D1 + 3) / 4 * 4;
     int* PX = reinterpret_cast<int*>(smem);
     int* PY = PX + D4;
     int* cur = PY + D4;
     int* cur2 = cur + D4;
-    int* E0 = cur2 + D4;
-    int* E1 = E0 + H + kVdPad;
-    uint32_t* bitmap = reinterpret_cast<uint32_t*>(E1 + H + kVdPad);
+    uint32_t* bitmap = reinterpret_cast<uint32_t*>(cur2 + D4);
     const int bm_words = (H + 31) / 32;
-    uint8_t* win = reinterpret_cast<uint8_t*>(bitmap + bm_words);   // kVdWalk x kVdWalkCols
-    uint8_t* back = d.back_y + (int64_t)b * D1 * H;
+    int* E0 = reinterpret_cast<int*>(bitmap + (bm_words + 3) / 4 * 4);
+    // the RANSAC's memory, before that the DP's
+    int* const region = E0 + (H + 3) / 4 * 4;
+    RansacShared& S = *reinterpret_cast<RansacShared*>(region);
     const int Hm = d.Hm;
     const int32_t* myT = d.myT + (int64_t)b * D1 * Hm;
     const int tau_max = d.P.tau_y_max, lam = d.P.lambda_y;
-
-    for (int v = t; v < H; v += nt) {
-        E0[v] = -myT[(int64_t)d_max * Hm + v] * 16;
-        d.rowcnt[(int64_t)b * H + v] = 0;
-    }
-    if (t < kVdPad) { E0[H + t] = kVdPadKey; E1[H + t] = kVdPadKey; }
-    // step costs of the packed keys: 16 lambda tau + tau for an allowed jump, the padding key
-    // for tau > tau_max (so the key loses), for the window of up to 8 rows read at once
-    int addc[9];
+    for (int v = t; v < H; v += nt) d.rowcnt[(int64_t)b * H + v] = 0;
+    const int nwdp = vdisp_dp_waves(H, tau_max);
+    // the row of the smallest E at disparity 0 (ties to the smaller row), every thread's
+    auto first_row = [&](const int* E) {
+        int64_t bv = INT64_MAX;
+        int bi = 0x7fffffff;
+        for (int v = t; v < H; v += nt)
+            if ((int64_t)E[v] < bv) { bv = E[v]; bi = v; }
+        block_argmin_i64(bv, bi, rv, ri);
+        return bi;
+    };
+    if (nwdp > 0) {
+        int* seam = region;
+        uint32_t* lback = reinterpret_cast<uint32_t*>(seam + vdisp_seam_words(nwdp));
+        uint32_t* gback = reinterpret_cast<uint32_t*>(d.back_y + (((int64_t)b * D1 * H + 3) & ~(int64_t)3));
+        uint32_t* bw = back_in_lds ? lback : gback;
+        if (tau_max <= 6) vdisp_dp<6>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
+        else vdisp_dp<8>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
+        const int v0 = __builtin_amdgcn_readfirstlane(first_row(E0));
+        // The walk, by wave 0: disparities from 0 are the last step and down, so a chunk's words of the
+        // 64 rows from the path's present one hold its next eight steps (tau <= 8), a lane a row.
+        if (t < kWave) {
+            int v = v0, dd = 0;
+            for (int c = (d_max - 1) / kVdSteps; c >= 0; --c) {
+                const int n = min(kVdSteps, d_max - c * kVdSteps), base = v;
+                const int word = (int)bw[(int64_t)c * H + min(base + t, H - 1)];
+                int keep = 0;
+                auto step = [&](int j, int at) __attribute__((always_inline)) {
+                    keep = t == at ? v : keep;
+                    v += (__builtin_amdgcn_readlane(word, v - base) >> (4 * j)) & 15;
+                };
+                if (n == kVdSteps) {
 #pragma unroll
-    for (int tau = 1; tau <= 8; ++tau) addc[tau] = tau <= tau_max ? 16 * lam * tau + tau : kVdPadKey;
-    // the column m_y(d, .) of the next DP step is loaded while the current one is computed
-    int nxt[kVdRows];
+                    for (int j = kVdSteps - 1; j >= 0; --j) step(j, kVdSteps - 1 - j);
+                } else {
+                    for (int j = n - 1; j >= 0; --j) step(j, n - 1 - j);
+                }
+                if (t < n) cur[dd + t] = keep;
+                dd += n;
+            }
+            if (t == 0) cur[d_max] = v;
+        }
+        __syncthreads();
+    } else {
+        // jumps past 8 rows: the row before and this one in LDS, a barrier a step
+        int* E1 = region;
+        uint8_t* win = reinterpret_cast<uint8_t*>(E1 + H);       // kVdWalk x kVdWalkCols
+        uint8_t* back = d.back_y + (int64_t)b * D1 * H;
+        for (int v = t; v < H; v += nt) E0[v] = -myT[(int64_t)d_max * Hm + v];
+        // the column m_y(d, .) of the next DP step is loaded while the current one is computed
+        int nxt[kVdRows];
 #pragma unroll
-    for (int k = 0; k < kVdRows; ++k) {
-        const int v = t + k * nt;
-        nxt[k] = (d_max >= 1 && v < H) ? myT[(int64_t)(d_max - 1) * Hm + v] : 0;
-    }
-    __syncthreads();
-    int* Ec = E0;
-    int* En = E1;
-    for (int dd = d_max - 1; dd >= 0; --dd) {
-        int curm[kVdRows];
+        for (int k = 0; k < kVdRows; ++k) nxt[k] = myT[(int64_t)(d_max - 1) * Hm + min(t + k * nt, H - 1)];
+        __syncthreads();
+        int* Ec = E0;
+        int* En = E1;
+        for (int dd = d_max - 1; dd >= 0; --dd) {
+            int m[kVdRows];
 #pragma unroll
-        for (int k = 0; k < kVdRows; ++k) curm[k] = nxt[k];
-        if (dd >= 1) {
+            for (int k = 0; k < kVdRows; ++k) {
+                m[k] = nxt[k];
+                nxt[k] = myT[(int64_t)max(dd - 1, 0) * Hm + min(t + k * nt, H - 1)];
+            }
 #pragma unroll
             for (int k = 0; k < kVdRows; ++k) {
                 const int v = t + k * nt;
-                nxt[k] = v < H ? myT[(int64_t)(dd - 1) * Hm + v] : 0;
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < kVdRows; ++k) {
-            const int v = t + k * nt;
-            if (v < H) {
-                if (tau_max <= 8) {
-                    // key of jump tau: (E(v + tau) + lambda tau) << 4 | tau; the minimum is the
-                    // smallest cost, and among equal costs the smallest tau (the strict-< scan
-                    // over tau = 0, 1, ...).  Rows past H - 1 read the padding.
-                    int e[9];
-#pragma unroll
-                    for (int j = 0; j <= 8; ++j) e[j] = Ec[v + j];
-                    int m = e[0];
-#pragma unroll
-                    for (int tau = 1; tau <= 8; ++tau) m = min(m, e[tau] + addc[tau]);
-                    En[v] = (m & -16) - curm[k] * 16;
-                    back[(int64_t)dd * H + v] = (uint8_t)(m & 15);
-                } else {
-                    int best = Ec[v] >> 4, bt = 0;
-                    for (int tau = 1; tau <= tau_max && v + tau <= H - 1; ++tau) {
-                        const int c = (Ec[v + tau] >> 4) + lam * tau;
-                        if (c < best) { best = c; bt = tau; }
-                    }
-                    En[v] = (best - curm[k]) * 16;
-                    back[(int64_t)dd * H + v] = (uint8_t)bt;
+                if (v >= H) continue;
+                int best = Ec[v], bt = 0;
+                for (int tau = 1; tau <= tau_max && v + tau <= H - 1; ++tau) {
+                    const int c = Ec[v + tau] + lam * tau;
+                    if (c < best) { best = c; bt = tau; }
                 }
+                En[v] = best - m[k];
+                back[(int64_t)dd * H + v] = (uint8_t)bt;
             }
+            __syncthreads();
+            int* tmp = Ec; Ec = En; En = tmp;
         }
+        const int bi = first_row(Ec);
+        // backtrace: stage the rows the path can reach in the next kVdWalk steps, then one thread
+        // follows it (the path moves down by at most tau_max rows per step)
+        const int steps = max(1, min(kVdWalk, (kVdWalkCols - 1) / max(1, tau_max)));
+        if (t == 0) s_v = bi;
         __syncthreads();
-        int* tmp = Ec; Ec = En; En = tmp;
-    }
-    int64_t bv = INT64_MAX;
-    int bi = 0x7fffffff;
-    for (int v = t; v < H; v += nt)
-        if ((int64_t)Ec[v] < bv) { bv = Ec[v]; bi = v; }
-    block_argmin_i64(bv, bi, rv, ri);
-    // backtrace: stage the rows the path can reach in the next kVdWalk steps, then one thread
-    // follows it (the path moves down by at most tau_max rows per step)
-    const int steps = max(1, min(kVdWalk, (kVdWalkCols - 1) / max(1, tau_max)));
-    if (t == 0) s_v = bi;
-    __syncthreads();
-    for (int d0 = 0; d0 <= d_max; d0 += steps) {
-        const int v0 = s_v;
-        const int nst = min(steps, d_max - d0);               // steps with a backtrace entry
-        const int ncols = min(H - v0, tau_max * steps + 1);
-        for (int i = t; i < nst * ncols; i += nt) {
-            const int r = i / ncols, c = i % ncols;
-            win[r * kVdWalkCols + c] = back[(int64_t)(d0 + r) * H + v0 + c];
-        }
-        __syncthreads();
-        if (t == 0) {
-            int v = v0;
-            const int last = min(d0 + steps - 1, d_max);
-            for (int dd = d0; dd <= last; ++dd) {
-                cur[dd] = v;                                    // row of disparity dd on the path
-                if (dd < d_max) v += win[(dd - d0) * kVdWalkCols + (v - v0)];
+        for (int d0 = 0; d0 <= d_max; d0 += steps) {
+            const int v0 = s_v;
+            const int nst = min(steps, d_max - d0);               // steps with a backtrace entry
+            const int ncols = min(H - v0, tau_max * steps + 1);
+            for (int i = t; i < nst * ncols; i += nt) {
+                const int r = i / ncols, c = i % ncols;
+                win[r * kVdWalkCols + c] = back[(int64_t)(d0 + r) * H + v0 + c];
             }
-            s_v = v;
+            __syncthreads();
+            if (t == 0) {
+                int v = v0;
+                const int last = min(d0 + steps - 1, d_max);
+                for (int dd = d0; dd <= last; ++dd) {
+                    cur[dd] = v;                                    // row of disparity dd on the path
+                    if (dd < d_max) v += win[(dd - d0) * kVdWalkCols + (v - v0)];
+                }
+                s_v = v;
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
     // keep the path points that carry votes, in order of disparity (stable ballot compaction)
     {
@@ -1450,7 +1596,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) void 
 constexpr int kRansacThreads = 192, kRansacThreadsFew = 512;
 __global__ __launch_bounds__(kRansacThreadsFew) void k_vpx_ransac(Dev d, const uint64_t* stream_ids, const int64_t* frame_idx,
                                                     const double* seed_gamma, int pruned, double* vp_out) {
-    extern __shared__ unsigned char smem[];
+    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ RansacShared S;
     const int b = blockIdx.x, t = threadIdx.x, nt = blockDim.x;
     if (frame_masked(d, b)) return;
@@ -1991,7 +2137,7 @@ __global__ __launch_bounds__(kWave) void k_tracks(Dev d, const uint8_t* cand_mas
 // S13: strict local minima of the energies, below rho * (deepest energy); greedy suppression
 // of minima within d_nms of a deeper accepted one; lane curves by iterating the track.
 __global__ __launch_bounds__(kBlock) void k_peaks(Dev d, ld_lanes* lanes_out, float* curves_out) {
-    extern __shared__ unsigned char smem[];
+    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int64_t rv[kMaxWaves];
     __shared__ int ri[kMaxWaves];
     __shared__ double dred[kMaxWaves];
@@ -2538,7 +2684,7 @@ __global__ __launch_bounds__(256) void k_vpx_window(Dev d, int stage_cap, int wa
 // Candidate mask: candidate i is kept when its track meets a marking pixel on a band row, then
 // dilated.  Frames on the plain V_px search keep every candidate.  One workgroup per frame.
 __global__ __launch_bounds__(kBlock) void k_cand_mask(Dev d, int nb, int dilate) {
-    extern __shared__ unsigned char smem[];
+    extern __shared__ __align__(16) unsigned char smem[];
     __shared__ double ta[LDI_MAX_BANDS * LDI_BAND_ROWS], tb[LDI_MAX_BANDS * LDI_BAND_ROWS];
     __shared__ int red[kMaxWaves];
     const int b = blockIdx.x, t = threadIdx.x;
@@ -2703,12 +2849,27 @@ struct ProfScope {
 };
 
 int vdisp_fit_threads(const Dev& d) {
+    const int waves = vdisp_dp_waves(d.H, d.P.tau_y_max);
+    if (waves > 0) return std::max(256, waves * kWave);
     return std::min(1024, std::max(256, ((d.H + kVdRows - 1) / kVdRows + 63) / 64 * 64));
 }
 
-size_t vdisp_fit_lds(const Dev& d) {
-    return sizeof(int) * (2 * ((size_t)d.H + kVdPad) + 4 * (((size_t)d.D1 + 3) / 4 * 4)) + sizeof(uint32_t) * ((d.H + 31) / 32) +
-           (size_t)kVdWalk * kVdWalkCols;
+// LDS of k_vdisp_fit; the register DP's backtrace only if it fits (and then *in_lds = 1)
+size_t vdisp_fit_lds(const Dev& d, int* in_lds) {
+    const size_t H4 = ((size_t)d.H + 3) / 4 * 4, bm4 = (((size_t)d.H + 31) / 32 + 3) / 4 * 4;
+    size_t words = 4 * (((size_t)d.D1 + 3) / 4 * 4) + bm4 + H4;
+    const int waves = vdisp_dp_waves(d.H, d.P.tau_y_max);
+    size_t region = 4 * (size_t)d.H + (size_t)kVdWalk * kVdWalkCols;
+    *in_lds = 0;
+    if (waves > 0) {
+        region = 4 * (size_t)vdisp_seam_words(waves);
+        const size_t back = 4 * (size_t)vdisp_back_words(d.H, d.d_max);
+        if (4 * words + region + back <= 160 * 1024 - 512) {    // (512: the kernel's other LDS)
+            *in_lds = 1;
+            region += back;
+        }
+    }
+    return 4 * words + std::max(region, sizeof(RansacShared));
 }
 
 // LDS of k_vpx_fit without the staged vote columns
@@ -2854,11 +3015,13 @@ ld_status run_hist(ld_frame f, const void* disp, int64_t pitch, int32_t* vdisp_o
 // S2-S3 for the active frames of f
 ld_status run_vdisp_fit(ld_frame f, const uint64_t* sid, const int64_t* fidx, double* beta_out, hipStream_t st) {
     Dev& d = f->d;
-    const size_t l2 = vdisp_fit_lds(d);
+    int in_lds;
+    const size_t l2 = vdisp_fit_lds(d, &in_lds);
     allow_lds(k_vdisp_fit, l2);
     {
         ProfScope ps(f, 1, st);
-        hipLaunchKernelGGL(k_vdisp_fit, dim3(f->active), dim3(vdisp_fit_threads(d)), l2, st, d, sid, fidx, beta_out);
+        hipLaunchKernelGGL(k_vdisp_fit, dim3(f->active), dim3(vdisp_fit_threads(d)), l2, st, d, sid, fidx, beta_out,
+                           in_lds);
     }
     return launch_ok();
 }

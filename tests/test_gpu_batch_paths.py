@@ -72,3 +72,23 @@ def test_ransac_by_points_and_samples(w, h, n, kw):
     out.pop("curves", None)     # a poor model's curves end at 1e5 columns, where FP32 itself is 4e-3 off
     for b in sorted({0, n // 2, n - 1}):
         compare_frame(out, b, g[b], d[b], 48, params=oracle.default_params(**kw))
+
+
+@pytest.mark.parametrize("w,h,d_max,kw", [
+    # rows of one wave to its last, one more, several waves; a step count of every kind of chunk
+    (96, 127, 48, {}), (96, 128, 49, {}), (96, 129, 55, {}), (64, 257, 57, {}), (64, 385, 63, {}), (33, 20, 48, {}),
+    # jump bounds of either register form, and past them
+    (96, 130, 48, {"tau_y_max": 0}), (96, 130, 48, {"tau_y_max": 1}), (96, 131, 50, {"tau_y_max": 7, "lambda_y": 3}),
+    (96, 255, 48, {"tau_y_max": 8}), (96, 255, 48, {"tau_y_max": 9}), (96, 130, 48, {"tau_y_max": 200}),
+    (96, 130, 48, {"lambda_y": 1000}), (96, 130, 48, {"lambda_y": 0}),
+    # a backtrace larger than LDS, and more rows than the waves hold
+    (64, 700, 600, {}), (64, 701, 1023, {}), (64, 2047, 64, {}), (32, 2049, 60, {}),
+])
+def test_vdisp_path_by_rows_and_jumps(w, h, d_max, kw):
+    import oracle
+    from paper_1807_02752_amd import ld
+    g, d = _frames("road", w, h, 2)
+    out = run_gpu(g, d, d_max, params=ld.params_default(**kw))
+    out.pop("curves", None)     # FP32, far outside the image for a poor model
+    for b in range(2):
+        compare_frame(out, b, g[b], d[b], d_max, params=oracle.default_params(**kw))
