@@ -580,16 +580,16 @@ __device__ void road_interval(int fmt, double f, double varpi, uint32_t& lo, uin
 }
 
 constexpr int kVdTau = 8;                  // largest tau of the DP in registers
-constexpr int kVdWaveRows = 2 * kWave;     // its rows a wave, two a lane
 constexpr int kVdSteps = 8;                // its steps a chunk: a word of 4-bit backtraces a row
 constexpr int kVdRows = 4;                 // rows per thread in the DP of wider jumps
 constexpr int kVdWalk = 32;                // its steps of the backtrace staged in LDS per walk chunk
 constexpr int kVdWalkCols = 257;           // staged rows per step (covers kVdWalk steps of tau_max)
 constexpr int kVdPadKey = 0x3FFFFFF0;      // padding key: above any real key, and twice it fits int32
 
-// waves of the DP in registers, 0 where it does not apply
+// rows a lane of the DP in registers, and its waves (0 where it does not apply)
+__host__ __device__ __forceinline__ int vdisp_lane_rows(int H) { return H <= 2 * kWave * kMaxWaves ? 2 : 4; }
 __host__ __device__ __forceinline__ int vdisp_dp_waves(int H, int tau_max) {
-    const int n = (H + kVdWaveRows - 1) / kVdWaveRows;
+    const int n = (H + kWave * vdisp_lane_rows(H) - 1) / (kWave * vdisp_lane_rows(H));
     return tau_max <= kVdTau && n <= kMaxWaves ? n : 0;
 }
 // words of its backtrace, and of the boundary rows that its waves hand on
@@ -597,89 +597,85 @@ __host__ __device__ __forceinline__ int vdisp_back_words(int H, int d_max) { ret
 __host__ __device__ __forceinline__ int vdisp_seam_words(int waves) { return (waves + 1) * 2 * kVdSteps * 8; }
 
 // The DP over jumps of at most TM <= kVdTau rows.  A row needs itself and the TM rows below, so
-// with two rows a lane the window comes from the next lanes by wave shifts, and a wave needs
+// with R rows a lane (two, or four past 2048 rows) the window comes from the next lanes by wave
+// shifts, and a wave needs
 // nothing but the eight topmost rows of the wave below it, before each step: those go
 // through LDS a chunk of steps at a time, and wave w works on a chunk one turn after wave w + 1 did,
 // so a turn of kVdSteps steps has one barrier.  The keys are packed: the key of jump tau is
 // (E(v + tau) + lambda tau) << 4 | tau; the minimum is the smallest cost, and among equal
 // costs the smallest tau (the strict-< scan over tau = 0, 1, ...).  Rows past H - 1 hold the
-// padding key.  m is int2 columns of the votes (the chunk after this one is loaded ahead), bw the
+// padding key.  The votes of the chunk after this one are loaded ahead; bw is the
 // backtrace (bits 4 j of word (chunk, row): step 8 chunk + j; step i is disparity d_max - 1 - i).
 // E0 receives the last row's keys.
 //
 // Bound: a wave's issue, about 45 instructions a step, and their chain.  A barrier and nine LDS
 // reads a row a step took 0.50 us a step at 375 rows and 0.70 at 1080; this takes 0.13 and 0.25
 // (the boundary rows of a step are read a step ahead).
-template <int TM>
+template <int TM, int R>
 __device__ __forceinline__ void vdisp_dp(const int32_t* myT, int Hm, int H, int d_max, int lam, int tau_max, int nwdp,
                                          uint32_t* bw, int* seam, int* E0) {
     const int t = threadIdx.x, lane = lane_id(), wave = t / kWave, nt = blockDim.x;
     for (int i = t; i < 2 * kVdSteps * 8; i += nt) seam[nwdp * 2 * kVdSteps * 8 + i] = kVdPadKey;   // below the last wave
-    const int v = wave * kVdWaveRows + 2 * lane;                 // this lane's rows v, v + 1
-    const int vc = min(v, Hm - 2);                               // (Hm is even)
-    const bool in0 = v < H, in1 = v + 1 < H;
+    const int v = (wave * kWave + lane) * R;                     // this lane's rows v .. v + R - 1
+    const int vc = min(v, Hm - R);                               // (Hm is a multiple of 32)
     const int chunks = (d_max + kVdSteps - 1) / kVdSteps;
     int addc[TM + 1];
 #pragma unroll
     for (int tau = 1; tau <= TM; ++tau) addc[tau] = tau <= tau_max ? 16 * lam * tau + tau : kVdPadKey;
-    int e0 = kVdPadKey, e1 = kVdPadKey;
-    int2 nxt[kVdSteps];
+    struct alignas(4 * R) Rows { int x[R]; };
+    Rows e, nxt[kVdSteps];
+    auto column = [&](int dd) __attribute__((always_inline)) {
+        return *reinterpret_cast<const Rows*>(myT + (int64_t)dd * Hm + vc);
+    };
     auto load = [&](int c) __attribute__((always_inline)) {
 #pragma unroll
-        for (int j = 0; j < kVdSteps; ++j) {
-            const int dd = max(d_max - 1 - (c * kVdSteps + j), 0);
-            nxt[j] = *reinterpret_cast<const int2*>(myT + (int64_t)dd * Hm + vc);
-        }
+        for (int j = 0; j < kVdSteps; ++j) nxt[j] = column(max(d_max - 1 - (c * kVdSteps + j), 0));
     };
     if (wave < nwdp) {
-        const int2 q = *reinterpret_cast<const int2*>(myT + (int64_t)d_max * Hm + vc);
-        e0 = in0 ? -q.x * 16 : kVdPadKey;
-        e1 = in1 ? -q.y * 16 : kVdPadKey;
+        e = column(d_max);
+#pragma unroll
+        for (int i = 0; i < R; ++i) e.x[i] = v + i < H ? -e.x[i] * 16 : kVdPadKey;
         load(0);
     }
     __syncthreads();
     for (int turn = 0; turn < chunks + nwdp - 1; ++turn) {
         const int c = turn - (nwdp - 1 - wave);
         if (wave < nwdp && c >= 0 && c < chunks) {
-            int2 m[kVdSteps];
+            Rows m[kVdSteps];
 #pragma unroll
-            for (int j = 0; j < kVdSteps; ++j) m[j] = make_int2(in0 ? nxt[j].x * 16 : 0, in1 ? nxt[j].y * 16 : 0);
+            for (int j = 0; j < kVdSteps; ++j)
+#pragma unroll
+                for (int i = 0; i < R; ++i) m[j].x[i] = v + i < H ? nxt[j].x[i] * 16 : 0;
             load(min(c + 1, chunks - 1));
             const int4* below = reinterpret_cast<const int4*>(seam + ((wave + 1) * 2 + (c & 1)) * kVdSteps * 8);
-            int2* mine = reinterpret_cast<int2*>(seam + (wave * 2 + (c & 1)) * kVdSteps * 8);
-            uint32_t b0 = 0, b1 = 0;
+            Rows* mine = reinterpret_cast<Rows*>(seam + (wave * 2 + (c & 1)) * kVdSteps * 8);
+            uint32_t back[R];
+#pragma unroll
+            for (int i = 0; i < R; ++i) back[i] = 0;
             const int n = min(kVdSteps, d_max - c * kVdSteps);
             int4 pn = below[0], qn = below[1];
             auto step = [&](int j) __attribute__((always_inline)) {
-                const int4 p = pn, q = qn;
+                const int old[8] = {pn.x, pn.y, pn.z, pn.w, qn.x, qn.y, qn.z, qn.w};
                 if (j + 1 < kVdSteps) {                          // the next step's, ahead of its use
                     pn = below[2 * j + 2];
                     qn = below[2 * j + 3];
                 }
-                if (lane < 4) mine[4 * j + lane] = make_int2(e0, e1);
-                // rows v .. v + 9: lane l + 1's by a shift whose last lane takes the wave below's
-                int w[10];
-                w[0] = e0; w[1] = e1;
-                w[2] = __builtin_amdgcn_update_dpp(p.x, w[0], 0x130, 0xF, 0xF, false);
-                w[3] = __builtin_amdgcn_update_dpp(p.y, w[1], 0x130, 0xF, 0xF, false);
-                w[4] = __builtin_amdgcn_update_dpp(p.z, w[2], 0x130, 0xF, 0xF, false);
-                w[5] = __builtin_amdgcn_update_dpp(p.w, w[3], 0x130, 0xF, 0xF, false);
-                w[6] = __builtin_amdgcn_update_dpp(q.x, w[4], 0x130, 0xF, 0xF, false);
-                w[7] = __builtin_amdgcn_update_dpp(q.y, w[5], 0x130, 0xF, 0xF, false);
-                if constexpr (TM > 6) {
-                    w[8] = __builtin_amdgcn_update_dpp(q.z, w[6], 0x130, 0xF, 0xF, false);
-                    w[9] = __builtin_amdgcn_update_dpp(q.w, w[7], 0x130, 0xF, 0xF, false);
-                }
-                int k0 = w[0], k1 = w[1];
+                if (lane < 8 / R) mine[8 / R * j + lane] = e;
+                // rows v .. v + R - 1 + TM: those past its own are the next lane's, by a shift whose last
+                // lane takes the wave below's
+                int w[R + TM];
 #pragma unroll
-                for (int tau = 1; tau <= TM; ++tau) {
-                    k0 = min(k0, w[tau] + addc[tau]);
-                    k1 = min(k1, w[tau + 1] + addc[tau]);
+                for (int i = 0; i < R; ++i) w[i] = e.x[i];
+#pragma unroll
+                for (int i = 0; i < TM; ++i) w[R + i] = __builtin_amdgcn_update_dpp(old[i], w[i], 0x130, 0xF, 0xF, false);
+#pragma unroll
+                for (int i = 0; i < R; ++i) {
+                    int k = w[i];
+#pragma unroll
+                    for (int tau = 1; tau <= TM; ++tau) k = min(k, w[i + tau] + addc[tau]);
+                    back[i] = (back[i] >> 4) | ((uint32_t)k << 28);
+                    e.x[i] = (k & -16) - m[j].x[i];
                 }
-                b0 = (b0 >> 4) | ((uint32_t)k0 << 28);
-                b1 = (b1 >> 4) | ((uint32_t)k1 << 28);
-                e0 = (k0 & -16) - m[j].x;
-                e1 = (k1 & -16) - m[j].y;
             };
             if (n == kVdSteps) {
 #pragma unroll
@@ -688,17 +684,19 @@ __device__ __forceinline__ void vdisp_dp(const int32_t* myT, int Hm, int H, int 
 #pragma unroll
                 for (int j = 0; j < kVdSteps; ++j)
                     if (j < n) step(j);
-                b0 >>= 4 * (kVdSteps - n);
-                b1 >>= 4 * (kVdSteps - n);
+#pragma unroll
+                for (int i = 0; i < R; ++i) back[i] >>= 4 * (kVdSteps - n);
             }
-            if (in0) bw[(int64_t)c * H + v] = b0;
-            if (in1) bw[(int64_t)c * H + v + 1] = b1;
+#pragma unroll
+            for (int i = 0; i < R; ++i)
+                if (v + i < H) bw[(int64_t)c * H + v + i] = back[i];
         }
         __syncthreads();
     }
     if (wave < nwdp) {
-        if (in0) E0[v] = e0;
-        if (in1) E0[v + 1] = e1;
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+            if (v + i < H) E0[v + i] = e.x[i];
     }
     __syncthreads();
 }
@@ -742,8 +740,9 @@ __global__ __launch_bounds__(1024) void k_vdisp_fit(Dev d, const uint64_t* strea
         uint32_t* lback = reinterpret_cast<uint32_t*>(seam + vdisp_seam_words(nwdp));
         uint32_t* gback = reinterpret_cast<uint32_t*>(d.back_y + (((int64_t)b * D1 * H + 3) & ~(int64_t)3));
         uint32_t* bw = back_in_lds ? lback : gback;
-        if (tau_max <= 6) vdisp_dp<6>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
-        else vdisp_dp<8>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
+        if (vdisp_lane_rows(H) > 2) vdisp_dp<8, 4>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
+        else if (tau_max <= 6) vdisp_dp<6, 2>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
+        else vdisp_dp<8, 2>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
         const int v0 = __builtin_amdgcn_readfirstlane(first_row(E0));
         // The walk, by wave 0: disparities from 0 are the last step and down, so a chunk's words of the
         // 64 rows from the path's present one hold its next eight steps (tau <= 8), a lane a row.

@@ -81,8 +81,8 @@ def test_ransac_by_points_and_samples(w, h, n, kw):
     (96, 130, 48, {"tau_y_max": 0}), (96, 130, 48, {"tau_y_max": 1}), (96, 131, 50, {"tau_y_max": 7, "lambda_y": 3}),
     (96, 255, 48, {"tau_y_max": 8}), (96, 255, 48, {"tau_y_max": 9}), (96, 130, 48, {"tau_y_max": 200}),
     (96, 130, 48, {"lambda_y": 1000}), (96, 130, 48, {"lambda_y": 0}),
-    # a backtrace larger than LDS, and more rows than the waves hold
-    (64, 700, 600, {}), (64, 701, 1023, {}), (64, 2047, 64, {}), (32, 2049, 60, {}),
+    # a backtrace larger than LDS, and four rows a lane
+    (64, 700, 600, {}), (64, 701, 1023, {}), (64, 2047, 64, {}), (32, 2049, 60, {}), (32, 2305, 57, {"tau_y_max": 8}),
 ])
 def test_vdisp_path_by_rows_and_jumps(w, h, d_max, kw):
     import oracle
