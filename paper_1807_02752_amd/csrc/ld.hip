@@ -2135,6 +2135,9 @@ __global__ __launch_bounds__(kWave) void k_tracks(Dev d, const uint8_t* cand_mas
 // ------------------------------------------------------------------------------------------
 // S13: strict local minima of the energies, below rho * (deepest energy); greedy suppression
 // of minima within d_nms of a deeper accepted one; lane curves by iterating the track.
+constexpr int kCurveRows = 256, kCurveStride = kCurveRows + 1;
+constexpr size_t kCurveLds = kCurveRows * 16 + sizeof(float) * LD_MAX_LANES * kCurveStride;
+
 __global__ __launch_bounds__(kBlock) void k_peaks(Dev d, ld_lanes* lanes_out, float* curves_out) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int64_t rv[kMaxWaves];
@@ -2207,14 +2210,40 @@ __global__ __launch_bounds__(kBlock) void k_peaks(Dev d, ld_lanes* lanes_out, fl
     if (curves_out) {
         float* cv = curves_out + (int64_t)b * LD_MAX_LANES * H;
         const float fnan = __int_as_float(0x7fc00000);
-        for (int i = t; i < LD_MAX_LANES * H; i += kBlock) cv[i] = fnan;
-        __syncthreads();
-        if (t < n) {
-            double u = (double)(acc[t] - d.half);
-            for (int v = v_max; v >= fi.v_end; --v) {
-                if (v < v_max) u = fma(tB[v], u, tA[v]);
-                cv[(int64_t)t * H + v] = (float)u;
+        // A curve is a chain of one fma a row, a lane each.  The rows' coefficients are staged in LDS and the
+        // columns leave through it, kCurveRows rows at a time, so that the chain waits for LDS only
+        // (loads and stores of memory in it took k_peaks 107 us for a 1920 x 1080 frame; now 40).
+        double2* ab = reinterpret_cast<double2*>(smem);
+        float* cu = reinterpret_cast<float*>(ab + kCurveRows);          // [lane][row]
+        double u = t < n ? (double)(acc[t] - d.half) : 0.0;
+        for (int v1 = v_max; v1 >= 0; v1 -= kCurveRows) {               // rows v1 and up to kCurveRows - 1 above
+            const int rows = min(kCurveRows, v1 + 1), swept = min(rows, max(v1 - fi.v_end + 1, 0));
+            for (int i = t; i < swept; i += kBlock)
+                ab[i] = v1 - i < v_max ? make_double2(tA[v1 - i], tB[v1 - i]) : make_double2(0.0, 1.0);
+            __syncthreads();
+            if (t < n) {
+                int i = 0;
+                for (; i + 8 <= swept; i += 8) {
+                    double2 c[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) c[k] = ab[i + k];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        u = fma(c[k].y, u, c[k].x);
+                        cu[t * kCurveStride + i + k] = (float)u;
+                    }
+                }
+                for (; i < swept; ++i) {
+                    u = fma(ab[i].y, u, ab[i].x);
+                    cu[t * kCurveStride + i] = (float)u;
+                }
             }
+            __syncthreads();
+            for (int i = t; i < LD_MAX_LANES * rows; i += kBlock) {
+                const int l = i / rows, r = rows - 1 - (i - l * rows);  // (upwards in memory)
+                cv[(int64_t)l * H + v1 - r] = l < n && r < swept ? cu[l * kCurveStride + r] : fnan;
+            }
+            __syncthreads();
         }
     }
 }
@@ -3153,7 +3182,8 @@ ld_status run_energy(ld_frame f, const uint8_t* mask, float* eout, hipStream_t s
 ld_status run_peaks(ld_frame f, ld_lanes* lanes, float* curves, hipStream_t st, const Dev* dsel = nullptr) {
     ProfScope ps(f, 5, st);
     const Dev& d = dsel ? *dsel : f->d;
-    hipLaunchKernelGGL(k_peaks, dim3(f->active), dim3(kBlock), (size_t)d.W2, st, d, lanes, curves);
+    const size_t l = curves ? std::max((size_t)d.W2, kCurveLds) : (size_t)d.W2;
+    hipLaunchKernelGGL(k_peaks, dim3(f->active), dim3(kBlock), l, st, d, lanes, curves);
     return launch_ok();
 }
 

@@ -92,3 +92,14 @@ def test_vdisp_path_by_rows_and_jumps(w, h, d_max, kw):
     out.pop("curves", None)     # FP32, far outside the image for a poor model
     for b in range(2):
         compare_frame(out, b, g[b], d[b], d_max, params=oracle.default_params(**kw))
+
+
+@pytest.mark.parametrize("h", [255, 256, 257, 513])
+def test_curves_by_rows(h):
+    # the curves leave in tiles of 256 rows
+    g, d = _frames("road", 320, h, 2)
+    out = run_gpu(g, d, 48)
+    for b in range(2):
+        r = compare_frame(out, b, g[b], d[b], 48)
+        top = out["curves"][b, :, :r.v_end]
+        assert np.isnan(top).all() and np.isnan(out["curves"][b, len(r.u_start):]).all()
