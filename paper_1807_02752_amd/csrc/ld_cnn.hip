@@ -37,6 +37,7 @@ constexpr int kNP = LD_CNN_PARAMS;
 constexpr int kOffW1 = 0, kOffB1 = 576, kOffW2 = 592, kOffB2 = 2896, kOffW3 = 2912, kOffB3 = 3056;
 constexpr int kPart = 3072;          // floats per workgroup partial: gradients, then the loss
 constexpr int kLossSlot = 3064;
+constexpr int kRedCols = 16, kRedRows = 256;   // columns and rows of a tile of the partials' reduction
 constexpr int kBR = LDI_BAND_ROWS;
 constexpr int kCT = 60;              // output columns owned by a workgroup
 constexpr int kXW = 72;              // LDS columns, u = u0 - 4 + x
@@ -731,13 +732,43 @@ __global__ __launch_bounds__(kT) void k_cnn_train(ldi_frame_view V, Net N, int n
     }
 }
 
-// grad[i] = sum over the workgroups, in workgroup order
-__global__ void k_cnn_reduce(const float* part, int nwg, float* grad) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= kPart || (i >= kNP && i != kLossSlot)) return;
+// grad[i] = sum over the workgroups, in workgroup order.  The order makes a column's sum one chain
+// of additions, so what a chain waits for must not be memory: a workgroup takes kRedCols columns,
+// all its threads load the next kRedRows partials of them while one lane a column adds the tile
+// before from LDS (1344 partials: 78 us with a thread a column loading as it adds, 5.2 so).
+__global__ __launch_bounds__(256) void k_cnn_reduce(const float* part, int nwg, float* grad) {
+    __shared__ __align__(16) float tile[kRedCols][kRedRows + 4];
+    const int t = threadIdx.x, c0 = blockIdx.x * kRedCols, col = t % kRedCols, r0 = t / kRedCols;
+    if (c0 >= kNP && (kLossSlot < c0 || kLossSlot >= c0 + kRedCols)) return;
+    constexpr int kEach = kRedRows * kRedCols / 256, kStep = 256 / kRedCols;
+    float x[kEach];
+    auto load = [&](int w0) {                                    // rows past the last are not used
+#pragma unroll
+        for (int k = 0; k < kEach; ++k) x[k] = part[(int64_t)min(w0 + r0 + k * kStep, nwg - 1) * kPart + c0 + col];
+    };
+    load(0);
     float s = 0.0f;
-    for (int w = 0; w < nwg; ++w) s += part[(int64_t)w * kPart + i];
-    grad[i] = s;
+    for (int w0 = 0; w0 < nwg; w0 += kRedRows) {
+#pragma unroll
+        for (int k = 0; k < kEach; ++k) tile[col][r0 + k * kStep] = x[k];
+        __syncthreads();
+        if (w0 + kRedRows < nwg) load(w0 + kRedRows);
+        if (t < kRedCols) {
+            const int n = min(kRedRows, nwg - w0);
+            int r = 0;
+            for (; r + 16 <= n; r += 16) {
+                float4 v[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) v[k] = *reinterpret_cast<const float4*>(&tile[t][r + 4 * k]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) { s += v[k].x; s += v[k].y; s += v[k].z; s += v[k].w; }
+            }
+            for (; r < n; ++r) s += tile[t][r];
+        }
+        __syncthreads();
+    }
+    const int i = c0 + t;
+    if (t < kRedCols && (i < kNP || i == kLossSlot)) grad[i] = s;
 }
 
 __global__ void k_cnn_adam(float* master, float* m, float* v, const float* grad, float lr, float b1, float b2,
@@ -1113,7 +1144,7 @@ ld_status ld_cnn_train_step(ld_cnn n, ld_frame f, const uint8_t* grey, int64_t g
     hipLaunchKernelGGL(k_cnn_train, dim3(nct, nb, V.active), dim3(kT), kTrainLds, st, V, N, nb, grey, grey_pitch,
                        static_cast<const uint8_t*>(disp), disp_pitch, labels, pos_weight, inv_norm, n->part);
     if ((s = hip_ok(hipGetLastError())) != LD_OK) return s;
-    hipLaunchKernelGGL(k_cnn_reduce, dim3((kPart + 255) / 256), dim3(256), 0, st, n->part, (int)nwg, n->grad);
+    hipLaunchKernelGGL(k_cnn_reduce, dim3(kPart / kRedCols), dim3(256), 0, st, n->part, (int)nwg, n->grad);
     if ((s = hip_ok(hipGetLastError())) != LD_OK) return s;
     if (grad_out && hipMemcpyAsync(grad_out, n->grad, sizeof(float) * kNP, hipMemcpyDeviceToDevice, st) != hipSuccess)
         return LD_E_HIP;

@@ -465,3 +465,38 @@ def test_trained_network_gain():
     det.close()
     net.close()
     net_c.close()
+
+
+@pytest.mark.parametrize("B,nb", [(1, 1), (15, 4), (16, 4), (17, 4), (33, 4), (43, 3)])
+def test_gradient_sums_every_workgroup_once(B, nb):
+    # B x nb x 4 workgroups: fewer than, as many as and more than the 256 a tile of the sum takes.
+    # With one frame labelled at a time the gradients and losses add up to the whole batch's (FP32
+    # sums of at most 528 terms: 528 x 2^-24 = 3e-5 of their absolute sum, which cancellation
+    # inside a frame is allowed to exceed the gradient by thirty times)
+    ld = _ld()
+    greys, disps = frames_c2(2, seed=4)
+    g = torch.from_numpy(np.stack([greys[b % 2][:, 480:720] for b in range(B)])).cuda()
+    d = torch.from_numpy(np.stack([disps[b % 2][:, 480:720] for b in range(B)])).cuda()
+    H, W = g.shape[1:]
+    net = ld.Cnn(random_params(7), n_bands=nb, max_batch=B, max_width=W)
+    det = ld.Detector(W, H, B, ld.LD_DISP_F32, 128)
+    labels = _labels_for(np.random.default_rng(9), B, nb, W)
+    det.vdisp(d)
+
+    def step(lab):
+        loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+        grad = torch.zeros(ld.LD_CNN_PARAMS, dtype=torch.float32, device="cuda")
+        net.train_step(det, g, d, torch.from_numpy(lab).cuda(), 4.0, 1e-4, 0.0, loss, grad)
+        det.sync()
+        return np.append(grad.cpu().numpy().astype(np.float64), float(loss.item()))
+
+    whole = step(labels)
+    parts = []
+    for b in range(B):
+        one = np.full_like(labels, 255)
+        one[b] = labels[b]
+        parts.append(step(one))
+    assert np.abs(whole).max() > 0
+    assert np.abs(whole - np.sum(parts, 0)).max() <= 1e-3 * np.sum(np.abs(parts), 0).max()
+    det.close()
+    net.close()
