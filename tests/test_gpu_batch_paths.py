@@ -103,3 +103,21 @@ def test_curves_by_rows(h):
         r = compare_frame(out, b, g[b], d[b], 48)
         top = out["curves"][b, :, :r.v_end]
         assert np.isnan(top).all() and np.isnan(out["curves"][b, len(r.u_start):]).all()
+
+
+@pytest.mark.parametrize("w,h,n", [(64, 41, 1), (64, 42, 3), (48, 39, 2458), (48, 40, 2457), (48, 42, 6700), (33, 44, 7100)])
+def test_vdisp_histogram_by_frame_count(w, h, n):
+    # four, eight and all rows a workgroup, with rows left over: counts of every row and disparity
+    import torch
+    from paper_1807_02752_amd import ld
+    rng = np.random.default_rng(h)
+    disp = rng.integers(0, 40, size=(n, h, w)).astype(np.uint8)
+    det = ld.Detector(w, h, n, ld.LD_DISP_U8, 32)
+    out = torch.full((n, h, 33), -1, dtype=torch.int32, device="cuda")
+    det.vdisp(torch.from_numpy(disp).cuda(), vdisp_out=out)
+    det.sync()
+    got = out.cpu().numpy()
+    det.close()
+    for b in sorted({0, 1 % n, n // 2, n - 1}):
+        want = np.stack([np.bincount(np.minimum(row[row > 0], 32), minlength=33) for row in disp[b]])
+        assert np.array_equal(got[b], want), b
