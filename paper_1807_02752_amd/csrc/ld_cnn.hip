@@ -43,6 +43,7 @@ constexpr int kCT = 60;              // output columns owned by a workgroup
 constexpr int kXW = 72;              // LDS columns, u = u0 - 4 + x
 constexpr int kLR = kBR + 2;         // LDS rows
 constexpr int kT = 256;              // threads per workgroup (4 waves)
+constexpr int kTrainWaves = 16, kTrainT = 64 * kTrainWaves;   // of a training workgroup
 constexpr int kChunks = 28;          // packed A operands: 2 + 5 + 5 forward, 1 + 5 input gradient, 5 + 5 row sweep
 constexpr int kFeatElems = kLR * kXW * 4;
 constexpr int kActElems = kLR * kXW * 16;
@@ -103,13 +104,14 @@ constexpr size_t kStageBytes = 18 * kGW + sizeof(float) * kBR * kDW + sizeof(dou
 // Features of the staged tile (grey rows top-1 .. top+16, columns u0-4 .. u0+67; disparities
 // of rows top .. top+15, columns u0-3 .. u0+62; f(v) of the 16 rows) into feat at x = 1 .. 66
 // of rows 1 .. 16; pixels outside the frame get zero features.
+template <int WV>
 __device__ void features_from_stage(const ldi_frame_view& V, int u0, uint16_t* feat, const unsigned char* stage) {
     const int W = V.W, t = threadIdx.x;
     const uint8_t* gs = stage;
     const float* ds = reinterpret_cast<const float*>(stage + 18 * kGW);
     const double* fs = reinterpret_cast<const double*>(ds + kBR * kDW);
     const float inv_pi = (float)(1.0 / 3.14159265358979323846);
-    for (int i = t; i < kBR * 66; i += kT) {
+    for (int i = t; i < kBR * 66; i += 64 * WV) {
         const int r = i / 66, x = 1 + i % 66, u = u0 - 4 + x;
         uint2 pk = make_uint2(0u, 0u);
         if (u >= 0 && u < W) {
@@ -150,6 +152,7 @@ __device__ __forceinline__ float disp_value(const uint8_t* row, int u, int fmt) 
 // with the Sobel pair G_x = d/du, G_y = d/dv (weights 1, 2, 1, zero outside the frame).
 // The grey rows top-1 .. top+16 and the disparities are first staged in LDS (every load of
 // the workgroup in flight at once), then each pixel's features are formed from LDS.
+template <int WV>
 __device__ void build_features(const ldi_frame_view& V, int b, int top, int u0, const uint8_t* grey, int64_t gp,
                                const uint8_t* disp, int64_t dp, uint16_t* feat, unsigned char* stage) {
     const int W = V.W, H = V.H, t = threadIdx.x;
@@ -158,17 +161,17 @@ __device__ void build_features(const ldi_frame_view& V, int b, int top, int u0, 
     double* fs = reinterpret_cast<double*>(ds + kBR * kDW);          // 16
     const uint8_t* gb = grey + (int64_t)b * H * gp;
     const uint8_t* db = disp + (int64_t)b * H * dp;
-    for (int i = t; i < 18 * kGW; i += kT) {
+    for (int i = t; i < 18 * kGW; i += 64 * WV) {
         const int r = i / kGW, u = u0 - 4 + i % kGW, v = top - 1 + r;
         gs[i] = (v >= 0 && v < H && u >= 0 && u < W) ? gb[(int64_t)v * gp + u] : (uint8_t)0;
     }
-    for (int i = t; i < kBR * kDW; i += kT) {
+    for (int i = t; i < kBR * kDW; i += 64 * WV) {
         const int r = i / kDW, u = u0 - 3 + i % kDW;
         ds[i] = (u >= 0 && u < W) ? disp_value(db + (int64_t)(top + r) * dp, u, V.fmt) : -1.0f;
     }
     if (t < kBR) fs[t] = V.tab[(int64_t)b * 6 * H + top + t];
     __syncthreads();
-    features_from_stage(V, u0, feat, stage);
+    features_from_stage<WV>(V, u0, feat, stage);
 }
 
 // The raw inputs of one tile held in registers between units: thread t holds the staged
@@ -215,8 +218,9 @@ __device__ __forceinline__ void stage_tile(const RawTile& R, unsigned char* stag
     if (t < kBR) fs[t] = R.f;
 }
 
+template <int WV>
 __device__ __forceinline__ void zero_lds(uint4* p, int n16) {
-    for (int i = threadIdx.x; i < n16; i += kT) p[i] = make_uint4(0u, 0u, 0u, 0u);
+    for (int i = threadIdx.x; i < n16; i += 64 * WV) p[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
 // The cells of an activation buffer that the layers read but never write: the zero rows 0
@@ -235,8 +239,9 @@ __device__ __forceinline__ void zero_act_border(uint16_t* act) {
     }
 }
 
-// Layer 1 (4 -> 16): 64 tiles (16 rows x 4), 16 per wave; writes ReLU(z1) as BF16 to a1 at
+// Layer 1 (4 -> 16): 64 tiles (16 rows x 4), 64 / WV per wave; writes ReLU(z1) as BF16 to a1 at
 // x = 2 .. 65, zero outside the frame.
+template <int WV>
 __device__ void layer1(const uint16_t* feat, uint16_t* a1, const Net& N, int u0, int W) {
     const int lane = __lane_id(), wave = threadIdx.x / 64, n = lane & 15, g = lane >> 4;
     const uint4 A0 = N.wpk[lane], A1 = N.wpk[64 + lane];
@@ -246,8 +251,8 @@ __device__ void layer1(const uint16_t* feat, uint16_t* a1, const Net& N, int u0,
     for (int j = 0; j < 4; ++j) bias[j] = b1[4 * g + j];
     const int t0 = 2 * g, t1 = 2 * g + 1;
 #pragma unroll 4
-    for (int k = 0; k < 16; ++k) {
-        const int tile = wave + 4 * k, r = tile >> 2, x0 = 2 + 16 * (tile & 3);
+    for (int k = 0; k < 64 / WV; ++k) {
+        const int tile = wave + WV * k, r = tile >> 2, x0 = 2 + 16 * (tile & 3);
         const uint16_t* base = feat + ((r + 1) * kXW + x0 + n) * 4;
         const uint2 p0 = *reinterpret_cast<const uint2*>(base + (tap_dy(t0) * kXW + tap_dx(t0)) * 4);
         const uint2 p1 = *reinterpret_cast<const uint2*>(base + (tap_dy(t1) * kXW + tap_dx(t1)) * 4);
@@ -271,7 +276,8 @@ __device__ void layer1(const uint16_t* feat, uint16_t* a1, const Net& N, int u0,
 }
 
 // 16-channel 3x3 convolution of `in` on the 64 tiles at x0 = xs + 16 ct; A = 5 packed chunks.
-__device__ __forceinline__ void conv16(const uint16_t* in, int xs, const uint4* A, f32x4 (&acc)[16]) {
+template <int WV>
+__device__ __forceinline__ void conv16(const uint16_t* in, int xs, const uint4* A, f32x4 (&acc)[64 / WV]) {
     const int lane = __lane_id(), wave = threadIdx.x / 64, n = lane & 15, g = lane >> 4;
     uint4 Ac[5];
 #pragma unroll
@@ -285,8 +291,8 @@ __device__ __forceinline__ void conv16(const uint16_t* in, int xs, const uint4* 
         off[c] = val[c] ? (tap_dy(tap) * kXW + tap_dx(tap)) * 16 + 8 * (g & 1) : 0;
     }
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int tile = wave + 4 * k, r = tile >> 2, x0 = xs + 16 * (tile & 3);
+    for (int k = 0; k < 64 / WV; ++k) {
+        const int tile = wave + WV * k, r = tile >> 2, x0 = xs + 16 * (tile & 3);
         const uint16_t* base = in + ((r + 1) * kXW + x0 + n) * 16;
         f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -299,15 +305,16 @@ __device__ __forceinline__ void conv16(const uint16_t* in, int xs, const uint4* 
 }
 
 // ReLU(acc + bias) as BF16 into `out` at the tiles of conv16(xs), zero outside the frame
-__device__ __forceinline__ void store16(uint16_t* out, int xs, const f32x4 (&acc)[16], const float* bias_all, int u0,
+template <int WV>
+__device__ __forceinline__ void store16(uint16_t* out, int xs, const f32x4 (&acc)[64 / WV], const float* bias_all, int u0,
                                         int W) {
     const int lane = __lane_id(), wave = threadIdx.x / 64, n = lane & 15, g = lane >> 4;
     float bias[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) bias[j] = bias_all[4 * g + j];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) {
-        const int tile = wave + 4 * k, r = tile >> 2, x0 = xs + 16 * (tile & 3);
+    for (int k = 0; k < 64 / WV; ++k) {
+        const int tile = wave + WV * k, r = tile >> 2, x0 = xs + 16 * (tile & 3);
         const int u = u0 - 4 + x0 + n;
         const bool in = u >= 0 && u < W;
         uint2 o;
@@ -393,7 +400,7 @@ __global__ __launch_bounds__(kT, 3) void k_cnn_fwd(ldi_frame_view V, Net N, int 
         const int q = (first + t) / nct;
         tops[t] = frame_band_top(V, q / nb, nb, q % nb);
     }
-    zero_lds(smem4, kFeatElems / 8);
+    zero_lds<kT / 64>(smem4, kFeatElems / 8);
     __syncthreads();
     {   // sparse: wave w looks for a voting road edge on the band rows and columns of unit w
         const int w = t / 64, l = t % 64;
@@ -445,7 +452,7 @@ __global__ __launch_bounds__(kT, 3) void k_cnn_fwd(ldi_frame_view V, Net N, int 
             __syncthreads();                   // the previous unit has finished reading act
             stage_tile(R, stage);
             __syncthreads();
-            features_from_stage(V, u0, feat, stage);
+            features_from_stage<kT / 64>(V, u0, feat, stage);
         }
         if (k + 1 < count) {                   // the next unit's inputs stay in flight below
             const int un = unit + 1, qn = un / nct, tn = need[k + 1] ? tops[k + 1] : -1;
@@ -455,12 +462,12 @@ __global__ __launch_bounds__(kT, 3) void k_cnn_fwd(ldi_frame_view V, Net N, int 
         __syncthreads();
         zero_act_border(act);
         __syncthreads();
-        layer1(feat, act, N, u0, W);
+        layer1<kT / 64>(feat, act, N, u0, W);
         __syncthreads();
         f32x4 acc[16];
         conv_rows(act, 3, N.wpk + 18 * 64, acc);
         __syncthreads();                       // every wave has read a1: a2 replaces it in place
-        store16(act, 3, acc, N.master + kOffB2, u0, W);
+        store16<kT / 64>(act, 3, acc, N.master + kOffB2, u0, W);
         __syncthreads();
         conv_rows(act, 4, N.wpk + 23 * 64, acc);
         // layer 3 is packed into all 16 output rows of the tile, so every lane holds z of its
@@ -484,9 +491,16 @@ __global__ __launch_bounds__(kT, 3) void k_cnn_fwd(ldi_frame_view V, Net N, int 
 // ------------------------------------------------------------------------------------------
 // Training: forward, loss, backward and this workgroup's share of every gradient (its own
 // 60 x 16 loss terms through the recomputed halo), written to one partial row.
+//
+// The two activation buffers of a tile take 83 of the 112 KB of LDS, so a CU holds one workgroup
+// and every phase is the latency of its chains of LDS reads and MFMAs: sixteen waves share a tile
+// (four tiles of 16 pixels a wave, a tap of dW2 a wave), the labels are loaded at the start, and
+// the channel sums of dz2 and dz1 are formed by waves that the weight gradients leave idle.  Every
+// sum keeps the order that it had over four waves.  16 frames x 4 bands of 1242 columns: 119 us
+// with four waves (the labels' loads alone 11 of a workgroup's 55), 72 with sixteen.
 __device__ __forceinline__ float softplus(float z) { return fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z))); }
 
-__global__ __launch_bounds__(kT) void k_cnn_train(ldi_frame_view V, Net N, int nb, const uint8_t* grey, int64_t gp,
+__global__ __launch_bounds__(kTrainT) void k_cnn_train(ldi_frame_view V, Net N, int nb, const uint8_t* grey, int64_t gp,
                                                   const uint8_t* disp, int64_t dp, const uint8_t* labels,
                                                   float pos_weight, float inv_norm, float* part) {
     extern __shared__ uint4 smem4[];
@@ -495,52 +509,58 @@ __global__ __launch_bounds__(kT) void k_cnn_train(ldi_frame_view V, Net N, int n
     uint16_t* a2 = a1 + kActElems;               // a2, later dz2
     uint16_t* dz3 = a2 + kActElems;              // kLR x kXW
     float* red = reinterpret_cast<float*>(dz3 + kLR * kXW);   // 4 x 256 + 256 x 4 floats
+    float* lterm = red + 2048;                                // 64 x 16 loss terms; the staged inputs before
     const int ct = blockIdx.x, band = blockIdx.y, b = blockIdx.z, t = threadIdx.x;
     const int lane = __lane_id(), wave = t / 64, n = lane & 15, g = lane >> 4;
     float* out = part + (((int64_t)b * nb + band) * gridDim.x + ct) * kPart;
     const int W = V.W, u0 = ct * kCT;
     const int top = (V.nact != nullptr && b >= *V.nact) ? -1 : frame_band_top(V, b, nb, band);
     if (top < 0) {
-        for (int i = t; i < kPart; i += kT) out[i] = 0.0f;
+        for (int i = t; i < kPart; i += kTrainT) out[i] = 0.0f;
         return;
     }
-    zero_lds(smem4, (kFeatElems + 2 * kActElems + kLR * kXW) / 8);
-    build_features(V, b, top, u0, grey, gp, disp, dp, feat, reinterpret_cast<unsigned char*>(red + 2048));
-    __syncthreads();
-    layer1(feat, a1, N, u0, W);
-    __syncthreads();
-    f32x4 acc[16];
-    conv16(a1, 3, N.wpk + 2 * 64, acc);
-    store16(a2, 3, acc, N.master + kOffB2, u0, W);
-    __syncthreads();
-    conv16(a2, 4, N.wpk + 7 * 64, acc);
-
-    // ---- loss and dL/dz3 (BF16) of the owned pixels
+    // the labels of the pixels this lane owns, needed much later
+    constexpr int kTiles = 64 / kTrainWaves;
     const uint8_t* lab = labels + ((int64_t)b * nb + band) * kBR * W;
-    float loss = 0.0f, db3 = 0.0f;
+    int y[kTiles];
+#pragma unroll
+    for (int k = 0; k < kTiles; ++k) {
+        const int tile = wave + kTrainWaves * k, col = 16 * (tile & 3) + n, u = u0 + col;
+        const int at = (tile >> 2) * W + min(u, W - 1);
+        y[k] = lab[at];
+        if (col >= kCT || u >= W) y[k] = 255;
+    }
+    zero_lds<kTrainWaves>(smem4, (kFeatElems + 2 * kActElems + kLR * kXW) / 8);
+    build_features<kTrainWaves>(V, b, top, u0, grey, gp, disp, dp, feat, reinterpret_cast<unsigned char*>(red + 2048));
+    __syncthreads();
+    layer1<kTrainWaves>(feat, a1, N, u0, W);
+    __syncthreads();
+    f32x4 acc[kTiles];
+    conv16<kTrainWaves>(a1, 3, N.wpk + 2 * 64, acc);
+    store16<kTrainWaves>(a2, 3, acc, N.master + kOffB2, u0, W);
+    __syncthreads();
+    conv16<kTrainWaves>(a2, 4, N.wpk + 7 * 64, acc);
+
+    // ---- loss terms and dL/dz3 (BF16) of the owned pixels
     if (lane < 16) {
         const float b3 = N.master[kOffB3];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int tile = wave + 4 * k, r = tile >> 2, col = 16 * (tile & 3) + n, u = u0 + col;
-            float gz = 0.0f;
-            if (col < kCT && u < W) {
-                const int y = lab[r * W + u];
-                if (y != 255) {
-                    const float z = acc[k][0] + b3;
-                    const float s = 1.0f / (1.0f + expf(-z));
-                    if (y) {
-                        gz = pos_weight * (s - 1.0f) * inv_norm;
-                        loss += pos_weight * softplus(-z) * inv_norm;
-                    } else {
-                        gz = s * inv_norm;
-                        loss += softplus(z) * inv_norm;
-                    }
+        for (int k = 0; k < kTiles; ++k) {
+            const int tile = wave + kTrainWaves * k, r = tile >> 2;
+            float gz = 0.0f, loss = 0.0f;
+            if (y[k] != 255) {
+                const float z = acc[k][0] + b3;
+                const float s = 1.0f / (1.0f + expf(-z));
+                if (y[k]) {
+                    gz = pos_weight * (s - 1.0f) * inv_norm;
+                    loss = pos_weight * softplus(-z) * inv_norm;
+                } else {
+                    gz = s * inv_norm;
+                    loss = softplus(z) * inv_norm;
                 }
             }
-            const uint32_t h = bf16_bits(gz);
-            db3 += bf16_val(h);
-            dz3[(r + 1) * kXW + 4 + 16 * (tile & 3) + n] = (uint16_t)h;
+            lterm[tile * 16 + n] = loss;
+            dz3[(r + 1) * kXW + 4 + 16 * (tile & 3) + n] = (uint16_t)bf16_bits(gz);
         }
     }
     __syncthreads();
@@ -550,14 +570,15 @@ __global__ __launch_bounds__(kT) void k_cnn_train(ldi_frame_view V, Net N, int n
         f32x4 d = {0.0f, 0.0f, 0.0f, 0.0f};
         const int tap = n;
         const int dyx = tap < 9 ? tap_dy(tap) * kXW + tap_dx(tap) : 0;
-        for (int kc = wave; kc < 32; kc += 4) {
+        for (int kc = wave; kc < 32 && wave < 4; kc += 4) {
             const int rr = kc >> 1, xq = 3 + 32 * (kc & 1) + 8 * g;
             const uint4 A = pack8(a2 + ((rr + 1) * kXW + xq) * 16 + n, 16);
             const uint4 B = tap < 9 ? pack8(dz3 + (rr + 1) * kXW + xq - dyx, 1) : make_uint4(0u, 0u, 0u, 0u);
             d = mfma(A, B, d);
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) red[wave * 256 + (4 * g + j) * 16 + n] = d[j];   // [c][tap]
+        for (int j = 0; j < 4; ++j)
+            if (wave < 4) red[wave * 256 + (4 * g + j) * 16 + n] = d[j];   // [c][tap]
     }
     __syncthreads();
     if (t < 144) {   // t = tap * 16 + c
@@ -568,12 +589,11 @@ __global__ __launch_bounds__(kT) void k_cnn_train(ldi_frame_view V, Net N, int n
     __syncthreads();
 
     // ---- dz2 = BF16(dL/da2 * (a2 > 0)) in place of a2; dL/da2[q][c] = sum_tap w3[tap][c] dz3[q - off(tap)]
-    float cs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     {
         const uint4 A = N.wpk[12 * 64 + lane];
-#pragma unroll 4
-        for (int k = 0; k < 16; ++k) {
-            const int tile = wave + 4 * k, r = tile >> 2, x0 = 3 + 16 * (tile & 3);
+#pragma unroll
+        for (int k = 0; k < kTiles; ++k) {
+            const int tile = wave + kTrainWaves * k, r = tile >> 2, x0 = 3 + 16 * (tile & 3);
             uint4 Bv = make_uint4(0u, 0u, 0u, 0u);
             const uint16_t* q = dz3 + (r + 1) * kXW + x0 + n;
             if (g == 0) {
@@ -596,55 +616,59 @@ __global__ __launch_bounds__(kT) void k_cnn_train(ldi_frame_view V, Net N, int n
             o[1] = positive(av.x >> 16) ? bf16_round(d[1]) : 0.0f;
             o[2] = positive(av.y) ? bf16_round(d[2]) : 0.0f;
             o[3] = positive(av.y >> 16) ? bf16_round(d[3]) : 0.0f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) cs[j] += o[j];
             uint2 w;
             w.x = bf16_bits(o[0]) | (bf16_bits(o[1]) << 16);
             w.y = bf16_bits(o[2]) | (bf16_bits(o[3]) << 16);
             *reinterpret_cast<uint2*>(cell) = w;
         }
     }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) red[1024 + t * 4 + j] = cs[j];
     __syncthreads();
-    if (t < 16) {   // db2[c], lanes with 4g <= c < 4g + 4 in a fixed order
-        const int gg = t >> 2, j = t & 3;
+    // sums over the pixels of the channels of `act` at the tiles from column xs on, for db2 and db1:
+    // in a fixed order, four lanes' worth of rows of 16 tiles each (the values are BF16, so the
+    // stored ones are the ones summed); ts is the thread's place among 256
+    auto channel_sums = [&](const uint16_t* act, int xs, int ts) {
+        const int vw = ts / 64, nn = ts & 15, gg = (ts & 63) >> 4;
+        float cs[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 4
+        for (int k = 0; k < 16; ++k) {
+            const int tile = vw + 4 * k, r = tile >> 2, x0 = xs + 16 * (tile & 3);
+            const uint2 v = *reinterpret_cast<const uint2*>(act + ((r + 1) * kXW + x0 + nn) * 16 + 4 * gg);
+            cs[0] += bf16_val(v.x & 0xFFFFu); cs[1] += bf16_val(v.x >> 16);
+            cs[2] += bf16_val(v.y & 0xFFFFu); cs[3] += bf16_val(v.y >> 16);
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) red[1024 + ts * 4 + j] = cs[j];
+    };
+    auto channel_total = [&](int c) {   // lanes with 4g <= c < 4g + 4 in a fixed order
+        const int gg = c >> 2, j = c & 3;
         float s = 0.0f;
         for (int w = 0; w < 4; ++w)
             for (int nn = 0; nn < 16; ++nn) s += red[1024 + (w * 64 + gg * 16 + nn) * 4 + j];
-        out[kOffB2 + t] = s;
-    }
+        return s;
+    };
 
-    // ---- dW2[tap][ci][co] = sum_q a1[q + off(tap)][ci] dz2[q][co]; wave w owns taps w, w+4, w+8
-    {
-        f32x4 d[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) d[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    // ---- dW2[tap][ci][co] = sum_q a1[q + off(tap)][ci] dz2[q][co]; wave w owns tap w; the waves
+    //      after them sum dz2 for db2
+    if (wave < 9) {
+        const int tap = wave;
+        f32x4 d = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 2
         for (int kc = 0; kc < 32; ++kc) {
             const int rr = kc >> 1, xq = 3 + 32 * (kc & 1) + 8 * g;
             const uint4 B = pack8(a2 + ((rr + 1) * kXW + xq) * 16 + n, 16);            // dz2[q][co = n]
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                const int tap = wave + 4 * i;
-                if (tap < 9) {
-                    const uint4 A = pack8(a1 + ((rr + 1 + tap_dy(tap)) * kXW + xq + tap_dx(tap)) * 16 + n, 16);
-                    d[i] = mfma(A, B, d[i]);
-                }
-            }
+            const uint4 A = pack8(a1 + ((rr + 1 + tap_dy(tap)) * kXW + xq + tap_dx(tap)) * 16 + n, 16);
+            d = mfma(A, B, d);
         }
 #pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const int tap = wave + 4 * i;
-            if (tap < 9)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) out[kOffW2 + (tap * 16 + 4 * g + j) * 16 + n] = d[i][j];
-        }
+        for (int j = 0; j < 4; ++j) out[kOffW2 + (tap * 16 + 4 * g + j) * 16 + n] = d[j];
+    } else if (wave < 13) {
+        channel_sums(a2, 3, t - 9 * 64);
     }
     __syncthreads();
+    if (t >= kTrainT - 64 && t < kTrainT - 48) out[kOffB2 + t - (kTrainT - 64)] = channel_total(t - (kTrainT - 64));
 
     // ---- dz1 = BF16(dL/da1 * (a1 > 0)) in place of a1; dL/da1 = conv of dz2 with the flipped,
     //      transposed w2 (5 chunks)
-    float cs1[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     {
         uint4 Ac[5];
         int off[5];
@@ -656,10 +680,10 @@ __global__ __launch_bounds__(kT) void k_cnn_train(ldi_frame_view V, Net N, int n
             val[c] = tap < 9;
             off[c] = val[c] ? -(tap_dy(tap) * kXW + tap_dx(tap)) * 16 + 8 * (g & 1) : 0;
         }
-        f32x4 dd[16];
+        f32x4 dd[kTiles];
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int tile = wave + 4 * k, r = tile >> 2, x0 = 2 + 16 * (tile & 3);
+        for (int k = 0; k < kTiles; ++k) {
+            const int tile = wave + kTrainWaves * k, r = tile >> 2, x0 = 2 + 16 * (tile & 3);
             const uint16_t* base = a2 + ((r + 1) * kXW + x0 + n) * 16;
             f32x4 a = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -670,8 +694,8 @@ __global__ __launch_bounds__(kT) void k_cnn_train(ldi_frame_view V, Net N, int n
             dd[k] = a;
         }
 #pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            const int tile = wave + 4 * k, r = tile >> 2, x0 = 2 + 16 * (tile & 3);
+        for (int k = 0; k < kTiles; ++k) {
+            const int tile = wave + kTrainWaves * k, r = tile >> 2, x0 = 2 + 16 * (tile & 3);
             uint16_t* cell = a1 + ((r + 1) * kXW + x0 + n) * 16 + 4 * g;
             const uint2 av = *reinterpret_cast<const uint2*>(cell);
             float o[4];
@@ -679,8 +703,6 @@ __global__ __launch_bounds__(kT) void k_cnn_train(ldi_frame_view V, Net N, int n
             o[1] = positive(av.x >> 16) ? bf16_round(dd[k][1]) : 0.0f;
             o[2] = positive(av.y) ? bf16_round(dd[k][2]) : 0.0f;
             o[3] = positive(av.y >> 16) ? bf16_round(dd[k][3]) : 0.0f;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) cs1[j] += o[j];
             uint2 w;
             w.x = bf16_bits(o[0]) | (bf16_bits(o[1]) << 16);
             w.y = bf16_bits(o[2]) | (bf16_bits(o[3]) << 16);
@@ -688,17 +710,6 @@ __global__ __launch_bounds__(kT) void k_cnn_train(ldi_frame_view V, Net N, int n
         }
     }
     __syncthreads();   // every wave has read dz2 and written its dz1 cells
-#pragma unroll
-    for (int j = 0; j < 4; ++j) red[1024 + t * 4 + j] = cs1[j];
-    __syncthreads();
-    if (t < 16) {
-        const int gg = t >> 2, j = t & 3;
-        float s = 0.0f;
-        for (int w = 0; w < 4; ++w)
-            for (int nn = 0; nn < 16; ++nn) s += red[1024 + (w * 64 + gg * 16 + nn) * 4 + j];
-        out[kOffB1 + t] = s;
-    }
-
     // ---- dW1[tap][ci][co] = sum_q x[q + off(tap)][ci] dz1[q][co]; M = 4 taps x 4 channels,
     //      wave w < 3 owns taps 4w .. 4w+3
     if (wave < 3) {
@@ -716,15 +727,25 @@ __global__ __launch_bounds__(kT) void k_cnn_train(ldi_frame_view V, Net N, int n
             const int m = 4 * g + j, tp = 4 * wave + (m >> 2), c = m & 3;
             if (tp < 9) out[kOffW1 + (tp * 4 + c) * 16 + n] = d[j];
         }
+    } else if (wave >= 4 && wave < 8) {
+        channel_sums(a1, 2, t - 256);
     }
+    __syncthreads();
+    if (t >= 256 && t < 272) out[kOffB1 + t - 256] = channel_total(t - 256);
 
-    // ---- loss and db3: wave sums, then the waves in order
+    // ---- loss and db3: 16 lanes' pixels of four rows of tiles each, wave sums, then the waves in order
+    float loss = 0.0f, db3 = 0.0f;
+    if (wave < 4 && lane < 16)
+        for (int k = 0; k < 16; ++k) {
+            const int tile = wave + 4 * k;
+            loss += lterm[tile * 16 + n];
+            db3 += bf16_val(dz3[((tile >> 2) + 1) * kXW + 4 + 16 * (tile & 3) + n]);
+        }
     for (int o = 32; o > 0; o >>= 1) {
         loss += __shfl_xor(loss, o, 64);
         db3 += __shfl_xor(db3, o, 64);
     }
-    __syncthreads();
-    if (lane == 0) { red[2 * wave] = loss; red[2 * wave + 1] = db3; }
+    if (lane == 0 && wave < 4) { red[2 * wave] = loss; red[2 * wave + 1] = db3; }
     __syncthreads();
     if (t == 0) {
         out[kLossSlot] = ((red[0] + red[2]) + red[4]) + red[6];
@@ -1141,7 +1162,7 @@ ld_status ld_cnn_train_step(ld_cnn n, ld_frame f, const uint8_t* grey, int64_t g
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     allow_lds(k_cnn_train, kTrainLds);
     Net N{n->wpk, n->master};
-    hipLaunchKernelGGL(k_cnn_train, dim3(nct, nb, V.active), dim3(kT), kTrainLds, st, V, N, nb, grey, grey_pitch,
+    hipLaunchKernelGGL(k_cnn_train, dim3(nct, nb, V.active), dim3(kTrainT), kTrainLds, st, V, N, nb, grey, grey_pitch,
                        static_cast<const uint8_t*>(disp), disp_pitch, labels, pos_weight, inv_norm, n->part);
     if ((s = hip_ok(hipGetLastError())) != LD_OK) return s;
     hipLaunchKernelGGL(k_cnn_reduce, dim3(kPart / kRedCols), dim3(256), 0, st, n->part, (int)nwg, n->grad);
