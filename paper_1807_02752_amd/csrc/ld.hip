@@ -921,7 +921,7 @@ __global__ __launch_bounds__(1024) void k_vdisp_fit(Dev d, const uint64_t* strea
 // vote of every road edge (Eq. sparse_vpx_estimation with the gradient read as the edge
 // slope).
 //
-// A workgroup takes kEdgeStrip rows of one frame across its whole width: wave w owns the 256
+// A workgroup takes up to kEdgeStrip rows of one frame across its whole width: wave w owns the 256
 // columns from 256 w, four consecutive columns per lane, and walks the rows down.  A row is
 // loaded as one aligned dword per lane (plus the dwords left and right of the wave's span for
 // its first and last lane); the six bytes a lane needs (columns ub-1 .. ub+4) come from its own
@@ -937,7 +937,7 @@ __global__ __launch_bounds__(1024) void k_vdisp_fit(Dev d, const uint64_t* strea
 // nothing carries over from an earlier call).
 template <int N> using IntC = std::integral_constant<int, N>;
 
-constexpr int kEdgeStrip = 32;                        // rows per workgroup
+constexpr int kEdgeStrip = 32;                        // rows per workgroup, at most
 constexpr int kEdgeCols = 4 * kWave;                  // columns per wave
 constexpr int kEdgeQueue = 512;                       // queued edge pixels per wave
 constexpr int kEdgeFlushAt = kEdgeQueue - kEdgeCols;  // a row queues at most kEdgeCols
@@ -981,12 +981,12 @@ __device__ __forceinline__ uint32_t dpp_from_next(uint32_t x) {   // lane l gets
 
 template <int FMT>
 __global__ __launch_bounds__(1024) void k_edges(Dev d, const uint8_t* grey, int64_t gpitch, const uint8_t* disp,
-                                                int64_t dpitch) {
+                                                int64_t dpitch, int strip) {
     extern __shared__ __attribute__((aligned(16))) unsigned char esm[];   // strip tables, then the wave queues
-    const int b = blockIdx.y, s0 = blockIdx.x * kEdgeStrip;
+    const int b = blockIdx.y, s0 = blockIdx.x * strip;
     if (frame_masked(d, b)) return;
     const int W = d.W, H = d.H, t = threadIdx.x, lane = lane_id(), wave = t / kWave;
-    const int rows = min(kEdgeStrip, H - s0);
+    const int rows = min(strip, H - s0);
     double* svpy = reinterpret_cast<double*>(esm);                      // V_py of the strip's rows
     uint32_t* sbnd = reinterpret_cast<uint32_t*>(svpy + kEdgeStrip);    // raw road interval per row
     int* scnt = reinterpret_cast<int*>(sbnd + 2 * kEdgeStrip);          // edges per row
@@ -3069,19 +3069,25 @@ ld_status run_vdisp(ld_frame f, const void* disp, int64_t pitch, const uint64_t*
 ld_status run_edges(ld_frame f, const uint8_t* grey, int64_t gp, const void* disp, int64_t dpt, hipStream_t st) {
     Dev& d = f->d;
     const int nw = (d.W + kEdgeCols - 1) / kEdgeCols;
-    dim3 g3((d.H + kEdgeStrip - 1) / kEdgeStrip, f->active);
+    // Rows a workgroup: its time is a chain of rows and of the disparities gathered for them, and each
+    // strip loads two rows more than it takes (us at 2, 4, 8 and 32 rows: one 1242 x 375 frame 7, 9,
+    // 12, 27; 16 frames 17, 14, 15, 31; 61 of 1241 x 376 40, 32, 28, 36; 128 79, 61, 49, 58; 256
+    // 153, 114, 87, 90; 1024 590, 426, 312, 285)
+    const int64_t all = (int64_t)f->active * d.H;
+    const int strip = all <= 2048 ? 2 : all <= 8192 ? 4 : all <= 64 * 1024 ? 8 : kEdgeStrip;
+    const dim3 g3((d.H + strip - 1) / strip, f->active);
     const size_t lds = edges_lds(nw);
     const uint8_t* dp = static_cast<const uint8_t*>(disp);
     ProfScope ps(f, 2, st);
     if (d.fmt == LD_DISP_U8) {
         allow_lds(k_edges<LD_DISP_U8>, lds);
-        hipLaunchKernelGGL(k_edges<LD_DISP_U8>, g3, dim3(nw * kWave), lds, st, d, grey, gp, dp, dpt);
+        hipLaunchKernelGGL(k_edges<LD_DISP_U8>, g3, dim3(nw * kWave), lds, st, d, grey, gp, dp, dpt, strip);
     } else if (d.fmt == LD_DISP_F32) {
         allow_lds(k_edges<LD_DISP_F32>, lds);
-        hipLaunchKernelGGL(k_edges<LD_DISP_F32>, g3, dim3(nw * kWave), lds, st, d, grey, gp, dp, dpt);
+        hipLaunchKernelGGL(k_edges<LD_DISP_F32>, g3, dim3(nw * kWave), lds, st, d, grey, gp, dp, dpt, strip);
     } else {
         allow_lds(k_edges<LD_DISP_U16Q4>, lds);
-        hipLaunchKernelGGL(k_edges<LD_DISP_U16Q4>, g3, dim3(nw * kWave), lds, st, d, grey, gp, dp, dpt);
+        hipLaunchKernelGGL(k_edges<LD_DISP_U16Q4>, g3, dim3(nw * kWave), lds, st, d, grey, gp, dp, dpt, strip);
     }
     return launch_ok();
 }

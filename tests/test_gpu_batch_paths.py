@@ -121,3 +121,13 @@ def test_vdisp_histogram_by_frame_count(w, h, n):
     for b in sorted({0, 1 % n, n // 2, n - 1}):
         want = np.stack([np.bincount(np.minimum(row[row > 0], 32), minlength=33) for row in disp[b]])
         assert np.array_equal(got[b], want), b
+
+
+@pytest.mark.parametrize("w,h,n", [(257, 40, 51), (257, 41, 50), (130, 63, 130), (130, 64, 129), (64, 39, 1681), (64, 40, 1638)])
+def test_edges_by_frame_count(w, h, n):
+    # strips of two, four, eight and 32 rows, with and without rows left over
+    g, d = _frames("road", w, h, n)
+    out = run_gpu(g, d, 48)
+    out.pop("curves", None)     # FP32, far outside the image for a poor model
+    for b in sorted({0, n // 2, n - 1}):
+        compare_frame(out, b, g[b], d[b], 48)
