@@ -10,7 +10,9 @@
 //   k_edges        S4-5 Sobel on road rows, road mask, V_px vote column per edge
 //   k_vpx_fit      S6-7 sliding band accumulator, row DP
 //   k_vpx_ransac   S8   RANSAC V_px, track tables
-//   k_energy       S9-12 w_g, M_0, M_1 row ring, candidate-by-row energy accumulation
+//   k_energy       S9-12 w_g, M_0, M_1 row ring, candidate-by-row energy accumulation; for few
+//                  frames in two launches over the whole chip:
+//   k_m1           S9-11 w_g, M_0, M_1 in tiles, k_tracks S12 a candidate a lane
 //   k_peaks        S13  minima, threshold, suppression, lane curves
 #include <hip/hip_runtime.h>
 
