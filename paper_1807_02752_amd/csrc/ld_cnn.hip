@@ -496,8 +496,9 @@ __global__ __launch_bounds__(kT, 3) void k_cnn_fwd(ldi_frame_view V, Net N, int 
 // and every phase is the latency of its chains of LDS reads and MFMAs: sixteen waves share a tile
 // (four tiles of 16 pixels a wave, a tap of dW2 a wave), the labels are loaded at the start, and
 // the channel sums of dz2 and dz1 are formed by waves that the weight gradients leave idle.  Every
-// sum keeps the order that it had over four waves.  16 frames x 4 bands of 1242 columns: 119 us
-// with four waves (the labels' loads alone 11 of a workgroup's 55), 72 with sixteen.
+// sum keeps the order that it had over four waves.  16 frames of 1242 columns, one band (336
+// workgroups, so two rounds on 256 CUs): 119 us with four waves (the labels' loads alone 11 of a
+// workgroup's 55), 71 with sixteen.
 __device__ __forceinline__ float softplus(float z) { return fmaxf(z, 0.0f) + log1pf(expf(-fabsf(z))); }
 
 __global__ __launch_bounds__(kTrainT) void k_cnn_train(ldi_frame_view V, Net N, int nb, const uint8_t* grey, int64_t gp,
@@ -756,7 +757,7 @@ __global__ __launch_bounds__(kTrainT) void k_cnn_train(ldi_frame_view V, Net N, 
 // grad[i] = sum over the workgroups, in workgroup order.  The order makes a column's sum one chain
 // of additions, so what a chain waits for must not be memory: a workgroup takes kRedCols columns,
 // all its threads load the next kRedRows partials of them while one lane a column adds the tile
-// before from LDS (1344 partials: 78 us with a thread a column loading as it adds, 5.2 so).
+// before from LDS (336 partials: 78 us with a thread a column loading as it adds, 5.2 so).
 __global__ __launch_bounds__(256) void k_cnn_reduce(const float* part, int nwg, float* grad) {
     __shared__ __align__(16) float tile[kRedCols][kRedRows + 4];
     const int t = threadIdx.x, c0 = blockIdx.x * kRedCols, col = t % kRedCols, r0 = t / kRedCols;
