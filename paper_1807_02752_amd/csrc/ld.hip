@@ -2914,19 +2914,6 @@ size_t edges_lds(int nwaves) {
 
 size_t energy_lds(int columns) { return sizeof(float) * (6 * (size_t)columns + 10); }
 
-// Raise a kernel's dynamic LDS limit once per size (later launches, including those recorded
-// into a captured graph, issue nothing but the launch).
-template <typename K>
-void allow_lds(K kernel, size_t bytes) {
-    static size_t granted = 0;   // one counter per kernel instantiation
-    if (bytes > 32 * 1024 && bytes > granted) {
-        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess)
-            granted = bytes;
-        else
-            (void)hipGetLastError();
-    }
-}
-
 constexpr int kRegions = 18;
 
 // Byte offsets and sizes of the regions of one frame object's device allocation.
@@ -3053,7 +3040,7 @@ ld_status run_vdisp_fit(ld_frame f, const uint64_t* sid, const int64_t* fidx, do
     Dev& d = f->d;
     int in_lds;
     const size_t l2 = vdisp_fit_lds(d, &in_lds);
-    allow_lds(k_vdisp_fit, l2);
+    allow_lds<k_vdisp_fit>(l2);
     {
         ProfScope ps(f, 1, st);
         hipLaunchKernelGGL(k_vdisp_fit, dim3(f->active), dim3(vdisp_fit_threads(d)), l2, st, d, sid, fidx, beta_out,
@@ -3082,13 +3069,13 @@ ld_status run_edges(ld_frame f, const uint8_t* grey, int64_t gp, const void* dis
     const uint8_t* dp = static_cast<const uint8_t*>(disp);
     ProfScope ps(f, 2, st);
     if (d.fmt == LD_DISP_U8) {
-        allow_lds(k_edges<LD_DISP_U8>, lds);
+        allow_lds<k_edges<LD_DISP_U8>>(lds);
         hipLaunchKernelGGL(k_edges<LD_DISP_U8>, g3, dim3(nw * kWave), lds, st, d, grey, gp, dp, dpt, strip);
     } else if (d.fmt == LD_DISP_F32) {
-        allow_lds(k_edges<LD_DISP_F32>, lds);
+        allow_lds<k_edges<LD_DISP_F32>>(lds);
         hipLaunchKernelGGL(k_edges<LD_DISP_F32>, g3, dim3(nw * kWave), lds, st, d, grey, gp, dp, dpt, strip);
     } else {
-        allow_lds(k_edges<LD_DISP_U16Q4>, lds);
+        allow_lds<k_edges<LD_DISP_U16Q4>>(lds);
         hipLaunchKernelGGL(k_edges<LD_DISP_U16Q4>, g3, dim3(nw * kWave), lds, st, d, grey, gp, dp, dpt, strip);
     }
     return launch_ok();
@@ -3111,7 +3098,7 @@ ld_status run_vpx_dp(ld_frame f, const Dev& d, hipStream_t st) {
     const int cap = (int)std::min((px + 7) / 8 * 8, room(per_cu));
     const size_t l4 = fixed + sizeof(uint16_t) * (size_t)cap;
     ProfScope ps(f, 3, st);
-    allow_lds(k_vpx_fit, l4);
+    allow_lds<k_vpx_fit>(l4);
     hipLaunchKernelGGL(k_vpx_fit, dim3(f->active), dim3(nt), l4, st, d, cap);
     return launch_ok();
 }
@@ -3121,7 +3108,7 @@ ld_status run_vpx_ransac(ld_frame f, const uint64_t* sid, const int64_t* fidx, c
                          double* vp_out, hipStream_t st) {
     const Dev& d = f->d;
     const size_t l = sizeof(int) * 4 * (((size_t)d.H + 3) / 4 * 4) + sizeof(uint32_t) * ((d.H + 31) / 32);
-    allow_lds(k_vpx_ransac, l);
+    allow_lds<k_vpx_ransac>(l);
     ProfScope ps(f, 10, st);
     // (44 against 47 us for one 1242 x 375 frame, 80 against 99 for 256 of 1920 x 1080)
     const int nt = f->active <= 2 * kCUs ? kRansacThreadsFew : kRansacThreads;
@@ -3143,7 +3130,7 @@ void launch_energy(ld_frame f, const Dev& d, const uint8_t* mask, float* eout, h
     const size_t base = (energy_lds(NC * BT) + 15) / 16 * 16, rows = (size_t)d.H * (sizeof(double) * 2 + sizeof(int));
     const bool staged = base + rows <= (size_t)kMaxLds;
     const size_t l = staged ? base + rows : base;
-    allow_lds(k_energy<NC, NT, BT, PD>, l);
+    allow_lds<k_energy<NC, NT, BT, PD>>(l);
     hipLaunchKernelGGL((k_energy<NC, NT, BT, PD>), dim3(f->active), dim3(BT), l, st, d, mask, eout,
                        staged ? (int)(base / sizeof(float)) : 0);
 }
@@ -3235,7 +3222,6 @@ static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 namespace {
 
-constexpr int kMaxDevices = 64;
 std::mutex scratch_mu;
 char* scratch_ptr[kMaxDevices] = {};
 
@@ -3453,7 +3439,7 @@ ld_status ld_detect_pruned(ld_frame f, ld_cnn n, const uint8_t* grey, int64_t gr
     if (s == LD_OK) {
         ProfScope ps(f, 7, st);
         const size_t ls = sizeof(int) * 2 * (size_t)d.W2;
-        allow_lds(k_seed, ls);
+        allow_lds<k_seed>(ls);
         hipLaunchKernelGGL(k_seed, dim3(f->active), dim3(kBlock), ls, st, d, nb, c->delta_x, c->min_votes,
                            c->seed_ransac);
         s = launch_ok();
@@ -3464,7 +3450,7 @@ ld_status ld_detect_pruned(ld_frame f, ld_cnn n, const uint8_t* grey, int64_t gr
         const size_t lw = sizeof(int) * (256 + kWave + 3 * (size_t)d.H + 2) + cap;
         const int wave_bytes = (int)((lw + 15) / 16 * 16);
         const int fpw = std::max(1, std::min(4, kMaxLds / wave_bytes));   // frames per workgroup
-        allow_lds(k_vpx_window, (size_t)fpw * wave_bytes);
+        allow_lds<k_vpx_window>((size_t)fpw * wave_bytes);
         hipLaunchKernelGGL(k_vpx_window, dim3((f->active + fpw - 1) / fpw), dim3(kWave * fpw), (size_t)fpw * wave_bytes,
                            st, d, cap, wave_bytes, f->active);
         s = launch_ok();
@@ -3481,7 +3467,7 @@ ld_status ld_detect_pruned(ld_frame f, ld_cnn n, const uint8_t* grey, int64_t gr
     if (s == LD_OK && pruning) {
         ProfScope ps(f, 9, st);
         const size_t lm = sizeof(uint32_t) * nb * LDI_BAND_ROWS * (size_t)((d.W + 31) / 32) + (size_t)d.W2;
-        allow_lds(k_cand_mask, lm);
+        allow_lds<k_cand_mask>(lm);
         hipLaunchKernelGGL(k_cand_mask, dim3(f->active), dim3(kBlock), lm, st, d, nb, c->dilate);
         s = launch_ok();
     }

@@ -872,17 +872,6 @@ static_assert(kStageBytes <= sizeof(uint16_t) * kActElems, "the staged inputs li
 constexpr size_t kTrainLds =
     sizeof(uint16_t) * (kFeatElems + 2 * kActElems + kLR * kXW) + sizeof(float) * (1024 + 1024) + kStageBytes;
 
-template <typename K>
-void allow_lds(K kernel, size_t bytes) {
-    static size_t granted = 0;
-    if (bytes > granted) {
-        if (hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess)
-            granted = bytes;
-        else
-            (void)hipGetLastError();
-    }
-}
-
 int col_tiles(int W) { return (W + kCT - 1) / kCT; }
 
 }  // namespace
@@ -939,7 +928,7 @@ ld_status ldi_cnn_bits(ld_cnn n, ld_frame f, const uint8_t* grey, int64_t gp, co
     const int nb = n->cfg.n_bands;
     const double th = (double)n->cfg.theta;
     const float thr_logit = (float)std::log(th / (1.0 - th));
-    allow_lds(k_cnn_fwd, kFwdLds);
+    allow_lds<k_cnn_fwd>(kFwdLds);
     Net N{n->wpk, n->master};
     const int64_t units = (int64_t)col_tiles(V.W) * nb * V.active;
     hipLaunchKernelGGL(k_cnn_fwd, dim3((unsigned)((units + kFwdUnits - 1) / kFwdUnits)), dim3(kT), kFwdLds, st, V, N,
@@ -1161,7 +1150,7 @@ ld_status ld_cnn_train_step(ld_cnn n, ld_frame f, const uint8_t* grey, int64_t g
     const int64_t nwg = (int64_t)V.active * nb * nct;
     if (nwg > n->part_rows) return LD_E_INVAL;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
-    allow_lds(k_cnn_train, kTrainLds);
+    allow_lds<k_cnn_train>(kTrainLds);
     Net N{n->wpk, n->master};
     hipLaunchKernelGGL(k_cnn_train, dim3(nct, nb, V.active), dim3(kTrainT), kTrainLds, st, V, N, nb, grey, grey_pitch,
                        static_cast<const uint8_t*>(disp), disp_pitch, labels, pos_weight, inv_norm, n->part);

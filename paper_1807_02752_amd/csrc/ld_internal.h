@@ -8,6 +8,22 @@
 #include <stdint.h>
 
 #include "ld.h"
+#include "ld_launch.h"
+
+// Raises a kernel's dynamic LDS limit on the current GPU once per size (later launches,
+// including those recorded into a captured graph, issue nothing but the launch).
+template <auto Kernel>
+void allow_lds(size_t bytes) {
+    if (bytes <= 32 * 1024) return;
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) dev = -1;
+    raise_lds<Kernel>(dev, bytes, [&] {
+        const bool ok = hipFuncSetAttribute(reinterpret_cast<const void*>(Kernel),
+                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+        if (!ok) (void)hipGetLastError();
+        return ok;
+    });
+}
 
 // A roctx range named after an ABI call around its host part (argument checks and the
 // enqueueing of its kernels; the kernels themselves run later on the caller's stream), so a

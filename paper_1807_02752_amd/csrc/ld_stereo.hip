@@ -694,8 +694,7 @@ void launch_strips(const uint8_t* left, int64_t lp, const uint8_t* right, int64_
                    uint8_t* lf, uint8_t* rt, hipStream_t st) {
     using G = Strip<RHO, LP, E, T>;
     const size_t lds = G::lds(V.d_max);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_stereo_strip<RHO, LP, E, T>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    allow_lds<k_stereo_strip<RHO, LP, E, T>>(lds);
     const dim3 grid((V.W + G::kUse - 1) / G::kUse, 2, V.active);
     for (int v = V.H - 1 - RHO; v >= RHO; v -= T)
         hipLaunchKernelGGL((k_stereo_strip<RHO, LP, E, T>), grid, dim3(G::NT), lds, st, left, lp, right, rp, V.W, V.H,
@@ -727,8 +726,7 @@ void launch(const uint8_t* left, int64_t lp, const uint8_t* right, int64_t rp, c
         if (strips_fit<RHO, 4, 128, 8>(V, 2400)) return launch_strips<RHO, 4, 128, 8>(left, lp, right, rp, V, tau, lf, rt, st);
     }
     const size_t lds = stereo_lds(V.W, RHO);
-    (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k_stereo<RHO>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    allow_lds<k_stereo<RHO>>(lds);
     hipLaunchKernelGGL(k_stereo<RHO>, dim3(V.active), dim3(2 * kT), lds, st, left, lp, right, rp, V.W, V.H, V.nact,
                        V.active, V.d_max, tau, lf, rt);
 }

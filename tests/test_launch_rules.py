@@ -1,0 +1,67 @@
+"""What the host decides before a launch (csrc/ld_launch.h holds it without HIP types), compiled
+with g++ and run here."""
+import os
+import subprocess
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+def run_host(tmp_path, body):
+    """Lines that a program with `body` in its main prints."""
+    src, exe = tmp_path / "p.cpp", tmp_path / "p"
+    src.write_text('#include <cstdio>\n#include <thread>\n#include <vector>\n#include "ld_launch.h"\n' + body)
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-pthread", "-Wall", "-Werror", "-I",
+                           os.path.join(ROOT, "paper_1807_02752_amd", "csrc"), "-o", str(exe), str(src)])
+    return subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout.split("\n")[:-1]
+
+
+def test_lds_limit_is_kept_by_kernel_and_gpu(tmp_path):
+    # two instantiations of one template have the same type; a larger grant of the one, or on another
+    # GPU, must not stand for the other's, and a refused size is asked for again
+    out = run_host(tmp_path, r"""
+template <int N> void kernel(int) {}
+template <auto K> void ask(const char* name, int dev, size_t bytes, bool ok = true) {
+    bool called = false;
+    raise_lds<K>(dev, bytes, [&] { called = true; return ok; });
+    std::printf("%s %d %zu %d\n", name, dev, bytes, called ? 1 : 0);
+}
+int main() {
+    ask<kernel<1>>("a", 0, 100000);
+    ask<kernel<2>>("b", 0, 71000);
+    ask<kernel<1>>("a", 0, 71000);
+    ask<kernel<1>>("a", 1, 71000);
+    ask<kernel<2>>("b", 0, 90000, false);
+    ask<kernel<2>>("b", 0, 90000);
+    ask<kernel<2>>("b", 0, 90000);
+    ask<kernel<2>>("b", 64, 1);
+    ask<kernel<2>>("b", 64, 1);
+    ask<kernel<2>>("b", -1, 1);
+}
+""")
+    assert out == ["a 0 100000 1", "b 0 71000 1", "a 0 71000 0", "a 1 71000 1", "b 0 90000 1", "b 0 90000 1",
+                   "b 0 90000 0", "b 64 1 1", "b 64 1 1", "b -1 1 1"]
+
+
+def test_lds_limit_never_falls_between_threads(tmp_path):
+    # the last size set is the largest one, whatever order the threads come in
+    out = run_host(tmp_path, r"""
+void kernel(int) {}
+int main() {
+    size_t last = 0;
+    int falls = 0;
+    std::vector<std::thread> ts;
+    for (int t = 0; t < 8; ++t)
+        ts.emplace_back([&, t] {
+            for (size_t i = 0; i < 2000; ++i) {
+                const size_t n = 1 + (i * 7919 + t * 104729) % 160000;
+                raise_lds<kernel>(0, n, [&] { falls += n < last; last = n; return true; });
+            }
+        });
+    for (auto& t : ts) t.join();
+    size_t most = 0;
+    for (size_t t = 0; t < 8; ++t)
+        for (size_t i = 0; i < 2000; ++i) most = std::max(most, 1 + (i * 7919 + t * 104729) % 160000);
+    std::printf("%d %d\n", falls, last == most);
+}
+""")
+    assert out == ["0 1"]
