@@ -1231,15 +1231,20 @@ __device__ void vpx_fit_tail(Dev& d, int b, FrameInfo fi, int* PX, int* PY, int*
 // What bounds it: one frame alone, a row's chain of barrier, seam and count reads (about 300
 // cycles) and its 200 operations; many frames, the operations issued, about 13 a column.  Ten
 // columns a thread make four waves of 1242 wide frames, one a SIMD; 4, 6, 8, 12 and 16 were
-// slower alone and with 1024 frames.  1242 x 375, one frame 218 -> 133 us, 1024 frames 418 -> 340
-// us; 1920 x 1080, one frame 660 -> 480 us, 256 frames 705 -> 518 us.
+// slower alone and with 1024 frames.
+//
+// Registers for seven waves a SIMD (the backtrace walk has two chunks in flight for that): at 79
+// VGPRs and 106 SGPRs the fourth five-wave frame of a CU found no place in half of the processes,
+// and 1024 frames of 1242 x 375 took 290 us in one and 400 to 440 in the next; now 300 in each.
+// 1242 x 375, one frame 218 -> 137 us, 1024 frames 410 -> 300 us; 1920 x 1080, one frame 660 -> 480
+// us, 256 frames 705 -> 518 us.
 constexpr int kFitCols = 10;         // columns a thread
 constexpr int kSeam = 8;             // LDS words of one end of a wave's row (five used)
 constexpr int kNoVote = 0xFFFF;      // a staged edge without a vote column
 
 __host__ __device__ constexpr int vpx_fit_waves(int W2) { return (W2 + kFitCols * kWave - 1) / (kFitCols * kWave); }
 
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) void k_vpx_fit(Dev d, int stage_cap) {
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void k_vpx_fit(Dev d, int stage_cap) {
     constexpr int K = kFitCols;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     __shared__ int64_t rv[kMaxWaves + 1];
@@ -1530,7 +1535,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(5))) void 
     // moves at most 5 columns a row, so the words centred on a chunk's start column, 32 K to
     // either side, cover it up to the end of the last of them.
     if (t < kWave) {
-        constexpr int kAhead = 3;
+        constexpr int kAhead = 2;
         static_assert(5 * (kAhead + 1) * kFitWalk + K <= 32 * K, "a chunk's words cover the path");
         const int l = t;
         int c = __builtin_amdgcn_readfirstlane(bi);
