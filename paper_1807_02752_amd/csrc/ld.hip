@@ -1236,11 +1236,12 @@ __device__ void vpx_fit_tail(Dev& d, int b, FrameInfo fi, int* PX, int* PY, int*
 // Registers for seven waves a SIMD (the backtrace walk has two chunks in flight for that): at 79
 // VGPRs and 106 SGPRs the fourth five-wave frame of a CU found no place in half of the processes,
 // and 1024 frames of 1242 x 375 took 290 us in one and 400 to 440 in the next; now 300 in each.
-// 1242 x 375, one frame 218 -> 137 us, 1024 frames 410 -> 300 us; 1920 x 1080, one frame 660 -> 480
+// 1242 x 375, one frame 218 -> 138 us, 1024 frames 410 -> 300 us; 1920 x 1080, one frame 660 -> 480
 // us, 256 frames 705 -> 518 us.
 constexpr int kFitCols = 10;         // columns a thread
 constexpr int kSeam = 8;             // LDS words of one end of a wave's row (five used)
 constexpr int kNoVote = 0xFFFF;      // a staged edge without a vote column
+constexpr int kSharedVotes = 600;    // weighted edges a road row, times the waves, past which all vote
 
 __host__ __device__ constexpr int vpx_fit_waves(int W2) { return (W2 + kFitCols * kWave - 1) / (kFitCols * kWave); }
 
@@ -1292,8 +1293,17 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
         if (lane == 0) roff[0] = 0;
     }
     __syncthreads();
+    // A frame with many edges would wait for the one wave that keeps the counts, which moves each vote
+    // twice (once for either parity) and reads what is not staged from memory: there all the waves
+    // share the votes of one row of counts, with a second barrier a row, and nothing is staged.  An
+    // edge that is not staged counts as five, and the more waves share the sooner it pays (us,
+    // one wave and shared, by edges a row and of them not staged; 1242 wide: 55, 0: 265, 301;
+    // 111, 0: 342, 321; 181, 0: 433, 341; 1024 frames 28, 4: 532, 538; 55, 31: 721, 570; 181, 156:
+    // 1561, 677; 320 wide: 287, 0: 175, 185; 1024 frames 287, 108: 329, 289; a 1920 x 540 frame of
+    // noise, 8900, 1680).
+    const bool shared_votes = __builtin_expect((roff[R] + 4 * max(roff[R] - stage_cap, 0)) * nw > kSharedVotes * R, 0);
     int nv = 0;   // votes that landed in a column
-    for (int r0 = wave * kStageRows; r0 < R; r0 += (nw + 1) * kStageRows) {
+    for (int r0 = wave * kStageRows; r0 < R && !shared_votes; r0 += (nw + 1) * kStageRows) {
         const int mine = roff[min(r0 + lane, R)];              // lane l: the offset of row r0 + l
 #pragma unroll
         for (int j = 0; j < kStageRows; ++j) {
@@ -1317,25 +1327,55 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
     auto vote = [&](int* to, int bin, int x) {
         if (bin != kNoVote) atomicAdd(&to[bin], 16 * x);
     };
-    // the votes of road rows r0 .. r1, from the lane's i-th edge of each row on
+    // votes of edges i, i + 64, ... < n of a run, four of them read at a time
+    auto vote_run = [&](int* to, auto bin_at, int i, int n, int x) {
+        for (; i < n; i += 4 * kWave) {
+            int bin[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bin[q] = i + q * kWave < n ? bin_at(i + q * kWave) : kNoVote;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) vote(to, bin[q], x);
+        }
+    };
+    // a road row's edge in memory
+    auto edge_of = [&](int r, int i) -> int {
+        const int e = fedges[(int64_t)(v_h + r) * W + i].bin;
+        return e >= 0 ? e : kNoVote;
+    };
+    // the votes of road rows r0 .. r1
     auto vote_rows = [&](int* to, int r0, int r1, int x) {
         for (int r = r0; r <= r1; ++r) {
             const int o = roff[r], n = roff[r + 1] - o;
-            const bool fits = o + n <= stage_cap;
-            for (int i = lane; i < n; i += kWave) {
-                int bin = fits ? wb[o + i] : kNoVote;
-                if (!fits) {
-                    const int e = fedges[(int64_t)(v_h + r) * W + i].bin;
-                    bin = e >= 0 ? e : kNoVote;
-                }
-                vote(to, bin, x);
-            }
+            if (o + n <= stage_cap)
+                for (int i = lane; i < n; i += kWave) vote(to, wb[o + i], x);
+            else vote_run(to, [&](int i) { return edge_of(r, i); }, lane, n, x);
         }
     };
     // the bands of the two lowest rows (road rows R - 1 and R - 2)
-    for (int r = max(R - 1 - chi, 0) + wave; r < R; r += nw + 1) vote_rows(hist + (v_max & 1) * WP, r, r, 1);
-    for (int r = max(R - 2 - chi, 0) + wave; r <= min(R - 2 + chi, R - 1); r += nw + 1)
+    for (int r = max(R - 1 - chi, 0) + wave; r < R && !shared_votes; r += nw + 1) vote_rows(hist + (v_max & 1) * WP, r, r, 1);
+    for (int r = max(R - 2 - chi, 0) + wave; r <= min(R - 2 + chi, R - 1) && !shared_votes; r += nw + 1)
         vote_rows(hist + ((v_max & 1) ^ 1) * WP, r, r, 1);
+    // shared votes: from the band of road row r + 1 to that of row r, one row enters and one leaves
+    // (rows outside the road hold nothing), four edges a thread of both in flight
+    auto move_band = [&](int ra, int rl) {
+        const int na = ra >= 0 ? roff[ra + 1] - roff[ra] : 0, nl = rl < R ? roff[rl + 1] - roff[rl] : 0;
+        for (int i = t; i < max(na, nl); i += 4 * nt) {
+            int a[4], l[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                a[q] = i + q * nt < na ? edge_of(ra, i + q * nt) : kNoVote;
+                l[q] = i + q * nt < nl ? edge_of(rl, i + q * nt) : kNoVote;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                vote(hist, a[q], 1);
+                vote(hist, l[q], -1);
+                nv += a[q] != kNoVote ? 1 : 0;
+            }
+        }
+    };
+    if (__builtin_expect(shared_votes, 0))
+        for (int r = max(R - 1 - chi, 0); r < R; ++r) move_band(r, R);
     // backtrace: the ranks of a thread's columns in two words, at the start of the q buffer's row
     // of W words (k_energy and k_m1 write that buffer later)
     const int L = (W2 + K - 1) / K;                            // threads with a column
@@ -1343,7 +1383,14 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
     const int64_t pitch = W / 2;
     const int c0 = t * K;
     int S[K];
-    if (wave == nw) {
+    if (__builtin_expect(wave == nw && shared_votes, 0)) {
+        __syncthreads();                                       // row v_max
+        for (int r = R - 2; r >= 0; --r) {
+            __syncthreads();
+            move_band(r - chi, r + chi + 1);
+            __syncthreads();
+        }
+    } else if (wave == nw) {
         // While row v is worked on from the counts of its parity, those of the other parity go
         // from the band of row v + 1 to that of v - 1: rows v - 1 - chi and v - chi enter, v + chi and
         // v + 1 + chi leave (with chi = 0 one each), two runs of staged edges.  Lane l holds
@@ -1436,7 +1483,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
         // consecutive entries share their middle three.  Instantiated for the full window
         // (tau_max = 5) and for a narrower one, and for the wave that holds the last column, whose
         // columns past it keep the padding value.
-        auto row = [&](auto full, auto last, int par, int v) __attribute__((always_inline)) {
+        auto row = [&](auto full, auto last, auto shared, int par, int v) __attribute__((always_inline)) {
             constexpr bool kFull = decltype(full)::value, kLast = decltype(last)::value;
             int w[K + 10];
             int h[K];
@@ -1444,7 +1491,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
                 const int* sg = get0 + par * seam_par;
                 const int4 g4 = *reinterpret_cast<const int4*>(sg);
                 const int g[5] = {g4.x, g4.y, g4.z, g4.w, sg[4]};
-                counts(par, h);
+                counts(decltype(shared)::value ? 0 : par, h);
 #pragma unroll
                 for (int j = 0; j < 5; ++j) {
                     w[j] = __builtin_amdgcn_update_dpp(g[j], S[K - 5 + j], 0x138, 0xF, 0xF, false);      // lane - 1
@@ -1496,30 +1543,43 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
             if (!kLast || c0 < W2) (back + v * pitch)[t] = make_uint2(word[0], word[1]);
             put_seams(par ^ 1);
         };
-        auto rows = [&](auto full, auto last) __attribute__((always_inline)) {
+        auto rows = [&](auto full, auto last, auto shared) __attribute__((always_inline)) {
+            constexpr bool kShared = decltype(shared)::value;
             __syncthreads();                                   // row v_max: its counts alone
             int h[K];
-            counts(v_max & 1, h);
+            counts(kShared ? 0 : v_max & 1, h);
 #pragma unroll
             for (int k = 0; k < K; ++k) S[k] = c0 + k < W2 ? -h[k] : kBig;
             put_seams((v_max & 1) ^ 1);
             int v = v_max - 1;
+            if constexpr (kShared) {
+                for (; v >= v_h; --v) {
+                    __syncthreads();                           // every wave has read the counts
+                    move_band(v - v_h - chi, v - v_h + chi + 1);
+                    __syncthreads();
+                    row(full, last, shared, v & 1, v);
+                }
+                return;
+            }
             if (v >= v_h && (v & 1) == 0) {
                 __syncthreads();
-                row(full, last, 0, v);
+                row(full, last, shared, 0, v);
                 --v;
             }
             for (; v >= v_h; v -= 2) {                         // v is odd here
                 __syncthreads();
-                row(full, last, 1, v);
+                row(full, last, shared, 1, v);
                 if (v - 1 < v_h) break;
                 __syncthreads();
-                row(full, last, 0, v - 1);
+                row(full, last, shared, 0, v - 1);
             }
         };
-        if (tau_max != 5) rows(std::false_type{}, std::true_type{});
-        else if ((wave + 1) * K * kWave > W2) rows(std::true_type{}, std::true_type{});
-        else rows(std::true_type{}, std::false_type{});
+        // (the common forms first in the code: behind the shared ones they took 3% longer)
+        if (!shared_votes && tau_max == 5 && (wave + 1) * K * kWave <= W2) rows(std::true_type{}, std::false_type{}, std::false_type{});
+        else if (!shared_votes && tau_max == 5) rows(std::true_type{}, std::true_type{}, std::false_type{});
+        else if (!shared_votes) rows(std::false_type{}, std::true_type{}, std::false_type{});
+        else if (tau_max == 5) rows(std::true_type{}, std::true_type{}, std::true_type{});
+        else rows(std::false_type{}, std::true_type{}, std::true_type{});
     }
     int64_t bvv = INT64_MAX;
     int bi = 0x7fffffff;

@@ -131,3 +131,52 @@ def test_edges_by_frame_count(w, h, n):
     out.pop("curves", None)     # FP32, far outside the image for a poor model
     for b in sorted({0, n // 2, n - 1}):
         compare_frame(out, b, g[b], d[b], 48)
+
+
+def _noise(w, h, d_max, every, seed=0):
+    """A noise image over a plane: every pixel of one in `every` groups of eight columns."""
+    g, d = synth.degenerate("random", w, h, synth.FMT_U8, 32, seed=seed)
+    d[:] = np.arange(h)[:, None] * d_max // h
+    g[:, (np.arange(w) // 8) % every != 0] = 90
+    return g, d
+
+
+@pytest.mark.parametrize("w,h,n,every,kw", [
+    # rows of many edges, whose votes all the waves share: none, some and most of them staged; a few
+    # more than a thread each, and several; bands of one row and past the road; narrower windows
+    (641, 120, 2, 1, {}), (641, 121, 2, 2, {"chi": 0}), (1000, 90, 2, 1, {"chi": 400}), (1242, 60, 1, 2, {"tau_x_max": 3}),
+    (641, 120, 600, 4, {}), (1242, 130, 2, 3, {"chi": 1}), (1930, 64, 1, 1, {"tau_x_max": 0}), (320, 96, 1030, 1, {}),
+])
+def test_vpx_votes_of_dense_rows(w, h, n, every, kw):
+    import oracle
+    from paper_1807_02752_amd import ld
+    pair = [_noise(w, h, 120, every, s) for s in range(2)]
+    g = np.stack([pair[i % 2][0] for i in range(n)])
+    d = np.stack([pair[i % 2][1] for i in range(n)])
+    out = run_gpu(g, d, 120, params=ld.params_default(**kw))
+    out.pop("curves", None)     # FP32, far outside the image for a poor model
+    for b in sorted({0, n // 2, n - 1}):
+        compare_frame(out, b, g[b], d[b], 120, params=oracle.default_params(**kw))
+
+
+def test_vpx_time_of_dense_rows():
+    # with one wave keeping the counts a frame of noise took fifteen times as long as one with a
+    # sixteenth of its edges, with the votes shared three times
+    import torch
+    from paper_1807_02752_amd import ld
+    us = []
+    for every in (1, 16):
+        g, d = _noise(1920, 540, 200, every)
+        det = ld.Detector(1920, 540, 1, ld.LD_DISP_U8, 200)
+        g, d = torch.from_numpy(g[None]).cuda(), torch.from_numpy(d[None]).cuda()
+        det.vdisp(d)
+        det.vp_ransac(g, d)
+        times = []
+        for _ in range(5):
+            det.profile(True)
+            det.vp_ransac(g, d)
+            det.sync()
+            times.append(det.kernel_times()["k_vpx_fit"][0] * 1e3)
+        us.append(min(times))
+        det.close()
+    assert us[0] < 6 * us[1], us
