@@ -45,8 +45,6 @@ struct FrameInfo {
 
 constexpr int kMaxRounds = 64;
 constexpr int kBig = 0x3FFFFFFF;
-constexpr int kCUs = 256;              // compute units of one GPU
-constexpr int kMaxLds = 160 * 1024;   // LDS bytes a workgroup may hold on gfx950
 
 // Device view of a frame object: sizes, parameters and the scratch carried between steps.
 struct Dev {

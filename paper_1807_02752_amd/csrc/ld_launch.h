@@ -1,11 +1,15 @@
 // ld_launch.h -- what the host decides before a launch, without HIP types: the dynamic LDS that
-// a kernel has been granted.  Not part of the C ABI.
+// a kernel has been granted, and which form of a kernel a launch takes.  Not part of the C ABI.
 #pragma once
 
+#include <algorithm>
 #include <atomic>
 #include <cstddef>
+#include <cstdint>
 #include <mutex>
 
+constexpr int kCUs = 256;              // compute units of one GPU
+constexpr int kMaxLds = 160 * 1024;    // LDS bytes a workgroup may hold on gfx950
 constexpr int kMaxDevices = 64;
 
 // The dynamic LDS granted to one kernel on each GPU.
@@ -29,4 +33,47 @@ void raise_lds(int device, size_t bytes, Set set) {
     if (bytes <= have.load(std::memory_order_acquire)) return;
     std::lock_guard<std::mutex> lock(grants.mu);
     if (bytes > have.load(std::memory_order_relaxed) && set()) have.store(bytes, std::memory_order_release);
+}
+
+// LDS of a stereo strip of E columns and T rows
+inline size_t stereo_strip_lds(int rho, int E, int T, int d_max) {
+    const size_t rows = (size_t)T + 2 * rho, own = (size_t)(E + 2 * rho + 3 + 8) / 4;
+    const size_t other = (size_t)(E + 255 + 2 * rho + 3 + 8) / 4, wb = (size_t)E + d_max, cols = E + wb + 4 * rho;
+    return 4 * rows * (own + other) + (size_t)T * (wb + E) * 12 + 2 * cols * 8 + 2 * 4 * (size_t)(E + 2) + 64;
+}
+
+// The form that a launch of the stereo maps takes: strips of eight or four lanes a pixel, of 16 or 8
+// rows, or one workgroup that sweeps a pair (kSweep).
+//
+// The sweep's time hardly depends on the number of pairs up to one a CU; the strips spread a pair over
+// the chip but work on their halo again.  Eight lanes a pixel have the shortest row and the most
+// halo (30 of 64 columns), so they are taken while all workgroups of a row block run at once, four
+// after that, and blocks of eight rows (two or three workgroups fit a CU, less halo) from there on, until
+// their work passes the sweep's.  ms for 1, 8, 16, 32, 96 and 128 pairs of 1242 x 375:
+//   8 lanes, 64 columns, 16 rows    0.68  1.35  2.08
+//   4 lanes, 128 columns, 16 rows   0.84  0.86  1.63  3.10
+//   4 lanes, 128 columns, 8 rows    0.91  0.95  1.23  1.58  3.92  4.89
+//   a pair a workgroup              4.64  4.68  4.74  4.80  4.82  4.83
+// Where the last two meet is a matter of the width: a launch of the strips costs by its workgroups (0.55
+// us each for a round of 15 launches), a sweep by its columns and by the rounds of 256 pairs
+// (ms for 120 rows, 8-row strips and sweep: 64 wide, 512 pairs 0.52, 0.87; 160 wide, 160 and 256 pairs
+// 0.41, 0.46 and 0.55, 0.46; 320 wide, 128 and 192 pairs 0.42, 0.56 and 0.64, 0.56; 640 wide, 96 and
+// 160 pairs 0.64, 0.76 and 0.96, 0.77; 960 wide, 96 and 160 pairs 1.04, 1.28 and 1.62, 1.30; 1920
+// wide, 96 and 160 pairs 1.80, 2.45 and 2.96, 2.47), so the limit is one on workgroups that grows with
+// the width, three quarters of it without a propagation bound, where the sweep has fewer candidates a
+// pixel to wait for (96 pairs of 1242 columns: 1.07, 0.92).
+enum class StereoForm { kStrip8, kStrip4, kStrip4Short, kSweep };
+
+inline StereoForm stereo_form(int W, int H, int rho, int d_max, int tau, int64_t pairs) {
+    if (W <= 2 * rho || W < 4 || H <= 2 * rho) return StereoForm::kSweep;   // (no block, or no word a row)
+    auto fits = [&](int E, int T, int64_t most) {
+        const int use = E - 2 * (T - 1);
+        return stereo_strip_lds(rho, E, T, d_max) <= (size_t)kMaxLds &&
+               (int64_t)((W + use - 1) / use) * 2 * pairs <= most;
+    };
+    if (fits(64, 16, kCUs)) return StereoForm::kStrip8;
+    if (fits(128, 16, kCUs)) return StereoForm::kStrip4;
+    const int64_t most = std::max(960, 2 * W) * ((pairs + kCUs - 1) / kCUs);
+    if (fits(128, 8, tau == 0 ? most * 3 / 4 : most)) return StereoForm::kStrip4Short;
+    return StereoForm::kSweep;
 }

@@ -34,7 +34,7 @@
 // lanes of its wave, so such pixels are queued: many (the first row) are taken one a lane, few
 // one a wave with a candidate per lane and a reduction over the wave.  The propagation makes
 // the rows of a frame sequential; frames are independent workgroups.  Launches of few frames
-// (up to about 100 of 1242 x 375) take the same maps in strips of columns and blocks of rows,
+// (stereo_form; up to 112 of 1242 x 375) take the same maps in strips of columns and blocks of rows,
 // k_stereo_strip, a launch per block of rows (1 pair: 5.15 -> 0.68 ms, 32: 5.3 -> 1.6 ms).
 #include <hip/hip_runtime.h>
 
@@ -423,10 +423,6 @@ struct Strip {
     static constexpr int kA = (E + 2 * RHO + 3 + 8) / 4;             // words of a row of the own image
     static constexpr int kB = (E + 255 + 2 * RHO + 3 + 8) / 4;       // and of the other one
     static_assert(kUse > 0 && T % 2 == 0, "columns left after the halo; pairs of words aligned behind T rows");
-    static size_t lds(int d_max) {
-        const size_t wb = (size_t)E + d_max, cols = 2 * (size_t)E + d_max + 4 * RHO;
-        return 4 * (size_t)kRows * (kA + kB) + (size_t)T * (wb * 12 + E * 12) + 2 * cols * 8 + 2 * 4 * (size_t)(E + 2) + 64;
-    }
 };
 
 template <int RHO, int LP, int E, int T>
@@ -693,7 +689,7 @@ template <int RHO, int LP, int E, int T>
 void launch_strips(const uint8_t* left, int64_t lp, const uint8_t* right, int64_t rp, const ldi_frame_view& V, int tau,
                    uint8_t* lf, uint8_t* rt, hipStream_t st) {
     using G = Strip<RHO, LP, E, T>;
-    const size_t lds = G::lds(V.d_max);
+    const size_t lds = stereo_strip_lds(RHO, E, T, V.d_max);
     allow_lds<k_stereo_strip<RHO, LP, E, T>>(lds);
     const dim3 grid((V.W + G::kUse - 1) / G::kUse, 2, V.active);
     for (int v = V.H - 1 - RHO; v >= RHO; v -= T)
@@ -701,29 +697,14 @@ void launch_strips(const uint8_t* left, int64_t lp, const uint8_t* right, int64_
                            V.nact, V.active, V.d_max, tau, lf, rt, v);
 }
 
-// Which form a launch takes.  A frame's sweep is one workgroup, 4.6 ms for a 1242 x 375 pair
-// however few there are; the strips spread a pair over the chip but work on their halo again.
-// Eight lanes a pixel have the shortest row and the most halo (30 of 64 columns), so they are
-// taken while all workgroups of a row block run at once, four after that, and blocks of eight rows
-// (two workgroups fit a CU, less halo) from there on (ms for 1, 8, 16, 32, 96 and 128 pairs):
-//   8 lanes, 64 columns, 16 rows    0.68  1.35  2.08
-//   4 lanes, 128 columns, 16 rows   0.84  0.86  1.63  3.10
-//   4 lanes, 128 columns, 8 rows    0.91  0.95  1.23  1.58  3.92  4.89
-//   a frame a workgroup             4.64  4.68  4.74  4.80  4.82  4.83
-// (two lanes a pixel were within 5% of the third row or behind it, one lane a pixel behind by half.)
-template <int RHO, int LP, int E, int T>
-bool strips_fit(const ldi_frame_view& V, int64_t most) {
-    using G = Strip<RHO, LP, E, T>;
-    return G::lds(V.d_max) <= 160 * 1024 && (int64_t)((V.W + G::kUse - 1) / G::kUse) * 2 * V.active <= most;
-}
-
 template <int RHO>
 void launch(const uint8_t* left, int64_t lp, const uint8_t* right, int64_t rp, const ldi_frame_view& V, int tau,
             uint8_t* lf, uint8_t* rt, hipStream_t st) {
-    if (V.W > 2 * RHO && V.W >= 4 && V.H > 2 * RHO) {   // (a block fits, and rows hold a word)
-        if (strips_fit<RHO, 8, 64, 16>(V, 256)) return launch_strips<RHO, 8, 64, 16>(left, lp, right, rp, V, tau, lf, rt, st);
-        if (strips_fit<RHO, 4, 128, 16>(V, 256)) return launch_strips<RHO, 4, 128, 16>(left, lp, right, rp, V, tau, lf, rt, st);
-        if (strips_fit<RHO, 4, 128, 8>(V, 2400)) return launch_strips<RHO, 4, 128, 8>(left, lp, right, rp, V, tau, lf, rt, st);
+    switch (stereo_form(V.W, V.H, RHO, V.d_max, tau, V.active)) {
+        case StereoForm::kStrip8: return launch_strips<RHO, 8, 64, 16>(left, lp, right, rp, V, tau, lf, rt, st);
+        case StereoForm::kStrip4: return launch_strips<RHO, 4, 128, 16>(left, lp, right, rp, V, tau, lf, rt, st);
+        case StereoForm::kStrip4Short: return launch_strips<RHO, 4, 128, 8>(left, lp, right, rp, V, tau, lf, rt, st);
+        case StereoForm::kSweep: break;
     }
     const size_t lds = stereo_lds(V.W, RHO);
     allow_lds<k_stereo<RHO>>(lds);

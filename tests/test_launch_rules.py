@@ -9,7 +9,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 def run_host(tmp_path, body):
     """Lines that a program with `body` in its main prints."""
     src, exe = tmp_path / "p.cpp", tmp_path / "p"
-    src.write_text('#include <cstdio>\n#include <thread>\n#include <vector>\n#include "ld_launch.h"\n' + body)
+    src.write_text('#include <algorithm>\n#include <cstdio>\n#include <thread>\n#include <vector>\n#include "ld_launch.h"\n' + body)
     subprocess.check_call(["g++", "-std=c++17", "-O1", "-pthread", "-Wall", "-Werror", "-I",
                            os.path.join(ROOT, "paper_1807_02752_amd", "csrc"), "-o", str(exe), str(src)])
     return subprocess.run([str(exe)], check=True, capture_output=True, text=True, timeout=60).stdout.split("\n")[:-1]
@@ -65,3 +65,40 @@ int main() {
 }
 """)
     assert out == ["0 1"]
+
+
+# (width, block radius, d_max, propagation bound, pairs) and the form that was the fastest or within a few
+# percent of it: strips of eight lanes (0), of four with 16 rows (1) or 8 (2), a pair a workgroup (3)
+STEREO = [
+    (64, 3, 48, 1, 1, 0), (64, 3, 48, 1, 64, 0), (64, 3, 48, 1, 96, 1), (64, 3, 48, 1, 128, 1), (64, 3, 48, 1, 256, 2), (64, 3, 48, 1, 512, 2),
+    (160, 3, 48, 1, 192, 2), (160, 3, 48, 1, 256, 3), (160, 3, 48, 1, 384, 2), (160, 3, 48, 1, 512, 3),
+    (320, 3, 64, 1, 128, 2), (320, 3, 64, 1, 192, 3), (320, 3, 64, 1, 400, 3), (320, 1, 64, 1, 192, 3), (320, 5, 64, 1, 192, 3),
+    (640, 3, 64, 1, 96, 2), (640, 3, 64, 1, 160, 3), (640, 3, 64, 1, 192, 3),
+    (1242, 3, 128, 1, 1, 0), (1242, 3, 128, 1, 8, 1), (1242, 3, 128, 1, 32, 2), (1242, 3, 128, 1, 109, 2), (1242, 3, 128, 1, 128, 3),
+    (1242, 3, 128, 0, 64, 2), (1242, 3, 128, 0, 96, 3), (1242, 3, 255, 1, 64, 2), (1242, 3, 128, 1, 512, 3),
+    (1920, 3, 128, 1, 96, 2), (1920, 3, 128, 1, 160, 3), (2048, 3, 128, 1, 96, 2), (2048, 3, 128, 1, 256, 3),
+    (6, 3, 48, 1, 1, 3), (3, 1, 48, 1, 1, 3), (7, 3, 48, 1, 1, 0),
+]
+
+
+def test_stereo_form_by_width_and_pairs(tmp_path):
+    # strips up to 2400 workgroups whatever the width made 192 to 400 pairs of 320 columns and 128 to 200
+    # of 640 slower than the sweep
+    calls = "".join(f"std::printf(\"%d\\n\", (int)stereo_form({w}, 60, {rho}, {dm}, {tau}, {n}));\n" for w, rho, dm, tau, n, _ in STEREO)
+    out = run_host(tmp_path, "int main() {\n" + calls + "std::printf(\"%d\\n\", (int)stereo_form(64, 6, 3, 48, 1, 1));\n}\n")
+    assert [(c[:-1], int(o)) for c, o in zip(STEREO, out)] == [(c[:-1], c[-1]) for c in STEREO]
+    assert out[-1] == "3"
+
+
+def test_stereo_strips_fit_lds(tmp_path):
+    # whatever form is taken fits, and no form is refused for its size at the largest disparities
+    out = run_host(tmp_path, r"""
+int main() {
+    size_t most = 0;
+    for (int rho = 1; rho <= 5; ++rho)
+        for (int E : {64, 128})
+            for (int T : {8, 16}) most = std::max(most, stereo_strip_lds(rho, E, T, 255));
+    std::printf("%d\n", most <= (size_t)kMaxLds);
+}
+""")
+    assert out == ["1"]
