@@ -167,3 +167,31 @@ def test_sweep_forms(rho, w, h, n, d_max, tau):
                       d_max, rho=rho, tau=tau)
     for i in sorted({0, 1, n - 2, n - 1} & set(range(n))):
         _check(views[i % 2][0][None], views[i % 2][1][None], d_max, [g[i:i + 1] for g in got], rho=rho, tau=tau)
+
+
+@pytest.mark.parametrize("rho,w,h,n,d_max,tau", [
+    # a workgroup a pair: enough pairs for every block size and bound, odd widths, one column pass and
+    # more, the largest disparity, and flat bands below which few pixels of a row (up to 256) or many
+    # search the full range
+    (1, 165, 23, 256, 40, 0), (2, 171, 25, 256, 64, 1), (3, 163, 30, 255, 255, 1), (4, 301, 33, 205, 90, 2),
+    (5, 325, 38, 203, 128, 1), (3, 641, 33, 130, 60, 1), (1, 700, 27, 118, 255, 3), (5, 1027, 36, 125, 48, 0),
+])
+def test_sweep_of_many_pairs(rho, w, h, n, d_max, tau):
+    rng = np.random.default_rng(77 * rho + w)
+    views = []
+    for k in range(2):
+        wide = rng.integers(0, 256, size=(h, w + 24)).astype(np.uint8)
+        shift = np.minimum(2 + np.arange(h) // 4 + 3 * k, 20)
+        left = wide[:, :w].copy()
+        right = np.stack([wide[v, shift[v]:shift[v] + w] for v in range(h)])
+        band = slice(h // 2 - rho, h // 2 + rho + 1)          # a row without a match above it
+        part = slice(0, w if k == 0 else w // 4)
+        left[band, part] = 77
+        right[band, part] = 77
+        left[h - rho - 3] = 50                                # an equal row: equal costs side by side
+        right[h - rho - 3] = 50
+        views.append((left, np.ascontiguousarray(right)))
+    got = _stereo_gpu(np.stack([views[i % 2][0] for i in range(n)]), np.stack([views[i % 2][1] for i in range(n)]),
+                      d_max, rho=rho, tau=tau)
+    for i in sorted({0, 1, n - 2, n - 1}):
+        _check(views[i % 2][0][None], views[i % 2][1][None], d_max, [g[i:i + 1] for g in got], rho=rho, tau=tau)
