@@ -601,7 +601,9 @@ __host__ __device__ __forceinline__ int vdisp_seam_words(int waves) { return (wa
 // shifts, and a wave needs
 // nothing but the eight topmost rows of the wave below it, before each step: those go
 // through LDS a chunk of steps at a time, and wave w works on a chunk one turn after wave w + 1 did,
-// so a turn of kVdSteps steps has one barrier.  The keys are packed: the key of jump tau is
+// so a turn of kVdSteps steps has one barrier.  Where the waves' turns to fill and drain that would
+// outlast the steps (many rows, few disparities), LOCK has all waves take the same step instead,
+// with a barrier a step.  The keys are packed: the key of jump tau is
 // (E(v + tau) + lambda tau) << 4 | tau; the minimum is the smallest cost, and among equal
 // costs the smallest tau (the strict-< scan over tau = 0, 1, ...).  Rows past H - 1 hold the
 // padding key.  The votes of the chunk after this one are loaded ahead; bw is the
@@ -611,7 +613,7 @@ __host__ __device__ __forceinline__ int vdisp_seam_words(int waves) { return (wa
 // Bound: a wave's issue, about 45 instructions a step, and their chain.  A barrier and nine LDS
 // reads a row a step took 0.50 us a step at 375 rows and 0.70 at 1080; this takes 0.13 and 0.25
 // (the boundary rows of a step are read a step ahead).
-template <int TM, int R>
+template <int TM, int R, bool LOCK>
 __device__ __forceinline__ void vdisp_dp(const int32_t* myT, int Hm, int H, int d_max, int lam, int tau_max, int nwdp,
                                          uint32_t* bw, int* seam, int* E0) {
     const int t = threadIdx.x, lane = lane_id(), wave = t / kWave, nt = blockDim.x;
@@ -638,20 +640,46 @@ __device__ __forceinline__ void vdisp_dp(const int32_t* myT, int Hm, int H, int 
         load(0);
     }
     __syncthreads();
-    for (int turn = 0; turn < chunks + nwdp - 1; ++turn) {
+    // the votes and backtraces of a chunk, and a step on: old holds the wave below's rows
+    Rows m[kVdSteps];
+    uint32_t back[R];
+    auto begin = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < kVdSteps; ++j)
+#pragma unroll
+            for (int i = 0; i < R; ++i) m[j].x[i] = v + i < H ? nxt[j].x[i] * 16 : 0;
+        load(min(c + 1, chunks - 1));
+#pragma unroll
+        for (int i = 0; i < R; ++i) back[i] = 0;
+    };
+    auto advance = [&](int j, const int (&old)[8]) __attribute__((always_inline)) {
+        // rows v .. v + R - 1 + TM: those past its own are the next lane's, by a shift whose last
+        // lane takes the wave below's
+        int w[R + TM];
+#pragma unroll
+        for (int i = 0; i < R; ++i) w[i] = e.x[i];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) w[R + i] = __builtin_amdgcn_update_dpp(old[i], w[i], 0x130, 0xF, 0xF, false);
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            int k = w[i];
+#pragma unroll
+            for (int tau = 1; tau <= TM; ++tau) k = min(k, w[i + tau] + addc[tau]);
+            back[i] = (back[i] >> 4) | ((uint32_t)k << 28);
+            e.x[i] = (k & -16) - m[j].x[i];
+        }
+    };
+    auto end = [&](int c, int n) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+            if (v + i < H) bw[(int64_t)c * H + v + i] = back[i] >> (4 * (kVdSteps - n));
+    };
+    for (int turn = 0; turn < chunks + nwdp - 1 && !LOCK; ++turn) {
         const int c = turn - (nwdp - 1 - wave);
         if (wave < nwdp && c >= 0 && c < chunks) {
-            Rows m[kVdSteps];
-#pragma unroll
-            for (int j = 0; j < kVdSteps; ++j)
-#pragma unroll
-                for (int i = 0; i < R; ++i) m[j].x[i] = v + i < H ? nxt[j].x[i] * 16 : 0;
-            load(min(c + 1, chunks - 1));
+            begin(c);
             const int4* below = reinterpret_cast<const int4*>(seam + ((wave + 1) * 2 + (c & 1)) * kVdSteps * 8);
             Rows* mine = reinterpret_cast<Rows*>(seam + (wave * 2 + (c & 1)) * kVdSteps * 8);
-            uint32_t back[R];
-#pragma unroll
-            for (int i = 0; i < R; ++i) back[i] = 0;
             const int n = min(kVdSteps, d_max - c * kVdSteps);
             int4 pn = below[0], qn = below[1];
             auto step = [&](int j) __attribute__((always_inline)) {
@@ -661,21 +689,7 @@ __device__ __forceinline__ void vdisp_dp(const int32_t* myT, int Hm, int H, int 
                     qn = below[2 * j + 3];
                 }
                 if (lane < 8 / R) mine[8 / R * j + lane] = e;
-                // rows v .. v + R - 1 + TM: those past its own are the next lane's, by a shift whose last
-                // lane takes the wave below's
-                int w[R + TM];
-#pragma unroll
-                for (int i = 0; i < R; ++i) w[i] = e.x[i];
-#pragma unroll
-                for (int i = 0; i < TM; ++i) w[R + i] = __builtin_amdgcn_update_dpp(old[i], w[i], 0x130, 0xF, 0xF, false);
-#pragma unroll
-                for (int i = 0; i < R; ++i) {
-                    int k = w[i];
-#pragma unroll
-                    for (int tau = 1; tau <= TM; ++tau) k = min(k, w[i + tau] + addc[tau]);
-                    back[i] = (back[i] >> 4) | ((uint32_t)k << 28);
-                    e.x[i] = (k & -16) - m[j].x[i];
-                }
+                advance(j, old);
             };
             if (n == kVdSteps) {
 #pragma unroll
@@ -684,14 +698,27 @@ __device__ __forceinline__ void vdisp_dp(const int32_t* myT, int Hm, int H, int 
 #pragma unroll
                 for (int j = 0; j < kVdSteps; ++j)
                     if (j < n) step(j);
-#pragma unroll
-                for (int i = 0; i < R; ++i) back[i] >>= 4 * (kVdSteps - n);
             }
-#pragma unroll
-            for (int i = 0; i < R; ++i)
-                if (v + i < H) bw[(int64_t)c * H + v + i] = back[i];
+            end(c, n);
         }
         __syncthreads();
+    }
+    for (int c = 0; c < chunks && LOCK; ++c) {
+        const int n = min(kVdSteps, d_max - c * kVdSteps);
+        if (wave < nwdp) begin(c);
+#pragma unroll
+        for (int j = 0; j < kVdSteps; ++j)
+            if (j < n) {                                         // (the rows by step parity)
+                if (wave < nwdp && lane < 8 / R) reinterpret_cast<Rows*>(seam + (wave * 2 + (j & 1)) * kVdSteps * 8)[lane] = e;
+                __syncthreads();
+                if (wave < nwdp) {
+                    const int4* below = reinterpret_cast<const int4*>(seam + ((wave + 1) * 2 + (j & 1)) * kVdSteps * 8);
+                    const int4 p = below[0], q = below[1];
+                    const int old[8] = {p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w};
+                    advance(j, old);
+                }
+            }
+        if (wave < nwdp) end(c, n);
     }
     if (wave < nwdp) {
 #pragma unroll
@@ -702,7 +729,7 @@ __device__ __forceinline__ void vdisp_dp(const int32_t* myT, int Hm, int H, int 
 }
 
 __global__ __launch_bounds__(1024) void k_vdisp_fit(Dev d, const uint64_t* stream_ids, const int64_t* frame_idx,
-                                                    double* beta_out, int back_in_lds) {
+                                                    double* beta_out, int back_in_lds, int lockstep) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ int64_t rv[kMaxWaves];
     __shared__ int ri[kMaxWaves];
@@ -740,9 +767,13 @@ __global__ __launch_bounds__(1024) void k_vdisp_fit(Dev d, const uint64_t* strea
         uint32_t* lback = reinterpret_cast<uint32_t*>(seam + vdisp_seam_words(nwdp));
         uint32_t* gback = reinterpret_cast<uint32_t*>(d.back_y + (((int64_t)b * D1 * H + 3) & ~(int64_t)3));
         uint32_t* bw = back_in_lds ? lback : gback;
-        if (vdisp_lane_rows(H) > 2) vdisp_dp<8, 4>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
-        else if (tau_max <= 6) vdisp_dp<6, 2>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
-        else vdisp_dp<8, 2>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
+        auto dp = [&](auto lock) __attribute__((always_inline)) {
+            constexpr bool L = decltype(lock)::value;
+            if (vdisp_lane_rows(H) > 2) vdisp_dp<8, 4, L>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
+            else if (tau_max <= 6) vdisp_dp<6, 2, L>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
+            else vdisp_dp<8, 2, L>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
+        };
+        if (lockstep) dp(std::true_type{}); else dp(std::false_type{});
         const int v0 = __builtin_amdgcn_readfirstlane(first_row(E0));
         // The walk, by wave 0: disparities from 0 are the last step and down, so a chunk's words of the
         // 64 rows from the path's present one hold its next eight steps (tau <= 8), a lane a row.
@@ -3102,12 +3133,13 @@ ld_status run_hist(ld_frame f, const void* disp, int64_t pitch, int32_t* vdisp_o
 ld_status run_vdisp_fit(ld_frame f, const uint64_t* sid, const int64_t* fidx, double* beta_out, hipStream_t st) {
     Dev& d = f->d;
     int in_lds;
+    const int lock = vdisp_lockstep(vdisp_dp_waves(d.H, d.P.tau_y_max), d.d_max) ? 1 : 0;
     const size_t l2 = vdisp_fit_lds(d, &in_lds);
     allow_lds<k_vdisp_fit>(l2);
     {
         ProfScope ps(f, 1, st);
         hipLaunchKernelGGL(k_vdisp_fit, dim3(f->active), dim3(vdisp_fit_threads(d)), l2, st, d, sid, fidx, beta_out,
-                           in_lds);
+                           in_lds, lock);
     }
     return launch_ok();
 }

@@ -35,6 +35,14 @@ void raise_lds(int device, size_t bytes, Set set) {
     if (bytes > have.load(std::memory_order_relaxed) && set()) have.store(bytes, std::memory_order_release);
 }
 
+// Whether the v-disparity DP of `waves` waves takes its steps in lockstep, a barrier a step, or in turns
+// of eight steps, a wave a turn behind the one below it.  The turns to fill and drain that pipeline
+// take as long as steps: us in turns and in lockstep, for 8, 24, 48 and 64 disparities, 375 rows (three
+// waves) 11, 10; 14, 15; 28, 31; 29, 35; 720 (six) 15, 12; 17, 17; 22, 24; 37, 41; 1080 (nine) 18, 13; 21,
+// 19; 26, 27; 30, 33; 2048 (sixteen) 27, 16; 30, 23; 38, 34; 42, 41; 4096 (sixteen, four rows a lane) 39, 20;
+// 44, 32; 61, 50; 67, 62 (before the pipeline, a barrier and nine LDS reads a step, 4096 rows: 23, 40, 68, 86).
+inline bool vdisp_lockstep(int waves, int d_max) { return d_max <= 4 * waves; }
+
 // LDS of a stereo strip of E columns and T rows
 inline size_t stereo_strip_lds(int rho, int E, int T, int d_max) {
     const size_t rows = (size_t)T + 2 * rho, own = (size_t)(E + 2 * rho + 3 + 8) / 4;

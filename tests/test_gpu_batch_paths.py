@@ -180,3 +180,23 @@ def test_vpx_time_of_dense_rows():
         us.append(min(times))
         det.close()
     assert us[0] < 6 * us[1], us
+
+
+@pytest.mark.parametrize("h,d_max,kw", [
+    # the v-disparity DP in lockstep and, one disparity on, in turns: one wave, several, sixteen of either
+    # number of rows a lane; steps of part of a chunk, a whole one and one more
+    (128, 1, {}), (128, 4, {}), (128, 5, {}), (129, 8, {"tau_y_max": 8}), (300, 12, {}), (300, 13, {}), (720, 7, {"tau_y_max": 7}),
+    (1080, 9, {}), (1080, 36, {}), (1080, 37, {}), (2048, 3, {}), (2048, 16, {"lambda_y": 0}), (2048, 64, {}), (2049, 8, {}),
+    (2049, 36, {"tau_y_max": 3}), (2049, 37, {}), (4096, 2, {}), (4096, 17, {}), (4096, 64, {}), (4096, 65, {"tau_y_max": 8}),
+])
+def test_vdisp_path_of_tall_frames(h, d_max, kw):
+    import oracle
+    from paper_1807_02752_amd import ld
+    pair = [_noise(40, h, d_max, 1, s) for s in range(2)]
+    g, d = np.stack([p[0] for p in pair]), np.stack([p[1] for p in pair])
+    rng = np.random.default_rng(h + d_max)
+    d = np.where(rng.random(d.shape) < 0.4, rng.integers(0, d_max + 1, d.shape), d).astype(np.uint8)
+    out = run_gpu(g, d, d_max, params=ld.params_default(**kw))
+    out.pop("curves", None)     # FP32, far outside the image for a poor model
+    for b in range(2):
+        compare_frame(out, b, g[b], d[b], d_max, params=oracle.default_params(**kw))

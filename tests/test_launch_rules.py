@@ -102,3 +102,11 @@ int main() {
 }
 """)
     assert out == ["1"]
+
+
+def test_vdisp_dp_in_lockstep_by_rows(tmp_path):
+    # (waves, d_max): tall frames of few disparities were slower in turns than before those
+    cases = [(16, 1, 1), (16, 8, 1), (16, 24, 1), (16, 48, 1), (16, 128, 0), (9, 8, 1), (9, 64, 0), (6, 8, 1), (6, 48, 0), (3, 8, 1),
+             (3, 48, 0), (3, 128, 0), (1, 48, 0), (2, 255, 0)]
+    calls = "".join(f'std::printf("%d\\n", vdisp_lockstep({w}, {d}) ? 1 : 0);\n' for w, d, _ in cases)
+    assert [int(x) for x in run_host(tmp_path, "int main() {\n" + calls + "}\n")] == [x for *_, x in cases]
