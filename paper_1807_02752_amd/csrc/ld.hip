@@ -3180,17 +3180,7 @@ ld_status run_edges(ld_frame f, const uint8_t* grey, int64_t gp, const void* dis
 ld_status run_vpx_dp(ld_frame f, const Dev& d, hipStream_t st) {
     const size_t fixed = vpx_fit_lds(d);
     const int nt = kWave * (vpx_fit_waves(d.W2) + 1);
-    // Vote columns staged: what LDS leaves when a CU holds the frames that it is given, fewer where
-    // that would not stage an edge on every 96 pixels (road scenes hold one on 55 to 170): a
-    // row that is not staged costs a load's latency, about two staged rows.
-    auto room = [&](int per_cu) -> size_t {
-        const size_t share = (size_t)kMaxLds / per_cu - 1024;      // 1 KiB: the static arrays
-        return share > fixed ? (share - fixed) / sizeof(uint16_t) / 8 * 8 : 0;
-    };
-    const size_t px = (size_t)d.W * d.H;
-    int per_cu = std::max(1, std::min(4, (f->active + kCUs - 1) / kCUs));
-    while (per_cu > 1 && room(per_cu) < px / 96) --per_cu;
-    const int cap = (int)std::min((px + 7) / 8 * 8, room(per_cu));
+    const int cap = vpx_staged_votes(d.W, d.H, nt / kWave, fixed, f->active);
     const size_t l4 = fixed + sizeof(uint16_t) * (size_t)cap;
     ProfScope ps(f, 3, st);
     allow_lds<k_vpx_fit>(l4);

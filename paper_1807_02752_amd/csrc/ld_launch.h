@@ -43,6 +43,26 @@ void raise_lds(int device, size_t bytes, Set set) {
 // 44, 32; 61, 50; 67, 62 (before the pipeline, a barrier and nine LDS reads a step, 4096 rows: 23, 40, 68, 86).
 inline bool vdisp_lockstep(int waves, int d_max) { return d_max <= 4 * waves; }
 
+// The largest LDS of a workgroup of which per_cu fit a CU: it is given out 1280 bytes at a time (with three
+// equal shares of the 160 KiB the third found no place: 768 frames of 320 x 96 took 100 us, now 57).
+inline size_t lds_share(int per_cu) { return (size_t)kMaxLds / per_cu / 1280 * 1280; }
+
+// Vote columns (16 bits) that the V_px row DP stages in LDS, of `waves` waves a frame and `fixed` bytes
+// beside them: what is left when a CU holds the frames that it is given (up to eight, and to seven waves
+// a SIMD), fewer frames where that would not stage an edge on every 96 pixels (road scenes hold one on
+// 55 to 170): a row that is not staged costs a load's latency, about two staged rows.  (With at
+// most four frames a CU, 1536 frames of 320 x 96 took 124 us, now 79.)
+inline int vpx_staged_votes(int W, int H, int waves, size_t fixed, int frames) {
+    auto room = [&](int per_cu) -> size_t {
+        const size_t share = lds_share(per_cu) - 1024;                 // 1 KiB: the static arrays
+        return share > fixed ? (share - fixed) / 2 / 8 * 8 : 0;
+    };
+    const size_t px = (size_t)W * H;
+    int per_cu = std::max(1, std::min(std::min(8, 28 / waves), (frames + kCUs - 1) / kCUs));
+    while (per_cu > 1 && room(per_cu) < px / 96) --per_cu;
+    return (int)std::min((px + 7) / 8 * 8, room(per_cu));
+}
+
 // LDS of a stereo strip of E columns and T rows
 inline size_t stereo_strip_lds(int rho, int E, int T, int d_max) {
     const size_t rows = (size_t)T + 2 * rho, own = (size_t)(E + 2 * rho + 3 + 8) / 4;

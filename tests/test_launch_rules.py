@@ -110,3 +110,16 @@ def test_vdisp_dp_in_lockstep_by_rows(tmp_path):
              (3, 48, 0), (3, 128, 0), (1, 48, 0), (2, 255, 0)]
     calls = "".join(f'std::printf("%d\\n", vdisp_lockstep({w}, {d}) ? 1 : 0);\n' for w, d, _ in cases)
     assert [int(x) for x in run_host(tmp_path, "int main() {\n" + calls + "}\n")] == [x for *_, x in cases]
+
+
+def test_vpx_votes_staged_by_frames(tmp_path):
+    # (width, height, waves, bytes beside, frames), frames a CU: the LDS of that many fits a CU, 1280 bytes
+    # at a time, and is not given away where fewer would do
+    cases = [(320, 96, 2, 5700, 1, 1), (320, 96, 2, 5700, 768, 3), (320, 96, 2, 5700, 1024, 4), (320, 96, 2, 5700, 1536, 6),
+             (320, 96, 2, 5700, 2048, 8), (160, 120, 2, 5800, 1500, 6), (1242, 375, 5, 22800, 768, 3), (1242, 375, 5, 22800, 1024, 4),
+             (1242, 375, 5, 22800, 2048, 4), (1920, 1080, 7, 36100, 256, 1), (1920, 1080, 7, 36100, 1024, 2), (4096, 700, 14, 71400, 600, 1)]
+    calls = "".join(f'std::printf("%d\\n", vpx_staged_votes({w}, {h}, {nw}, {fx}, {n}));\n' for w, h, nw, fx, n, _ in cases)
+    for (w, h, nw, fixed, n, per_cu), x in zip(cases, run_host(tmp_path, "int main() {\n" + calls + "}\n")):
+        lds = -(-(fixed + 2 * int(x) + 512) // 1280) * 1280      # (the kernel's static arrays take 304)
+        assert per_cu * lds <= 160 * 1024, (w, n, x)
+        assert int(x) >= w * h or (per_cu + 1) * (lds + 1280 + 1024) > 160 * 1024, (w, n, x)
