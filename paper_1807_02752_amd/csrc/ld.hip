@@ -2023,7 +2023,7 @@ __global__ __launch_bounds__(BT) void k_energy(Dev d, const uint8_t* cand_mask, 
     }
 }
 
-// The same energies by two launches, for up to kSplitFrames frames: k_m1 forms M_1 of every
+// The same energies by two launches, for few frames (energy_form): k_m1 forms M_1 of every
 // track row (in the q buffer, which is a frame's size), k_tracks follows the tracks, a candidate
 // a thread.  Every sum is taken in the order of k_energy, so the energies are the same bits.
 // Neither has a chain over the rows with a barrier a row: 1242 x 375, one frame, 187 us by
@@ -3220,36 +3220,20 @@ void launch_energy(ld_frame f, const Dev& d, const uint8_t* mask, float* eout, h
                        staged ? (int)(base / sizeof(float)) : 0);
 }
 
-// Which form of the energies a launch takes (us of the step; 1242 x 375 and, after the slash,
-// 1920 x 1080 frames with u16 disparity):
-//   frames          1     61    128     192     256     384    512    1024
-//   two launches  24/51   59   109/412 163/591 206/785  322   426     806
-//   k_energy 512    -      -   189/602 194/614 198/617  257   262/914  515
-//   k_energy 256  187/740 201  218/828 223/836 225/837  257   260/1047 388
-// A frame's sweep is one workgroup with a barrier a row, so below about a workgroup per CU its
-// time is its latency; the two launches use the whole chip for any number of frames but move
-// M_1 through memory (R W floats a frame, written and read).  Past kSplitFrames that costs more
-// than the sweep.  With one or two frames per CU the sweep is shortest with 512 threads (two
-// waves a SIMD, edges loaded three rows ahead); with four, 256 threads issue less for the same
-// columns.  Above 1536 columns 256 threads would own 8 and more columns each (192 VGPRs, two
-// workgroups a CU): 512 threads there for every number of frames.
-constexpr int kSplitFrames = 192, kWideFrames = 384, kWideColumns = 1536;
-
 ld_status run_energy(ld_frame f, const uint8_t* mask, float* eout, hipStream_t st, const Dev* dsel = nullptr) {
     ProfScope ps(f, 4, st);
     const Dev& d = dsel ? *dsel : f->d;
-    if (f->active <= kSplitFrames) {
+    const EnergyForm form = energy_form(d.W, f->active);
+    if (form == EnergyForm::kTwoLaunches) {
         const int cols = kM1Waves * kM1Cols;
         const dim3 g1((d.W + cols - 1) / cols, (d.H + kM1Rows - 1) / kM1Rows, f->active);
         hipLaunchKernelGGL(k_m1, g1, dim3(kM1Waves * kWave), 0, st, d);
         hipLaunchKernelGGL(k_tracks, dim3((d.W2 + kWave - 1) / kWave, f->active), dim3(kWave), 0, st, d, mask, eout);
         return launch_ok();
     }
-    if (f->active <= kWideFrames || d.W > kWideColumns) {
+    if (form == EnergyForm::kThreads512) {                   // (more than 1024 columns)
         const int nc = (d.W + 511) / 512;
-        if (nc <= 1) launch_energy<1, 2, 512, 3>(f, d, mask, eout, st);
-        else if (nc <= 2) launch_energy<2, 4, 512, 3>(f, d, mask, eout, st);
-        else if (nc <= 3) launch_energy<3, 6, 512, 3>(f, d, mask, eout, st);
+        if (nc <= 3) launch_energy<3, 6, 512, 3>(f, d, mask, eout, st);
         else if (nc <= 4) launch_energy<4, 8, 512, 3>(f, d, mask, eout, st);
         else if (nc <= 6) launch_energy<6, 12, 512, 3>(f, d, mask, eout, st);
         else launch_energy<8, 16, 512, 3>(f, d, mask, eout, st);

@@ -63,6 +63,29 @@ inline int vpx_staged_votes(int W, int H, int waves, size_t fixed, int frames) {
     return (int)std::min((px + 7) / 8 * 8, room(per_cu));
 }
 
+// Which form of the energies a launch takes: two launches over the whole chip (k_m1 and k_tracks), or one
+// workgroup of 512 or of 256 threads a frame (k_energy); us of the step, 1242 x 375 and, after
+// the slash, 1920 x 1080 frames with u16 disparity:
+//   frames          1     61    128     192     256     384    512    1024
+//   two launches  24/51   59   109/412 163/591 206/785  322   426     806
+//   k_energy 512    -      -   189/602 194/614 198/617  257   262/914  515
+//   k_energy 256  187/740 201  218/828 223/836 225/837  257   260/1047 388
+// A frame's sweep is one workgroup with a barrier a row, so below about a workgroup per CU its
+// time is its latency; the two launches use the whole chip for any number of frames but move M_1
+// through memory (R W floats a frame, written and read), which costs more than the sweep the sooner
+// the wider the frame is: from 192 frames, or from 384 up to 1024 columns (us at 384 frames, two
+// launches, 512 and 256 threads: 64 x 64 28, 45, 38; 320 x 96 55, 63, 60; 512 x 160 84, 118, 98; 641 x
+// 240 131, 189, 179; 960 x 300 227, 236, 243).  With one or two frames per CU the sweep of a wider
+// frame is shortest with 512 threads (two waves a SIMD, edges loaded three rows ahead); with
+// four, 256 threads issue less for the same columns.  Above 1536 columns 256 threads would own 8 and
+// more columns each (192 VGPRs, two workgroups a CU): 512 threads there for every number of frames.
+enum class EnergyForm { kTwoLaunches, kThreads512, kThreads256 };
+
+inline EnergyForm energy_form(int W, int frames) {
+    if (frames <= (W <= 1024 ? 384 : 192)) return EnergyForm::kTwoLaunches;
+    return (frames <= 384 || W > 1536) ? EnergyForm::kThreads512 : EnergyForm::kThreads256;
+}
+
 // LDS of a stereo strip of E columns and T rows
 inline size_t stereo_strip_lds(int rho, int E, int T, int d_max) {
     const size_t rows = (size_t)T + 2 * rho, own = (size_t)(E + 2 * rho + 3 + 8) / 4;

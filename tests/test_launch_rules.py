@@ -123,3 +123,13 @@ def test_vpx_votes_staged_by_frames(tmp_path):
         lds = -(-(fixed + 2 * int(x) + 512) // 1280) * 1280      # (the kernel's static arrays take 304)
         assert per_cu * lds <= 160 * 1024, (w, n, x)
         assert int(x) >= w * h or (per_cu + 1) * (lds + 1280 + 1024) > 160 * 1024, (w, n, x)
+
+
+def test_energy_form_by_width_and_frames(tmp_path):
+    # two launches (0), 512 threads a frame (1) or 256 (2), the fastest measured: one line at 192 frames for
+    # every width made 193 to 384 frames of up to 512 columns slower than 256 threads had been
+    cases = [(64, 1, 0), (64, 193, 0), (64, 384, 0), (64, 385, 2), (320, 320, 0), (512, 256, 0), (512, 384, 0), (512, 385, 2), (960, 384, 0),
+             (1024, 384, 0), (1025, 193, 1), (1242, 192, 0), (1242, 193, 1), (1242, 384, 1), (1242, 385, 2), (1536, 1024, 2), (1537, 1024, 1),
+             (1920, 192, 0), (1920, 193, 1), (4096, 1, 0), (4096, 500, 1)]
+    calls = "".join(f'std::printf("%d\\n", (int)energy_form({w}, {n}));\n' for w, n, _ in cases)
+    assert [int(x) for x in run_host(tmp_path, "int main() {\n" + calls + "}\n")] == [x for *_, x in cases]
