@@ -3112,12 +3112,7 @@ void launch_hist(int npt, dim3 g, size_t lds, hipStream_t st, const Dev& d, cons
 // S1 for the active frames of f
 ld_status run_hist(ld_frame f, const void* disp, int64_t pitch, int32_t* vdisp_out, hipStream_t st) {
     Dev d = f->d;
-    // Rows a workgroup: a group of rows is a load's latency and its LDS atomics, so few frames want
-    // one group a workgroup; very many want longer runs, whose counts leave as whole cache lines
-    // (us at 4, 8 and 32 rows: one 1242 x 375 frame 9, 13, 34; 128 frames 65, 68, 77; 512 frames
-    // 170, 156, 180; 256 of 1920 x 1080 401, 351, 453; 1024 of 1242 x 375 470, 480, 443).
-    const int64_t groups = (int64_t)f->active * ((d.H + kHistGroup - 1) / kHistGroup);
-    if (groups <= 72 * 1024) d.hist_rows = std::min(d.hist_rows, (groups <= 24 * 1024 ? 1 : 2) * kHistGroup);
+    d.hist_rows = hist_rows(d.W, d.H, f->active, kHistGroup, d.hist_rows);
     dim3 g1((d.H + d.hist_rows - 1) / d.hist_rows, f->active);
     const size_t l1 = sizeof(int) * d.hist_rows * d.D1;
     const uint8_t* dp = static_cast<const uint8_t*>(disp);

@@ -86,6 +86,25 @@ inline EnergyForm energy_form(int W, int frames) {
     return (frames <= 384 || W > 1536) ? EnergyForm::kThreads512 : EnergyForm::kThreads256;
 }
 
+// Rows a workgroup of the v-disparity histogram, from `group` (a load's rows) to `most`.  A group of rows is
+// a load's latency and its LDS atomics, so few groups want one a workgroup; many want longer runs, whose
+// counts leave as whole cache lines, the sooner the narrower the rows are; beyond 1024 columns the load takes
+// longer and runs of 16 rows were the slowest.  us at 4, 8, 16 and 32 rows, u8 disparity:
+//   64 x 375      64 frames 13, 12, 11, 14   256 32, 26, 24, 26   512 57, 44, 40, 41   1500 173, 130, 117, 108
+//   160 x 120     64 8, 8, 9, 12             512 25, 22, 22, 22   1024 46, 36, 36, 37   2048 87, 68, 68, 65
+//   320 x 96      64 8, 9, 11, 16            256 18, 16, 16, 19   1024 50, 43, 39, 42   2048 93, 76, 68, 69
+//   641 x 240     64 17, 18, 19, 25          256 44, 42, 43, 51   512 80, 72, 72, 87    2048 289, 256, 244, 300
+//   1242 x 375    1 8, 11, 17, 30            128 51, 50, 57, 61   512 172, 160, 188, 187   (f32, 1024 frames 470, 480, 443 at 4, 8 and 32)
+//   1920 x 1080   1 10, 15, 25, 44           64 95, 95, 101, 113  256 340, 323, 326, 336
+inline int hist_rows(int W, int H, int frames, int group, int most) {
+    const int64_t groups = (int64_t)frames * ((H + group - 1) / group);
+    int rows = 8 * group;
+    if (groups <= (int64_t)9 * W) rows = group;
+    else if (groups <= (W < 1024 ? (int64_t)36 * W : 72 * 1024)) rows = 2 * group;
+    else if (W < 1024 && (W >= 256 || groups <= 48 * 1024)) rows = 4 * group;
+    return std::min(rows, most);
+}
+
 // LDS of a stereo strip of E columns and T rows
 inline size_t stereo_strip_lds(int rho, int E, int T, int d_max) {
     const size_t rows = (size_t)T + 2 * rho, own = (size_t)(E + 2 * rho + 3 + 8) / 4;

@@ -133,3 +133,15 @@ def test_energy_form_by_width_and_frames(tmp_path):
              (1920, 192, 0), (1920, 193, 1), (4096, 1, 0), (4096, 500, 1)]
     calls = "".join(f'std::printf("%d\\n", (int)energy_form({w}, {n}));\n' for w, n, _ in cases)
     assert [int(x) for x in run_host(tmp_path, "int main() {\n" + calls + "}\n")] == [x for *_, x in cases]
+
+
+def test_histogram_rows_by_width_and_frames(tmp_path):
+    # rows a workgroup, within a few percent of the fastest measured: one line on the groups for every width
+    # made some hundred narrow frames slower than 32 rows had been
+    cases = [(64, 375, 256, 16), (64, 375, 1500, 32), (64, 64, 1, 4), (64, 64, 1024, 16), (160, 120, 1, 4), (160, 120, 256, 16), (160, 120, 2048, 32),
+             (320, 96, 1, 4), (320, 96, 256, 8), (320, 96, 768, 16), (320, 96, 2048, 16), (641, 240, 256, 8), (641, 240, 2048, 16), (960, 300, 1, 4),
+             (1242, 375, 1, 4), (1242, 375, 61, 4), (1242, 375, 512, 8), (1242, 375, 1024, 32), (1920, 1080, 1, 4), (1920, 1080, 256, 8),
+             (4096, 700, 600, 32)]
+    calls = "".join(f'std::printf("%d\\n", hist_rows({w}, {h}, {n}, 4, 32));\n' for w, h, n, _ in cases)
+    out = run_host(tmp_path, "int main() {\n" + calls + 'std::printf("%d\\n", hist_rows(1242, 375, 1024, 4, 8));\n}\n')
+    assert [int(x) for x in out] == [x for *_, x in cases] + [8]
