@@ -968,7 +968,7 @@ __global__ __launch_bounds__(1024) void k_vdisp_fit(Dev d, const uint64_t* strea
 // nothing carries over from an earlier call).
 template <int N> using IntC = std::integral_constant<int, N>;
 
-constexpr int kEdgeStrip = 32;                        // rows per workgroup, at most
+constexpr int kEdgeStrip = 32;                        // rows per workgroup (edge_rows), at most
 constexpr int kEdgeCols = 4 * kWave;                  // columns per wave
 constexpr int kEdgeQueue = 512;                       // queued edge pixels per wave
 constexpr int kEdgeFlushAt = kEdgeQueue - kEdgeCols;  // a row queues at most kEdgeCols
@@ -3148,12 +3148,7 @@ ld_status run_vdisp(ld_frame f, const void* disp, int64_t pitch, const uint64_t*
 ld_status run_edges(ld_frame f, const uint8_t* grey, int64_t gp, const void* disp, int64_t dpt, hipStream_t st) {
     Dev& d = f->d;
     const int nw = (d.W + kEdgeCols - 1) / kEdgeCols;
-    // Rows a workgroup: its time is a chain of rows and of the disparities gathered for them, and each
-    // strip loads two rows more than it takes (us at 2, 4, 8 and 32 rows: one 1242 x 375 frame 7, 9,
-    // 12, 27; 16 frames 17, 14, 15, 31; 61 of 1241 x 376 40, 32, 28, 36; 128 79, 61, 49, 58; 256
-    // 153, 114, 87, 90; 1024 590, 426, 312, 285)
-    const int64_t all = (int64_t)f->active * d.H;
-    const int strip = all <= 2048 ? 2 : all <= 8192 ? 4 : all <= 64 * 1024 ? 8 : kEdgeStrip;
+    const int strip = edge_rows(d.H, nw, f->active);
     const dim3 g3((d.H + strip - 1) / strip, f->active);
     const size_t lds = edges_lds(nw);
     const uint8_t* dp = static_cast<const uint8_t*>(disp);

@@ -105,6 +105,19 @@ inline int hist_rows(int W, int H, int frames, int group, int most) {
     return std::min(rows, most);
 }
 
+// Rows a workgroup of the edges, `waves` waves wide.  Its time is a chain of rows and of the disparities
+// gathered for them, and each strip loads two rows more than it takes, so the line is one on rows times
+// waves.  us at 2, 4, 8 and 32 rows:
+//   1242 x 375 (5 waves)    1 frame 7, 9, 12, 27   16 17, 14, 15, 31   128 79, 61, 49, 58   256 153, 114, 87, 90   1024 590, 426, 312, 285
+//   320 x 96 (2)            64 10, 10, 12, 23      256 22, 18, 16, 27  1024 64, 48, 42, 39
+//   641 x 240 (3)           64 18, 16, 16, 27      512 100, 75, 61, 78 1024 190, 139, 109, 135
+//   1920 x 1080 (8)         4 16, 14, 13, 25       32 83, 61, 47, 53   64 158, 114, 82, 80
+//   4000 x 400 (16)         4 16, 15, 13, 30       16 44, 37, 29, 31   32 81, 65, 52, 54    64 163, 126, 94, 81   128 317, 241, 180, 143
+inline int edge_rows(int H, int waves, int frames) {
+    const int64_t all = (int64_t)frames * H * waves;
+    return all <= 10 * 1024 ? 2 : all <= 40 * 1024 ? 4 : all <= 300 * 1024 ? 8 : 32;
+}
+
 // LDS of a stereo strip of E columns and T rows
 inline size_t stereo_strip_lds(int rho, int E, int T, int d_max) {
     const size_t rows = (size_t)T + 2 * rho, own = (size_t)(E + 2 * rho + 3 + 8) / 4;

@@ -200,3 +200,13 @@ def test_vdisp_path_of_tall_frames(h, d_max, kw):
     out.pop("curves", None)     # FP32, far outside the image for a poor model
     for b in range(2):
         compare_frame(out, b, g[b], d[b], d_max, params=oracle.default_params(**kw))
+
+
+@pytest.mark.parametrize("w,h,n", [(130, 63, 200), (257, 41, 180), (300, 64, 90), (64, 41, 4000), (64, 39, 8000), (64, 64, 4801)])
+def test_edges_by_rows_of_waves(w, h, n):
+    # strips of four, eight and 32 rows, with and without rows left over
+    g, d = _frames("road", w, h, n)
+    out = run_gpu(g, d, 48)
+    out.pop("curves", None)     # FP32, far outside the image for a poor model
+    for b in sorted({0, n // 2, n - 1}):
+        compare_frame(out, b, g[b], d[b], 48)

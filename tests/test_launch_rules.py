@@ -145,3 +145,13 @@ def test_histogram_rows_by_width_and_frames(tmp_path):
     calls = "".join(f'std::printf("%d\\n", hist_rows({w}, {h}, {n}, 4, 32));\n' for w, h, n, _ in cases)
     out = run_host(tmp_path, "int main() {\n" + calls + 'std::printf("%d\\n", hist_rows(1242, 375, 1024, 4, 8));\n}\n')
     assert [int(x) for x in out] == [x for *_, x in cases] + [8]
+
+
+def test_edge_rows_by_width_and_frames(tmp_path):
+    # rows a workgroup by rows times waves: one line on the rows alone made 64 frames of 2560 x 720 and 64 to
+    # 128 of 4000 x 400 slower than 32 rows had been
+    cases = [(64, 1, 1, 2), (64, 1, 256, 4), (96, 2, 1, 2), (96, 2, 256, 8), (375, 5, 1, 2), (375, 5, 16, 4), (376, 5, 61, 8), (375, 5, 128, 8),
+             (375, 5, 256, 32), (375, 5, 1024, 32), (1080, 8, 1, 2), (1080, 8, 4, 4), (1080, 8, 32, 8), (1080, 8, 64, 32), (720, 10, 64, 32),
+             (400, 16, 4, 4), (400, 16, 32, 8), (400, 16, 64, 32), (400, 16, 128, 32)]
+    calls = "".join(f'std::printf("%d\\n", edge_rows({h}, {nw}, {n}));\n' for h, nw, n, _ in cases)
+    assert [int(x) for x in run_host(tmp_path, "int main() {\n" + calls + "}\n")] == [x for *_, x in cases]
