@@ -1684,12 +1684,10 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
 }
 
 // S8 for every frame: RANSAC of the quartic through the row-DP path (read back from the path
-// columns), V_px and the track tables.  One workgroup per frame: three waves, so that a 1024
-// batch's frames are all on the chip at once, eight where the chip holds those.  Hypothesis 0:
+// columns), V_px and the track tables.  One workgroup per frame (ransac_threads).  Hypothesis 0:
 // the seed of the narrowed search for the frames that kept one (pruned = 1), otherwise the
 // caller's seed rows.
-constexpr int kRansacThreads = 192, kRansacThreadsFew = 512;
-__global__ __launch_bounds__(kRansacThreadsFew) void k_vpx_ransac(Dev d, const uint64_t* stream_ids, const int64_t* frame_idx,
+__global__ __launch_bounds__(512) void k_vpx_ransac(Dev d, const uint64_t* stream_ids, const int64_t* frame_idx,
                                                     const double* seed_gamma, int pruned, double* vp_out) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ RansacShared S;
@@ -3185,8 +3183,7 @@ ld_status run_vpx_ransac(ld_frame f, const uint64_t* sid, const int64_t* fidx, c
     const size_t l = sizeof(int) * 4 * (((size_t)d.H + 3) / 4 * 4) + sizeof(uint32_t) * ((d.H + 31) / 32);
     allow_lds<k_vpx_ransac>(l);
     ProfScope ps(f, 10, st);
-    // (44 against 47 us for one 1242 x 375 frame, 80 against 99 for 256 of 1920 x 1080)
-    const int nt = f->active <= 2 * kCUs ? kRansacThreadsFew : kRansacThreads;
+    const int nt = ransac_threads(f->active);
     hipLaunchKernelGGL(k_vpx_ransac, dim3(f->active), dim3(nt), l, st, d, sid, fidx, seed_gamma, pruned, vp_out);
     return launch_ok();
 }

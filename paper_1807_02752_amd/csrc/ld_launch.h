@@ -118,6 +118,11 @@ inline int edge_rows(int H, int waves, int frames) {
     return all <= 10 * 1024 ? 2 : all <= 40 * 1024 ? 4 : all <= 300 * 1024 ? 8 : 32;
 }
 
+// Threads a frame of the V_px RANSAC: eight waves while every frame has a CU to itself, else three, so that a
+// CU's frames share it evenly.  us with 192 and 512 threads: 1242 x 375, one frame 29, 27; 256 frames 78, 68; 320
+// 89, 93; 512 89, 108; 1280 x 720, 256 frames 127, 105; 384 131, 133; 320 x 96, 1 to 256 frames 18, 19; 384 20, 33.
+inline int ransac_threads(int frames) { return frames <= kCUs ? 512 : 192; }
+
 // LDS of a stereo strip of E columns and T rows
 inline size_t stereo_strip_lds(int rho, int E, int T, int d_max) {
     const size_t rows = (size_t)T + 2 * rho, own = (size_t)(E + 2 * rho + 3 + 8) / 4;

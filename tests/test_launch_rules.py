@@ -155,3 +155,9 @@ def test_edge_rows_by_width_and_frames(tmp_path):
              (400, 16, 4, 4), (400, 16, 32, 8), (400, 16, 64, 32), (400, 16, 128, 32)]
     calls = "".join(f'std::printf("%d\\n", edge_rows({h}, {nw}, {n}));\n' for h, nw, n, _ in cases)
     assert [int(x) for x in run_host(tmp_path, "int main() {\n" + calls + "}\n")] == [x for *_, x in cases]
+
+
+def test_ransac_threads_by_frames(tmp_path):
+    # 512 threads with two frames a CU were slower than 192 at every size, for short frames than before those
+    body = "int main() { for (int n : {1, 256, 257, 384, 512, 513, 4096}) std::printf(\"%d\\n\", ransac_threads(n)); }\n"
+    assert [int(x) for x in run_host(tmp_path, body)] == [512, 512, 192, 192, 192, 192, 192]
