@@ -1325,11 +1325,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
     // A frame with many edges would wait for the one wave that keeps the counts, which moves each vote
     // twice (once for either parity) and reads what is not staged from memory: there all the waves
     // share the votes of one row of counts, with a second barrier a row, and nothing is staged.  An
-    // edge that is not staged counts as five, and the more waves share the sooner it pays (us,
-    // one wave and shared, by edges a row and of them not staged; 1242 wide: 55, 0: 265, 301;
-    // 111, 0: 342, 321; 181, 0: 433, 341; 1024 frames 28, 4: 532, 538; 55, 31: 721, 570; 181, 156:
-    // 1561, 677; 320 wide: 287, 0: 175, 185; 1024 frames 287, 108: 329, 289; a 1920 x 540 frame of
-    // noise, 8900, 1680).
+    // edge that is not staged counts as five, and the more waves share the sooner it pays (us, one
+    // wave and shared, by edges a row and of them not staged; 1242 wide: 55, 0: 265, 301; 111, 0:
+    // 342, 321; 181, 0: 433, 400; 1024 frames 28, 4: 532, 538; 55, 31: 721, 644; 181, 156: 1561, 760;
+    // 320 wide: 287, 0: 175, 185; 1024 frames 287, 108: 329, 302; 1920 x 540: 271, 151: 1400, 774;
+    // 1778, 1658: 8900, 1670; there every thread kept counts before: 1242 wide 402 to 445, 1024 frames
+    // 685 to 835, 1920 x 540 622 and 1370).
     const bool shared_votes = __builtin_expect((roff[R] + 4 * max(roff[R] - stage_cap, 0)) * nw > kSharedVotes * R, 0);
     int nv = 0;   // votes that landed in a column
     for (int r0 = wave * kStageRows; r0 < R && !shared_votes; r0 += (nw + 1) * kStageRows) {
@@ -1384,27 +1385,44 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
     for (int r = max(R - 1 - chi, 0) + wave; r < R && !shared_votes; r += nw + 1) vote_rows(hist + (v_max & 1) * WP, r, r, 1);
     for (int r = max(R - 2 - chi, 0) + wave; r <= min(R - 2 + chi, R - 1) && !shared_votes; r += nw + 1)
         vote_rows(hist + ((v_max & 1) ^ 1) * WP, r, r, 1);
-    // shared votes: from the band of road row r + 1 to that of row r, one row enters and one leaves
-    // (rows outside the road hold nothing), four edges a thread of both in flight
-    auto move_band = [&](int ra, int rl) {
-        const int na = ra >= 0 ? roff[ra + 1] - roff[ra] : 0, nl = rl < R ? roff[rl + 1] - roff[rl] : 0;
-        for (int i = t; i < max(na, nl); i += 4 * nt) {
-            int a[4], l[4];
+    // Shared votes: from the band of road row r + 1 to that of row r, one row enters and one leaves
+    // (rows outside the road hold nothing).  A thread's first edge of either is read a row ahead, the
+    // others two of either row at a time; the loops are the workgroup's, so that the votes are
+    // counted a wave at a time (nvs) and take no register.
+    int nvs = 0, na = 0, nl = 0, enters = kNoVote, leaves = kNoVote;
+    auto edges_of = [&](int r) { return r >= 0 && r < R ? __builtin_amdgcn_readfirstlane(roff[r + 1] - roff[r]) : 0; };
+    auto ahead = [&](int ra, int rl) __attribute__((always_inline)) {
+        na = edges_of(ra);
+        nl = edges_of(rl);
+        enters = t < na ? edge_of(ra, t) : kNoVote;
+        leaves = t < nl ? edge_of(rl, t) : kNoVote;
+    };
+    auto move = [&](int a, int l) __attribute__((always_inline)) {
+        vote(hist, a, 1);
+        vote(hist, l, -1);
+        nvs += __popcll(__ballot(a != kNoVote));
+    };
+    auto move_band = [&](int ra, int rl) __attribute__((always_inline)) {
+        const int a0 = enters, l0 = leaves, ca = na, cl = nl;
+        ahead(ra - 1, rl - 1);
+        move(a0, l0);
+        for (int i0 = nt; i0 < max(ca, cl); i0 += 2 * nt) {
+            int a[2], l[2];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                a[q] = i + q * nt < na ? edge_of(ra, i + q * nt) : kNoVote;
-                l[q] = i + q * nt < nl ? edge_of(rl, i + q * nt) : kNoVote;
+            for (int q = 0; q < 2; ++q) {
+                const int i = i0 + q * nt + t;
+                a[q] = i < ca ? edge_of(ra, i) : kNoVote;
+                l[q] = i < cl ? edge_of(rl, i) : kNoVote;
             }
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                vote(hist, a[q], 1);
-                vote(hist, l[q], -1);
-                nv += a[q] != kNoVote ? 1 : 0;
-            }
+            for (int q = 0; q < 2; ++q) move(a[q], l[q]);
         }
     };
-    if (__builtin_expect(shared_votes, 0))
-        for (int r = max(R - 1 - chi, 0); r < R; ++r) move_band(r, R);
+    if (__builtin_expect(shared_votes, 0)) {
+        ahead(R - 1, R);
+        for (int r = R - 1; r >= max(R - 1 - chi, 0); --r) move_band(r, R + 1);
+        ahead(R - 2 - chi, R - 1 + chi);
+    }
     // backtrace: the ranks of a thread's columns in two words, at the start of the q buffer's row
     // of W words (k_energy and k_m1 write that buffer later)
     const int L = (W2 + K - 1) / K;                            // threads with a column
@@ -1675,7 +1693,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
             }
         }
     }
-    nv = block_sum_i32(nv, red);
+    nv = block_sum_i32(nv + (lane == 0 ? nvs : 0), red);
     if (t == 0) {
         fi.n_edges = roff[R];
         fi.n_votes = nv;
