@@ -500,3 +500,45 @@ def test_gradient_sums_every_workgroup_once(B, nb):
     assert np.abs(whole - np.sum(parts, 0)).max() <= 1e-3 * np.sum(np.abs(parts), 0).max()
     det.close()
     net.close()
+
+
+@pytest.mark.parametrize("B", [1, 15, 16, 17, 255, 256, 257, 336, 513])
+def test_gradient_is_the_sum_of_the_workgroups(B):
+    # frames of one 60-column tile and one band, so that each is one workgroup: the batch's gradients and
+    # loss against the FP64 sum of those of each frame launched alone, which passes through no long sum.
+    # An FP32 sum of B terms is within B 2^-24 of their absolute sum, whatever they cancel to
+    ld = _ld()
+    greys, disps = frames_c2(2, seed=4)
+    u = slice(600, 660)
+    gs, ds = [np.ascontiguousarray(x[:, u]) for x in greys], [np.ascontiguousarray(x[:, u]) for x in disps]
+    g = torch.from_numpy(np.stack([gs[b % 2] for b in range(B)])).cuda()
+    d = torch.from_numpy(np.stack([ds[b % 2] for b in range(B)])).cuda()
+    H, W = g.shape[1:]
+    net = ld.Cnn(random_params(7), n_bands=1, max_batch=B, max_width=W)
+    labels = torch.from_numpy(_labels_for(np.random.default_rng(11), B, 1, W)).cuda()
+    ids = torch.zeros(B, dtype=torch.int64, device="cuda")
+
+    def frames(lo, hi):
+        det = ld.Detector(W, H, hi - lo, ld.LD_DISP_F32, 128)
+        det.vdisp(d[lo:hi], stream_ids=ids[lo:hi], frame_idx=ids[lo:hi])
+        return det
+
+    def step(det, lo, hi):
+        loss = torch.zeros(1, dtype=torch.float32, device="cuda")
+        grad = torch.zeros(ld.LD_CNN_PARAMS, dtype=torch.float32, device="cuda")
+        net.train_step(det, g[lo:hi], d[lo:hi], labels[lo:hi], 4.0, 1e-4, 0.0, loss, grad)
+        det.sync()
+        return np.append(grad.cpu().numpy().astype(np.float64), float(loss.item()))
+
+    det = frames(0, B)
+    whole = step(det, 0, B)
+    det.close()
+    alone = [frames(b, b + 1) for b in range(min(B, 2))]
+    parts = np.stack([step(alone[b % 2], b, b + 1) for b in range(B)])
+    for x in alone:
+        x.close()
+    net.close()
+    assert (np.abs(parts).sum(1) > 0).all()              # a road, and so a band, in every frame
+    scale = np.abs(parts).sum(0)
+    bad = np.flatnonzero(np.abs(whole - parts.sum(0)) > B * 2.0 ** -24 * scale)
+    assert bad.size == 0, (bad[:5], whole[bad[:5]], parts.sum(0)[bad[:5]], scale[bad[:5]])
