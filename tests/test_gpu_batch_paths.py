@@ -210,3 +210,39 @@ def test_edges_by_rows_of_waves(w, h, n):
     out.pop("curves", None)     # FP32, far outside the image for a poor model
     for b in sorted({0, n // 2, n - 1}):
         compare_frame(out, b, g[b], d[b], 48)
+
+
+@pytest.mark.parametrize("w,h,n", [
+    # a workgroup a frame: 512 threads with three to eight columns each, 256 with two to six; widths that
+    # fill the threads' columns, one more, and the largest
+    (1025, 64, 193), (1242, 66, 193), (1536, 61, 384), (2048, 50, 193), (2049, 50, 193), (3072, 40, 193), (3073, 40, 193),
+    (4096, 41, 193), (256, 70, 385), (257, 64, 385), (513, 64, 385), (769, 62, 385), (1024, 60, 385), (1280, 58, 385), (1281, 60, 385),
+])
+def test_energies_by_columns_a_thread(w, h, n):
+    g, d = _frames("road", w, h, n)
+    out = run_gpu(g, d, 48)
+    out.pop("curves", None)     # FP32, far outside the image for a poor model
+    for b in sorted({0, n // 2, n - 1}):
+        compare_frame(out, b, g[b], d[b], 48)
+
+
+@pytest.mark.parametrize("kind,w,h,few", [("road", 300, 96, 384), ("road", 1024, 64, 384), ("random", 320, 60, 384),
+                                          ("road", 1100, 64, 192), ("road", 1600, 70, 192), ("random", 1242, 50, 192)])
+def test_energies_same_bits_in_either_form(kind, w, h, few):
+    # the most frames that take two launches, and one more: every sum is taken in the same order
+    from paper_1807_02752_amd import ld
+    import torch
+    g, d = _frames(kind, w, h, few + 1)
+    dm = 32 if kind == "random" else 48
+    res = []
+    for n in (few, few + 1):
+        det = ld.Detector(w, h, n, ld.LD_DISP_U8, dm)
+        gg, dd = torch.from_numpy(g[:n]).cuda(), torch.from_numpy(d[:n]).cuda()
+        det.vdisp(dd)
+        det.vp_ransac(gg, dd)
+        det.lane_energy()
+        det.sync()
+        res.append(np.stack([det.read(ld.LD_STATE_ENERGY, b) for b in (0, 1, few // 2, few - 1)]))
+        det.close()
+    assert np.abs(res[0]).max() > 0
+    assert np.array_equal(res[0], res[1])
