@@ -61,11 +61,13 @@ struct Dev {
     double* tab;        // B x 6 x H    f, f', V_py, V_px, A_v, B_v
     int32_t* rowcnt;    // B x H        road edges per row
     ld_edge* edges;     // B x H x W    per-row edge buckets
-    int8_t* back_x;     // B x H x ceil(2W/8) x 4 B   row-DP backtrace, 4-bit tie ranks
+    int8_t* back_x;     // B x H x ceil(2W/8) x 4 B   backtrace of the windowed search (k_vpx_window), 4-bit tie ranks
     int32_t* mxpath;    // B x H        row-DP path columns
     double* energy;     // B x 2W
     int32_t* trace;     // B x 2 x 3 x kMaxRounds
-    float* qbuf;        // B x H x W    G_x w_g of every road edge, in bucket order
+    float* qbuf;        // B x H x W    in turn: the row DP's backtrace, two words for every ten columns of 2W at
+                        // the start of a row's W words (k_vpx_fit; read to its end there); then, from the
+                        // edges, G_x w_g of every road edge in bucket order (k_energy) or M_1 (k_m1)
     uint32_t* rbound;   // B x H x 2    raw disparity interval of the road test per row
     uint8_t* lbits;     // B x 4 x 16 x W   network decisions on the bands (pruned search)
     int32_t* prune;     // B x 16       pruned-search state (LD_STATE_PRUNE layout)
@@ -773,7 +775,7 @@ __global__ __launch_bounds__(1024) void k_vdisp_fit(Dev d, const uint64_t* strea
             else if (tau_max <= 6) vdisp_dp<6, 2, L>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
             else vdisp_dp<8, 2, L>(myT, Hm, H, d_max, lam, tau_max, nwdp, bw, seam, E0);
         };
-        if (lockstep) dp(std::true_type{}); else dp(std::false_type{});
+        if (__builtin_expect(!lockstep, 1)) dp(std::false_type{}); else dp(std::true_type{});
         const int v0 = __builtin_amdgcn_readfirstlane(first_row(E0));
         // The walk, by wave 0: disparities from 0 are the last step and down, so a chunk's words of the
         // 64 rows from the path's present one hold its next eight steps (tau <= 8), a lane a row.
@@ -1272,6 +1274,13 @@ constexpr int kSeam = 8;             // LDS words of one end of a wave's row (fi
 constexpr int kNoVote = 0xFFFF;      // a staged edge without a vote column
 constexpr int kSharedVotes = 600;    // weighted edges a road row, times the waves, past which all vote
 
+constexpr bool back_rows_fit() {     // the backtrace's words of a row in the even ones of its W words
+    for (int W = 8; W <= 4096; ++W)
+        if (2 * ((2 * W + kFitCols - 1) / kFitCols) > W / 2 * 2) return false;
+    return true;
+}
+static_assert(back_rows_fit(), "the row DP's backtrace fits the q buffer's rows");
+
 __host__ __device__ constexpr int vpx_fit_waves(int W2) { return (W2 + kFitCols * kWave - 1) / (kFitCols * kWave); }
 
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void k_vpx_fit(Dev d, int stage_cap) {
@@ -1424,7 +1433,8 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
         ahead(R - 2 - chi, R - 1 + chi);
     }
     // backtrace: the ranks of a thread's columns in two words, at the start of the q buffer's row
-    // of W words (k_energy and k_m1 write that buffer later)
+    // of W words (rounded down to an even one, so perhaps from the last word of the frame before, where no
+    // backtrace lies)
     const int L = (W2 + K - 1) / K;                            // threads with a column
     uint2* back = reinterpret_cast<uint2*>(d.qbuf + ((int64_t)b * H * W & ~(int64_t)1));
     const int64_t pitch = W / 2;

@@ -18,9 +18,9 @@
 // reads as its partner's, so an image's ring, column sums, block sums and variances are formed
 // once for both maps.  The 2 rho + 1 image rows of both images sit in LDS rings (one new row
 // per step into the slot of the row that leaves, fetched from HBM while the row before it is
-// matched), stored word-interleaved (word g
-// of all slots together) so that a block's words are constant offsets from one address; the
-// sum of products takes the rows in slot order for both blocks, which leaves it unchanged.  The
+// matched), stored word-interleaved (word g of all slots together) so that a block's words are
+// constant offsets from one address; the sum of products takes the rows in slot order for both
+// blocks, which leaves it unchanged.  The
 // column sums over the ring follow each new row incrementally, the block sums of a row come
 // from the column sums four columns a thread, and the block variances are kept per column as
 // integers with their FP32 reciprocal roots.  A candidate costs its 2 rho + 1 rows of byte dot
@@ -28,11 +28,12 @@
 // candidates); the quotient in FP64 is formed only for two candidates whose FP32 values are
 // within 2e-6 of each other, some ten times the rounding of those (1 ulp of the root, half of the
 // conversion and of the product), so the choice is the FP64 one.  The FP64 division and roots of
-// every candidate were a tenth of the sweep (512 pairs of 1242 x 375: 11.0 -> 9.9 ms).  A pixel with a matched neighbour below scores
-// its few propagated candidates (up to three runs) in one loop of its own lane; a pixel without
-// one (every pixel of the first row) searches all of 1..d_max, which would hold up the 63 other
-// lanes of its wave, so such pixels are queued: many (the first row) are taken one a lane, few
-// one a wave with a candidate per lane and a reduction over the wave.  The propagation makes
+// every candidate were a tenth of the sweep (512 pairs of 1242 x 375: 11.0 -> 9.9 ms).  A pixel
+// with a matched neighbour below scores its few propagated candidates (up to three runs) in one
+// loop of its own lane; a pixel without one (every pixel of the first row) searches all of
+// 1..d_max, which would hold up the 63 other lanes of its wave, so such pixels are queued: many
+// (the first row) are taken one a lane, few one a wave with a candidate per lane and a reduction
+// over the wave.  The propagation makes
 // the rows of a frame sequential; frames are independent workgroups.  Launches of few frames
 // (stereo_form; up to 112 of 1242 x 375) take the same maps in strips of columns and blocks of rows,
 // k_stereo_strip, a launch per block of rows (1 pair: 5.15 -> 0.68 ms, 32: 5.3 -> 1.6 ms).
@@ -607,7 +608,7 @@ __global__ __launch_bounds__(E* LP) void k_stereo_strip(const uint8_t* left, int
         }
         // the best of the pixel's lanes: pairs, quads, then (both quads of eight lanes each hold
         // one value) the mirror of eight
-        static_assert(LP == 1 || LP == 2 || LP == 4 || LP == 8, "lanes a pixel");
+        static_assert(LP == 4 || LP == 8, "lanes a pixel");
         auto merge = [&](auto ctl) {
             constexpr int C = decltype(ctl)::value;
             Best c;
@@ -616,9 +617,9 @@ __global__ __launch_bounds__(E* LP) void k_stereo_strip(const uint8_t* left, int
             c.d = __builtin_amdgcn_update_dpp(0, best.d, C, 0xF, 0xF, true);
             keep(c, (c.d != 0) & (c.d != best.d));
         };
-        if constexpr (LP >= 2) merge(std::integral_constant<int, 0xB1>{});     // quad_perm 1 0 3 2
-        if constexpr (LP >= 4) merge(std::integral_constant<int, 0x4E>{});     // quad_perm 2 3 0 1
-        if constexpr (LP >= 8) merge(std::integral_constant<int, 0x141>{});    // row_half_mirror
+        merge(std::integral_constant<int, 0xB1>{});                            // quad_perm 1 0 3 2
+        merge(std::integral_constant<int, 0x4E>{});                            // quad_perm 2 3 0 1
+        if constexpr (LP == 8) merge(std::integral_constant<int, 0x141>{});    // row_half_mirror
         if (sub == 0) {
             cur[p + 1] = best.d;
             if (p >= T - 1 && p < T - 1 + G::kUse && u < W) out[(int64_t)v * W + u] = (uint8_t)best.d;
