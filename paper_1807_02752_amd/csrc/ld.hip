@@ -1272,7 +1272,6 @@ __device__ void vpx_fit_tail(Dev& d, int b, FrameInfo fi, int* PX, int* PY, int*
 constexpr int kFitCols = 10;         // columns a thread
 constexpr int kSeam = 8;             // LDS words of one end of a wave's row (five used)
 constexpr int kNoVote = 0xFFFF;      // a staged edge without a vote column
-constexpr int kSharedVotes = 600;    // weighted edges a road row, times the waves, past which all vote
 
 constexpr bool back_rows_fit() {     // the backtrace's words of a row in the even ones of its W words
     for (int W = 8; W <= 4096; ++W)
@@ -1334,13 +1333,15 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
     // A frame with many edges would wait for the one wave that keeps the counts, which moves each vote
     // twice (once for either parity) and reads what is not staged from memory: there all the waves
     // share the votes of one row of counts, with a second barrier a row, and nothing is staged.  An
-    // edge that is not staged counts as five, and the more waves share the sooner it pays (us, one
-    // wave and shared, by edges a row and of them not staged; 1242 wide: 55, 0: 265, 301; 111, 0:
-    // 342, 321; 181, 0: 433, 400; 1024 frames 28, 4: 532, 538; 55, 31: 721, 644; 181, 156: 1561, 760;
-    // 320 wide: 287, 0: 175, 185; 1024 frames 287, 108: 329, 302; 1920 x 540: 271, 151: 1400, 774;
-    // 1778, 1658: 8900, 1670; there every thread kept counts before: 1242 wide 402 to 445, 1024 frames
-    // 685 to 835, 1920 x 540 622 and 1370).
-    const bool shared_votes = __builtin_expect((roff[R] + 4 * max(roff[R] - stage_cap, 0)) * nw > kSharedVotes * R, 0);
+    // edge that is not staged counts as seven, and more waves to share pay sooner, up to one a SIMD
+    // (us, one wave and shared, by edges a row and of them not staged; 1242 wide, four waves of
+    // columns: 55, 0: 272, 301; 111, 0: 382, 367; 181, 0: 514, 402; 1024 frames 28, 4: 528, 538; 55, 31:
+    // 721, 644; 181, 156: 1561, 760; 641 wide, three: 180, 0: 309, 293; 320 wide, one: 287, 0: 205, 194;
+    // 176, 0: 132, 157; 1920 x 1080, six: 512 frames 49, 11: 830, 1196; 1920 x 540: 271, 151: 1400, 774; 1778,
+    // 1658: 8900, 1670; there every thread kept counts before: 1242 wide 402 to 445, 1024 frames 685 to 835,
+    // 1920 x 540 622 and 1370).
+    const int dense = nw <= 4 ? 100 * nw + 180 : 220 * nw;
+    const bool shared_votes = __builtin_expect((roff[R] + 6 * max(roff[R] - stage_cap, 0)) * nw > dense * R, 0);
     int nv = 0;   // votes that landed in a column
     for (int r0 = wave * kStageRows; r0 < R && !shared_votes; r0 += (nw + 1) * kStageRows) {
         const int mine = roff[min(r0 + lane, R)];              // lane l: the offset of row r0 + l
