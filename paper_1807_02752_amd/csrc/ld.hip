@@ -1333,15 +1333,18 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
     // A frame with many edges would wait for the one wave that keeps the counts, which moves each vote
     // twice (once for either parity) and reads what is not staged from memory: there all the waves
     // share the votes of one row of counts, with a second barrier a row, and nothing is staged.  An
-    // edge that is not staged counts as seven, and more waves to share pay sooner, up to one a SIMD
-    // (us, one wave and shared, by edges a row and of them not staged; 1242 wide, four waves of
-    // columns: 55, 0: 272, 301; 111, 0: 382, 367; 181, 0: 514, 402; 1024 frames 28, 4: 528, 538; 55, 31:
-    // 721, 644; 181, 156: 1561, 760; 641 wide, three: 180, 0: 309, 293; 320 wide, one: 287, 0: 205, 194;
-    // 176, 0: 132, 157; 1920 x 1080, six: 512 frames 49, 11: 830, 1196; 1920 x 540: 271, 151: 1400, 774; 1778,
-    // 1658: 8900, 1670; there every thread kept counts before: 1242 wide 402 to 445, 1024 frames 685 to 835,
-    // 1920 x 540 622 and 1370).
-    const int dense = nw <= 4 ? 100 * nw + 180 : 220 * nw;
-    const bool shared_votes = __builtin_expect((roff[R] + 6 * max(roff[R] - stage_cap, 0)) * nw > dense * R, 0);
+    // edge that is not staged counts as five, and the line lies the higher the more waves meet at that
+    // barrier; with one of columns, two share the votes and so gain little (us, one wave and shared, by
+    // edges a row and of them not staged; 320 x 96, one: 121, 0: 96, 91; 176, 0: 127, 127; 1024 frames 155,
+    // 176; 287, 110: 304, 199; 512 x 160, two: 96, 0: 144, 138; 512 frames 157, 173; 141, 0: 199, 172;
+    // 641 x 240, three: 89, 0: 177, 207; 143, 0: 258, 208; 1024 frames 61, 13: 312, 380; 71, 23: 376, 382; 1242 x
+    // 375, four: 89, 0: 270, 326; 116, 0: 318, 327; 179, 0: 442, 323; 1024 frames 26, 3: 290, 365; 44, 21: 654, 628;
+    // 89, 66: 875, 640; 1536 x 400, five: 107, 0: 339, 426; 143, 0: 413, 432; 1024 frames 53, 22: 1065, 997; 1920 x
+    // 1080, six: 71, 12: 1020, 1158; 89, 31: 1218, 1145; 1778, 1720: 11400, 2290; 2560 x 400, eight: 124, 0: 348,
+    // 458; 512 frames 88, 42: 696, 678; 4096 x 256, thirteen: 197, 15: 353, 424; 287, 105: 530, 425; there every thread
+    // kept counts before: 1242 wide 413, 1024 frames 750, 1920 x 1080 1230 to 2750).
+    const int dense = nw == 1 ? 200 : max(120, 28 * nw);
+    const bool shared_votes = __builtin_expect(roff[R] + 4 * max(roff[R] - stage_cap, 0) > dense * R, 0);
     int nv = 0;   // votes that landed in a column
     for (int r0 = wave * kStageRows; r0 < R && !shared_votes; r0 += (nw + 1) * kStageRows) {
         const int mine = roff[min(r0 + lane, R)];              // lane l: the offset of row r0 + l
@@ -1378,10 +1381,7 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
         }
     };
     // a road row's edge in memory
-    auto edge_of = [&](int r, int i) -> int {
-        const int e = fedges[(int64_t)(v_h + r) * W + i].bin;
-        return e >= 0 ? e : kNoVote;
-    };
+    auto edge_of = [&](int r, int i) -> int { return (uint16_t)fedges[(int64_t)(v_h + r) * W + i].bin; };
     // the votes of road rows r0 .. r1
     auto vote_rows = [&](int* to, int r0, int r1, int x) {
         for (int r = r0; r <= r1; ++r) {
@@ -1396,9 +1396,12 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
     for (int r = max(R - 2 - chi, 0) + wave; r <= min(R - 2 + chi, R - 1) && !shared_votes; r += nw + 1)
         vote_rows(hist + ((v_max & 1) ^ 1) * WP, r, r, 1);
     // Shared votes: from the band of road row r + 1 to that of row r, one row enters and one leaves
-    // (rows outside the road hold nothing).  A thread's first edge of either is read a row ahead, the
-    // others two of either row at a time; the loops are the workgroup's, so that the votes are
-    // counted a wave at a time (nvs) and take no register.
+    // (rows outside the road hold nothing).  A thread's first edge of either is read a row ahead, as
+    // soon as the one before has been counted and into the same register, so that no wave waits for
+    // a copy of a load in flight (read before it, and compared when read: 1242 x 375 with 179 edges a
+    // row 449 us, now 323, 1920 x 1080 with 271 1532, now 1158); the others two of either row at a
+    // time.  The loops are the workgroup's, so that the votes are counted a wave at a time
+    // (nvs) and take no register.
     int nvs = 0, na = 0, nl = 0, enters = kNoVote, leaves = kNoVote;
     auto edges_of = [&](int r) { return r >= 0 && r < R ? __builtin_amdgcn_readfirstlane(roff[r + 1] - roff[r]) : 0; };
     auto ahead = [&](int ra, int rl) __attribute__((always_inline)) {
@@ -1413,20 +1416,19 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
         nvs += __popcll(__ballot(a != kNoVote));
     };
     auto move_band = [&](int ra, int rl) __attribute__((always_inline)) {
-        const int a0 = enters, l0 = leaves, ca = na, cl = nl;
-        ahead(ra - 1, rl - 1);
-        move(a0, l0);
-        for (int i0 = nt; i0 < max(ca, cl); i0 += 2 * nt) {
+        move(enters, leaves);
+        for (int i0 = nt; i0 < max(na, nl); i0 += 2 * nt) {
             int a[2], l[2];
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 const int i = i0 + q * nt + t;
-                a[q] = i < ca ? edge_of(ra, i) : kNoVote;
-                l[q] = i < cl ? edge_of(rl, i) : kNoVote;
+                a[q] = i < na ? edge_of(ra, i) : kNoVote;
+                l[q] = i < nl ? edge_of(rl, i) : kNoVote;
             }
 #pragma unroll
             for (int q = 0; q < 2; ++q) move(a[q], l[q]);
         }
+        ahead(ra - 1, rl - 1);
     };
     if (__builtin_expect(shared_votes, 0)) {
         ahead(R - 1, R);
